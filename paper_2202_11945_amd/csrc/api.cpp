@@ -68,6 +68,8 @@ struct Plan {
   Range idwt_res, fdwt_res, pg, gt, pt, upd;
   Range idwt_res4;          // the resident inverse levels in quarters (four tiles per layer)
   bool idwt_split = false;  // launch them instead of one workgroup per layer
+  Range idwt_dir;           // the inverse transform in one launch of output tiles
+  int dir_tile = 0;         // their side (0: the level-by-level kernels)
   Range sin;  // slopes input: 2 x 2 groups of the propagation stage's subaperture tiles
   Range sin_frame, pg_pol;  // a frame's slope input: open-loop problems / closed-loop problems
   Range aug;                // augmented PCG: vector-update chunks of the problems with augmentation
@@ -381,6 +383,28 @@ struct PtLists {
   }
 };
 
+// Side of the output tiles of the one-launch inverse transform: 64 once that
+// gives the chip more than one workgroup per CU, else 32 (four times the
+// workgroups; measured on 39 m problems, 24 tiles of 64 each: 7.0 against 10.4
+// us for one, 10.3 against 11.2 for 8, 15.9 against 15.4 for 16, 25.5 against
+// 20.1 for 32; the level-by-level kernels take 17.0, 18.7, 21.4 and 27.4), or 0
+// where a layer is smaller than a tile or has more levels than a tile can halve (or
+// fewer than kDirMinLevels): the level-by-level kernels then.
+constexpr long kDirTiles64 = 320;
+int dir_tile(const std::vector<const HostModel*>& models) {
+  bool ok32 = true, ok64 = true;
+  long tiles64 = 0;
+  for (const HostModel* m : models)
+    for (const LayerHost& lh : m->layers) {
+      const int n = lh.d.n, lv = lh.d.levels;
+      ok32 = ok32 && n >= 32 && lv >= kDirMinLevels && lv <= 5;
+      ok64 = ok64 && n >= 64 && lv >= kDirMinLevels && lv <= 6;
+      tiles64 += (long)(n / 64) * (n / 64);
+    }
+  if (ok64 && tiles64 >= kDirTiles64) return 64;
+  return ok32 ? 32 : 0;
+}
+
 // Byte-offset carving of the arena (256-byte aligned pieces).
 struct Carver {
   size_t off = 0;
@@ -445,6 +469,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   P.pt_rows = pt_rows;
   P.pt_split = pt_split != 0;
   P.idwt_split = split == 4;
+  P.dir_tile = dir_tile(models);
   P.nprob = (int)models.size();
   P.models = models;
   HIP_TRY(hipSetDevice(device));
@@ -467,6 +492,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   std::vector<ProbLayout> lay(P.nprob);
   Carver cv;
   std::vector<Tile> t_sin, t_sinf, t_pgpol, t_aug, t_r64gt;
+  std::vector<Tile> t_idwt_dir;
   std::vector<Tile> t_idwt_res, t_idwt_res4, t_fdwt_res, t_pg, t_gt, t_pt, t_upd, t_sinit, t_gprior, t_ghgt, t_r64wfs,
       t_r64pt;
   HatTables hats;  // hat tables and band records of every problem and fitting view, one set per plan
@@ -679,6 +705,9 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       // transform tiles carry the global layer index (mask), so that the
       // layer and problem records load in parallel
       t_idwt_res.push_back({k, l, 0, 0, 0, 0, pd.layer0 + l, 0});
+      const int td = P.dir_tile > 0 ? P.hL[pd.layer0 + l].n / P.dir_tile : 0;
+      for (int ty = 0; ty < td; ++ty)
+        for (int tx = 0; tx < td; ++tx) t_idwt_dir.push_back({k, l, ty, tx, 0, 0, pd.layer0 + l, 0});
       for (int q = 0; q < 4; ++q) t_idwt_res4.push_back({k, l, 0, q, 0, 0, pd.layer0 + l, 0});
       t_fdwt_res.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
     }
@@ -993,6 +1022,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   };
   P.idwt_res = add(t_idwt_res);
   P.idwt_res4 = add(t_idwt_res4);
+  P.idwt_dir = add(t_idwt_dir);
   P.fdwt_res = add(t_fdwt_res);
   P.pg = add(t_pg);
   P.sin = add(t_sin);
@@ -1380,6 +1410,10 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
 const Tile* T(const Plan& P, const Range& r) { return P.dT + r.off; }
 
 void enq_idwt(const Plan& P, const LaunchArgs& a, int src, int out, int iter) {
+  if (P.dir_tile > 0) {
+    launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, P.dir_tile, src, out, iter);
+    return;
+  }
   if (P.idwt_split)
     launch_idwt_res4(a, T(P, P.idwt_res4), P.idwt_res4.n, src, out, iter);
   else
@@ -2731,7 +2765,10 @@ fewha_status fewha_batch_time_stage(fewha_batch* b, int stage, int reps, double*
   auto run = [&]() {
     switch (stage) {
       case FEWHA_STAGE_IDWT_RES:
-        if (P.idwt_split) {
+        if (P.dir_tile > 0) {
+          launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, P.dir_tile, SRC_PUPD, OUT_PHI, it);
+          wg = P.idwt_dir.n;
+        } else if (P.idwt_split) {
           launch_idwt_res4(a, T(P, P.idwt_res4), P.idwt_res4.n, SRC_PUPD, OUT_PHI, it);
           wg = P.idwt_res4.n;
         } else {
@@ -2741,7 +2778,7 @@ fewha_status fewha_batch_time_stage(fewha_batch* b, int stage, int reps, double*
         break;
       case FEWHA_STAGE_IDWT_GLOB:
         wg = 0;
-        for (size_t st = 0; st < P.idwt_glob.size(); ++st) {
+        for (size_t st = 0; P.dir_tile == 0 && st < P.idwt_glob.size(); ++st) {
           launch_idwt_glob(a, T(P, P.idwt_glob[st]), P.idwt_glob[st].n, SRC_PUPD, OUT_PHI, it, (int)st);
           wg += P.idwt_glob[st].n;
         }

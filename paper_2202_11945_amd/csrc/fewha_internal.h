@@ -34,6 +34,7 @@ constexpr int kBandMax = pt_band(3, kBandRows);  // corner rows of the widest ba
 constexpr int kWideMaxK = 6;
 constexpr int pt_band_wide(int K) { return K == 4 ? 10 : (K == 5 ? 13 : 15); }
 constexpr int kBandWideMax = pt_band_wide(kWideMaxK);
+constexpr int kDirMinLevels = 3;  // levels of the layers that the one-launch inverse transform takes
 constexpr int kUpdChunk = 2048;   // coefficients per workgroup of the vector update
 constexpr int kDotRing = 256;     // PCG iterations whose inner products are kept (ring, power of two)
 constexpr int kGradChunk = 2048;  // coefficients per workgroup of the prior-term reductions

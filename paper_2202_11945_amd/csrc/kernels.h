@@ -53,6 +53,8 @@ struct LaunchArgs {
 };
 
 void launch_idwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter);
+// the whole inverse transform in one launch of T x T output tiles (tile = T = 32 or 64)
+void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode, int iter);
 // the resident inverse levels over four workgroups per (problem, layer): tile.tx = quadrant
 void launch_idwt_res4(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter);
 void launch_idwt_glob(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter,

@@ -1068,6 +1068,301 @@ __global__ __launch_bounds__(256) void k_idwt_glob2(const ProbDev* P, const Laye
     idwt_glob_tile(P, LD, IO, t, F, src_mode, out_mode, iter, step, A, B);
 }
 
+// ------------------------------------------- inverse DWT, all levels per tile
+// One launch for the whole transform: a T x T output tile (T = 32 or 64)
+// synthesizes, from the deepest level up, just the windows that it needs.
+// Level j (1 the finest, of output side n) takes a w(j) x w(j) window of each
+// of its bands: the tile's own (T >> j) coefficients per direction and a(j)
+// before them (6 taps; the halo settles at 4), indices periodic.  Every
+// coefficient of the windows is loaded in one round; the levels are short
+// runs in LDS.  Each p_k entry is stored by the tile whose own coefficients
+// hold it.  The sums are those of the level-by-level kernels, in the same
+// order.
+//
+// Bound: a chain of memory round trips (tile, records, coefficients) and two
+// barriers per level for few tiles, the windows' loads for many.  T = 32
+// loads 1.69 coefficients per output, T = 64 1.30, with a quarter of the
+// workgroups (see dir_tile in api.cpp for the choice).
+template <int T>
+struct DirWin {
+  static constexpr int kLevels = T == 64 ? 6 : 5;
+  static constexpr int a(int j) {
+    int v = 2;
+    for (int i = 1; i < j; ++i) v = (v + 1) / 2 + 2;
+    return v;
+  }
+  static constexpr int w(int j) { return (T >> j) + a(j); }
+  static constexpr int stride(int j) { return 2 * w(j) + 1; }
+  static constexpr int pairs(int j) { return w(j) - 2; }  // output pairs per direction of level j
+  // the first output of level j + 1 lies before level j's window when a(j) is odd
+  static constexpr int drop(int j) { return a(j) & 1; }
+  // level j's window in LDS, one word before it (the dropped output of its row 0)
+  static constexpr int base(int j) {
+    int o = 1;
+    for (int i = 1; i < j; ++i) o += 2 * w(i) * stride(i) + 1;
+    return o;
+  }
+  static constexpr int words() { return base(kLevels + 1); }
+  // pairs of a run: about 4, the runs of a line of nearly equal length
+  static constexpr int runs(int j) { return (pairs(j) + 3) / 4; }
+  static constexpr int run(int j) { return (pairs(j) + runs(j) - 1) / runs(j); }
+};
+
+// Window entries of level J in registers: the three detail bands, and from
+// level 3 on (kDirMinLevels) the coarse band, taken when J is the deepest.
+template <int T, int J, int NT>
+struct DirLoads {
+  static constexpr int kBands = J >= kDirMinLevels ? 4 : 3;
+  static constexpr int kR = (kBands * DirWin<T>::w(J) * DirWin<T>::w(J) + NT - 1) / NT;
+  CoefLoad v[kR];
+  DirLoads<T, J + 1, NT> next;
+};
+template <int NT>
+struct DirLoads<32, 6, NT> {};
+template <int NT>
+struct DirLoads<64, 7, NT> {};
+
+// Entry e of level J's window: LDS position, position in the coefficient
+// vector, and whether it is the tile's own.
+template <int T, int J>
+__device__ __forceinline__ int dir_entry(int e, int n, int off, int ty, int tx, int& lds, bool& own) {
+  using W = DirWin<T>;
+  constexpr int w = W::w(J), a = W::a(J);
+  const int half = n >> J;
+  const int b = e / (w * w), i = e - b * (w * w);  // bands (y, x): (0, 1), (1, 0), (1, 1), coarse (0, 0)
+  const int iy = i / w, ix = i - iy * w;
+  const int by = b == 1 || b == 2, bx = b == 0 || b == 2;
+  lds = W::base(J) + (by * w + iy) * W::stride(J) + bx * w + ix;
+  own = iy >= a && ix >= a;
+  return off + (by * half + (((T >> J) * ty - a + iy) & (half - 1))) * n + bx * half +
+         (((T >> J) * tx - a + ix) & (half - 1));
+}
+
+// NOPS operands per coefficient: the plain source; r, J^{-1}; or r, J^{-1}, p_{k-1}.
+template <int NOPS>
+__device__ __forceinline__ CoefLoad dir_load(const CoefPtrs& p, int e) {
+  CoefLoad v{p.a[e], 0.f, 0.f};
+  if (NOPS > 1) v.b = p.b[e];
+  if (NOPS > 2) v.c = p.c[e];
+  return v;
+}
+template <int NOPS>
+__device__ __forceinline__ float dir_finish(const PSrc& s, int e, const CoefLoad& v, bool own) {
+  if (NOPS == 1) return v.a;
+  const float z = v.a * v.b;
+  const float p = NOPS == 2 ? z : fmaf(s.beta, v.c, z);
+  if (own) ((gptr_w)s.pnew)[e] = p;
+  return p;
+}
+
+template <int T, int J, int NT, int NOPS>
+__device__ __forceinline__ void dir_fetch(const CoefPtrs& cp, int n, int levels, int off, const Tile& t,
+                                          DirLoads<T, J, NT>& L) {
+  using W = DirWin<T>;
+  if constexpr (J < W::kLevels) dir_fetch<T, J + 1, NT, NOPS>(cp, n, levels, off, t, L.next);
+  const int jj = min(J, levels);  // a level past the deepest loads from the deepest one's place, unused
+  const int ne = (J == levels ? 4 : 3) * W::w(J) * W::w(J);
+#pragma unroll
+  for (int u = 0; u < DirLoads<T, J, NT>::kR; ++u) {
+    int lds;
+    bool own;
+    const int pos = dir_entry<T, J>(min((int)threadIdx.x + u * NT, ne - 1), n, off, t.ty, t.tx, lds, own);
+    L.v[u] = dir_load<NOPS>(cp, jj == J ? pos : off);
+  }
+}
+template <int T, int J, int NT, int NOPS>
+__device__ __forceinline__ void dir_place(const PSrc& ps, int n, int levels, int off, const Tile& t,
+                                          const DirLoads<T, J, NT>& L, float* A) {
+  using W = DirWin<T>;
+  if (J > levels) return;
+  if constexpr (J < W::kLevels) dir_place<T, J + 1, NT, NOPS>(ps, n, levels, off, t, L.next, A);
+  const int ne = (J == levels ? 4 : 3) * W::w(J) * W::w(J);
+#pragma unroll
+  for (int u = 0; u < DirLoads<T, J, NT>::kR; ++u) {
+    const int e = threadIdx.x + u * NT;
+    int lds;
+    bool own;
+    const int pos = dir_entry<T, J>(e, n, off, t.ty, t.tx, lds, own);
+    if (e < ne) A[lds] = dir_finish<NOPS>(ps, pos, L.v[u], own);
+  }
+}
+
+// A run of NP synthesis output pairs, as syn_run, with the rounding of every
+// sum fixed by explicit multiply-adds: six products added in turn, of which
+// the first to be rounded by itself is that of the second tap (K1) or of the
+// first.  Which of the two depends on the level's output side alone, as in
+// the level-by-level kernels at the default resident side (a long PCG run
+// carries a different rounding into its fifth digit): see syn_order.
+template <int NP, bool K1>
+__device__ __forceinline__ void syn_run_fixed(const float* a_src, const float* d_src, int S, int base, const Filter& F,
+                                              float* dst, int ds) {
+  float a[NP + 2], d[NP + 2];
+#pragma unroll
+  for (int i = 0; i < NP + 2; ++i) {
+    a[i] = a_src[(base + i) * S];
+    d[i] = d_src[(base + i) * S];
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float v = K1 ? F.h[2 + q] * a[p + 1] : F.h[q] * a[p + 2];
+      v = K1 ? fmaf(F.h[q], a[p + 2], v) : fmaf(F.h[2 + q], a[p + 1], v);
+      v = fmaf(F.h[4 + q], a[p], v);
+      v = fmaf(F.g[q], d[p + 2], v);
+      v = fmaf(F.g[2 + q], d[p + 1], v);
+      v = fmaf(F.g[4 + q], d[p], v);
+      dst[(2 * p + q) * ds] = v;
+    }
+}
+
+// Levels J .. 2: columns of the window into B, rows into the coarse band of level J - 1.
+template <int T, int J, bool K1>
+__device__ __forceinline__ void dir_columns(const Filter& F, const float* A, float* B) {
+  using W = DirWin<T>;
+  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J);
+  for (int task = threadIdx.x; task < 2 * w * NR; task += blockDim.x) {
+    const int c = task % (2 * w), p0 = min((task / (2 * w)) * R, W::pairs(J) - R);
+    syn_run_fixed<R, K1>(A + W::base(J) + c, A + W::base(J) + w * S + c, S, p0, F, B + 2 * p0 * S + c, S);
+  }
+  __syncthreads();
+}
+template <int T, int J, bool K1>
+__device__ __forceinline__ void dir_level(const Filter& F, float* A, float* B) {
+  using W = DirWin<T>;
+  dir_columns<T, J, K1>(F, A, B);
+  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J), up = W::w(J - 1), d = W::drop(J - 1);
+  for (int task = threadIdx.x; task < up * NR; task += blockDim.x) {
+    const int r = task % up, p0 = min((task / up) * R, W::pairs(J) - R);
+    const float* Br = B + (r + d) * S;
+    syn_run_fixed<R, K1>(Br, Br + w, 1, p0, F, A + W::base(J - 1) + r * W::stride(J - 1) + 2 * p0 - d, 1);
+  }
+  __syncthreads();
+}
+template <int T, int J>
+__device__ __forceinline__ void dir_levels(int n, int levels, const Filter& F, float* A, float* B) {
+  using W = DirWin<T>;
+  if constexpr (J < W::kLevels) dir_levels<T, J + 1>(n, levels, F, A, B);
+  if (J > levels) return;
+  if (J > 3 && n >> (J - 1) <= 4)
+    dir_level<T, J, true>(F, A, B);
+  else
+    dir_level<T, J, false>(F, A, B);
+}
+
+// Four consecutive outputs from position e on (16-byte stores where the
+// caller's pointers allow: vec).
+struct OutLoad4 {
+  v4f a, ap;
+};
+__device__ __forceinline__ OutLoad4 out_fetch4(const OutDst& d, int e) {
+  OutLoad4 o{v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+  // a_prev and a lie in the 16-byte aligned state at multiples of 4 (F = I)
+  if (d.mode == OUTD_CONTROL || d.mode == OUTD_CLOSED) o.a = *(gptr_f4)(d.a + e);
+  if (d.mode == OUTD_CLOSED) o.ap = *(gptr_f4)(d.aprev + e);
+  return o;
+}
+__device__ __forceinline__ void put4(gptr_w p, int e, const v4f& v, bool vec) {
+  if (vec) {
+    *(gptr_w4)(p + e) = v;
+  } else {
+    p[e] = v.x;
+    p[e + 1] = v.y;
+    p[e + 2] = v.z;
+    p[e + 3] = v.w;
+  }
+}
+__device__ __forceinline__ void out_finish4(const OutDst& d, int e, const v4f& v, const OutLoad4& o, bool vec) {
+  if (d.mode == OUTD_PHI) {
+    *(gptr_w4)(d.phi + e) = v;
+  } else if (d.mode == OUTD_USER) {
+    put4(d.out, e, v, vec);
+  } else if (d.mode == OUTD_FITTED) {
+    *(gptr_w4)(d.phi + e) = v;
+    if (d.layers_out) put4(d.layers_out, e, v, vec);
+  } else {
+    if (d.layers_out) put4(d.layers_out, e, v, vec);
+    v4f nw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      nw[i] = d.mode == OUTD_CLOSED ? o.a[i] + d.gain * (v[i] - o.ap[i]) : (1.0f - d.gain) * o.a[i] + d.gain * v[i];
+    *(gptr_w4)(d.aprev + e) = o.a;
+    *(gptr_w4)(d.a + e) = nw;
+    if (d.dm_out) put4(d.dm_out, e, nw, vec);
+  }
+}
+
+// The window's coefficients into LDS.
+template <int T, int NT, int NOPS>
+__device__ __forceinline__ void dir_window(const ProbDev& pr, int n, int levels, int off, const Tile& t, PSrc& ps,
+                                           int iter, float* A) {
+  const CoefPtrs cp = coef_ptrs(ps);
+  DirLoads<T, 1, NT> L;
+  if (NOPS == 3) {
+    BetaLoads<2> bl;
+    beta_issue<2>(pr, SRC_PUPD, iter, bl);
+    dir_fetch<T, 1, NT, NOPS>(cp, n, levels, off, t, L);
+    ps.beta = beta_reduce<2>(SRC_PUPD, bl);
+  } else {
+    dir_fetch<T, 1, NT, NOPS>(cp, n, levels, off, t, L);
+  }
+  dir_place<T, 1, NT, NOPS>(ps, n, levels, off, t, L, A);
+}
+
+// The finest level: columns, then rows four outputs per task straight to the output.
+template <int T, int NT, bool K1>
+__device__ __forceinline__ void dir_finest(const OutDst& od, int off, int n, const Tile& t, const Filter& F,
+                                           float inv_delta, bool vec, float* A, float* B) {
+  using W = DirWin<T>;
+  constexpr int w = W::w(1), S = W::stride(1), kQ = T / 4, kO = T * kQ / NT;
+  static_assert(T * kQ % NT == 0, "whole rounds of output quadruples");
+  OutLoad4 o[kO];
+#pragma unroll
+  for (int u = 0; u < kO; ++u) {
+    const int q = threadIdx.x + u * NT;
+    o[u] = out_fetch4(od, off + (t.ty * T + q / kQ) * n + t.tx * T + 4 * (q % kQ));
+  }
+  dir_columns<T, 1, K1>(F, A, B);
+#pragma unroll
+  for (int u = 0; u < kO; ++u) {
+    const int q = threadIdx.x + u * NT, r = q / kQ, c = q % kQ;
+    const float* Br = B + r * S;
+    float x[4];
+    syn_run_fixed<2, K1>(Br, Br + w, 1, 2 * c, F, x, 1);
+    out_finish4(od, off + (t.ty * T + r) * n + t.tx * T + 4 * c,
+                v4f{x[0] * inv_delta, x[1] * inv_delta, x[2] * inv_delta, x[3] * inv_delta}, o[u], vec);
+  }
+}
+
+template <int T, int NT>
+__global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
+                                                 const Tile* tiles, Filter F, int src_mode, int out_mode, int iter) {
+  __shared__ float A[DirWin<T>::words()];
+  __shared__ float B[T * DirWin<T>::stride(1)];
+  const Tile t = my_tile(tiles);
+  const ProbDev& pr = P[t.prob];
+  const LayerDev& ly = LD[t.mask];
+  const IoDev& io = IO[t.prob];
+  PSrc ps = make_psrc(pr, io, src_mode, iter, 0.f);
+  // every record field before the first store (a store could alias the records)
+  const int n = ly.n, off = ly.off, levels = ly.levels;
+  const float inv_delta = ly.inv_delta;
+  const OutDst od = out_dst(pr, io, out_mode);
+  const bool vec = (((uintptr_t)io.out | (uintptr_t)io.layers_out | (uintptr_t)io.dm_out) & 15) == 0;
+  if (ps.mode == SRC_PUPD)
+    dir_window<T, NT, 3>(pr, n, levels, off, t, ps, iter, A);
+  else if (ps.mode == SRC_PUPD0)
+    dir_window<T, NT, 2>(pr, n, levels, off, t, ps, iter, A);
+  else
+    dir_window<T, NT, 1>(pr, n, levels, off, t, ps, iter, A);
+  __syncthreads();
+  dir_levels<T, 2>(n, levels, F, A, B);
+  if (n > kResMax)
+    dir_finest<T, NT, true>(od, off, n, t, F, inv_delta, vec, A, B);
+  else
+    dir_finest<T, NT, false>(od, off, n, t, F, inv_delta, vec, A, B);
+}
+
 // ------------------------------------------------ forward DWT, one global level
 // Input side m = 2^t.level (> the resident side); output 16x16 coefficients of each of
 // the four quadrants per tile; input window 36x36 (2k .. 2k+5 per output).
@@ -3118,6 +3413,14 @@ void launch_idwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int src
     k_idwt_res<64><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
   else
     k_idwt_res<128><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
+}
+void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode,
+                     int iter) {
+  if (ntiles <= 0) return;
+  if (tile == 64)
+    k_idwt_dir<64, 256><<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
+  else
+    k_idwt_dir<32, 256><<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
 }
 void launch_idwt_res4(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter) {
   if (ntiles <= 0) return;

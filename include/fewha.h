@@ -431,9 +431,11 @@ FEWHA_API void fewha_batch_destroy(fewha_batch* b);
  * (else FEWHA_EINVAL when the plan is built).
  * pt_split: 1 = the propagation adjoint's tiles are 4 node rows x 64
  * columns and each tile's sensor list is split over its 4 waves (sensor i
- * to wave i mod 4, the partial sums added in a fixed order), a quarter of
- * the serial chain of sensors per wave; for launches with few tiles, such
- * as one problem's frame.  Needs pt_rows 0 or 4.  0 = default (off).
+ * to wave i mod 4, every sensor's sums added in sensor order, so the values
+ * are bitwise those of unsplit tiles), a quarter of the serial chain of
+ * sensors per wave; for launches with few tiles, such as one problem's
+ * frame.  Needs pt_rows 0 or 4.  0 = default: split where the launch has few
+ * tiles.
  * glob_fuse: 1 = a layer with two or more global levels (side above twice
  * dwt_resident) runs its last two inverse levels in one launch: each output
  * tile synthesizes the part of the inner level it needs itself (about 27 %

@@ -50,6 +50,7 @@ struct Plan {
   int pt_rows = 4;        // node rows per thread of the propagation adjoint (tuning)
   bool pt_wide = false;   // some (sensor, layer) pair has K > 3 corners per node (wide band records)
   bool pt_split = false;  // propagation-adjoint tiles of one band record, sensors split over the waves
+  bool fit_split = false; // the same for the fitting step's DM grids
   bool glob_fuse = false; // some inverse global tiles run a layer's last two levels (k_idwt_glob2)
   std::vector<const HostModel*> models;
   void* arena = nullptr;
@@ -405,6 +406,15 @@ int dir_tile(const std::vector<const HostModel*>& models) {
   return ok32 ? 32 : 0;
 }
 
+// Split propagation-adjoint tiles (one band record, the sensors over the
+// waves) up to this many of them, where the chip has fewer than 16
+// workgroups of them per CU and a launch lasts as long as its longest sensor
+// chain; measured on 39 m problems, 384 split tiles each, against unsplit
+// tiles: 3.8 against 7.3 us for one, 5.6 against 8.0 for 8, 9.2 against 9.0
+// for 16, 16.3 against 12.1 for 32; one 37 m problem (six corners per node
+// and axis) 5.0 against 11.2.  The values are bitwise the same.
+constexpr long kPtSplitTiles = 4096;
+
 // Byte-offset carving of the arena (256-byte aligned pieces).
 struct Carver {
   size_t off = 0;
@@ -449,9 +459,18 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
     err = "tuning: four workgroups per layer need every layer's resident side >= 16 and >= 2 (n >> levels)";
     return FEWHA_EINVAL;
   }
-  // node rows of a propagation-adjoint tile, and its band records per wave
-  const int kPtH = pt_split ? kBandRows : 4 * pt_rows;
-  const int pt_recs = pt_split ? 1 : pt_rows;
+  // propagation-adjoint tiles, split or not: on request, or while split tiles are few
+  long split_tiles = 0, fit_split_tiles = 0;
+  auto tiles_of = [](int n) { return (long)cdiv(n, kBandRows) * cdiv(n, kPtW); };
+  for (const HostModel* m : models) {
+    for (const LayerHost& lh : m->layers) split_tiles += tiles_of(lh.d.n);
+    for (const fewha_dm_desc& dm : m->fit.dms) fit_split_tiles += tiles_of(dm.n_act);
+  }
+  const bool split_pt = pt_split || (pt_rows == 4 && split_tiles <= kPtSplitTiles);
+  const bool split_fit = pt_split || (pt_rows == 4 && fit_split_tiles <= kPtSplitTiles);
+  // node rows of a tile, and its band records per wave
+  const int kPtH = split_pt ? kBandRows : 4 * pt_rows, kFitH = split_fit ? kBandRows : 4 * pt_rows;
+  const int pt_recs = split_pt ? 1 : pt_rows, fit_recs = split_fit ? 1 : pt_rows;
   for (const HostModel* m : models)
     for (const LayerHost& lh : m->layers)
       if ((lh.d.n >> lh.d.levels) > res) {
@@ -467,7 +486,8 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   P.device = device;
   P.res_max = res;
   P.pt_rows = pt_rows;
-  P.pt_split = pt_split != 0;
+  P.pt_split = split_pt;
+  P.fit_split = split_fit;
   P.idwt_split = split == 4;
   P.dir_tile = dir_tile(models);
   P.nprob = (int)models.size();
@@ -987,13 +1007,13 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
         }
     for (int q = 0; q < nd; ++q) {
       const int na = f.dms[q].n_act;
-      for (int ty = 0; ty < cdiv(na, kPtH); ++ty)
+      for (int ty = 0; ty < cdiv(na, kFitH); ++ty)
         for (int tx = 0; tx < cdiv(na, kPtW); ++tx) {  // the directions that add to the tile
           std::vector<int> use;
           for (int d = 0; d < K; ++d)
-            if (pair_meets_tile(fl.glp[(size_t)d * nd + q], hats, na, ty * kPtH, kPtH, tx * kPtW, kPtW))
+            if (pair_meets_tile(fl.glp[(size_t)d * nd + q], hats, na, ty * kFitH, kFitH, tx * kPtW, kPtW))
               use.push_back(d);
-          const auto li = ptl.add(fl.glp, nd, q, use, na, ty, tx, pt_recs);
+          const auto li = ptl.add(fl.glp, nd, q, use, na, ty, tx, fit_recs);
           if (li.first < 0) {
             err = "more than 63 fitting directions";
             return FEWHA_EINVAL;
@@ -1478,12 +1498,14 @@ void enq_frame_body(const Plan& P, const LaunchArgs& a, int iters, bool refresh)
   launch_aug_store(a, T(P, P.aug), P.aug.n, iters);  // the next frame's W and A W
   enq_idwt(P, a, SRC_STATE_C, OUT_FIT, 0);
   if (P.fit_cg.n > 0) {  // DM fitting: CG on (sum_k B_k^T M B_k + eps I) a = sum_k B_k^T M P_k phi
+    LaunchArgs f = a;
+    f.pt_split = P.fit_split ? 1 : 0;
     launch_fit_fwd(a, T(P, P.fit_fwdL), P.fit_fwdL.n);
-    launch_pT(a, T(P, P.fit_pt), P.fit_pt.n, PT_PHIADJ);
+    launch_pT(f, T(P, P.fit_pt), P.fit_pt.n, PT_PHIADJ);
     launch_fit_cg(a, P.dF, P.fit_cg.n, FIT_INIT);
     for (int k = 0; k < P.max_fit_iters; ++k) {
       launch_fit_fwd(a, T(P, P.fit_fwdD), P.fit_fwdD.n);
-      launch_pT(a, T(P, P.fit_pt), P.fit_pt.n, PT_PHIADJ);
+      launch_pT(f, T(P, P.fit_pt), P.fit_pt.n, PT_PHIADJ);
       launch_fit_cg(a, P.dF, P.fit_cg.n, FIT_ITER);
     }
     launch_fit_cg(a, P.dF, P.fit_cg.n, FIT_FINAL);

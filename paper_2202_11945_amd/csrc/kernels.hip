@@ -2385,13 +2385,33 @@ __device__ __forceinline__ BandHdr load_hdr(const BandRec* rec) {
   return BandHdr{p[0], p[1], p[2]};
 }
 
-// One band row, K corners per lane: raw buffer loads with the lane's column
-// offset vo (from the column hat) and the wave-uniform row offset off.
+// One band row, K consecutive corners per lane: raw buffer loads of up to four
+// words (4-byte aligned, as buffer loads need no more) with the lane's column
+// offset vo (from the column hat) and the wave-uniform row offset off.  One
+// load per corner had the kernel bound by the texture-address rate.
 template <int K>
 __device__ __forceinline__ void pt_row(__amdgpu_buffer_rsrc_t rs, int vo, int off, float v[K]) {
+  constexpr int W = K < 4 ? K : 4;
+  if constexpr (W == 2) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b64(rs, vo, off, 0);
+    v[0] = __uint_as_float(x[0]);
+    v[1] = __uint_as_float(x[1]);
+  } else if constexpr (W == 3) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b96(rs, vo, off, 0);
 #pragma unroll
-  for (int b = 0; b < K; ++b)
-    v[b] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, vo + b * (int)sizeof(float), off, 0));
+    for (int b = 0; b < 3; ++b) v[b] = __uint_as_float(x[b]);
+  } else {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, off, 0);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v[b] = __uint_as_float(x[b]);
+  }
+  constexpr int at = 4 * (int)sizeof(float);
+  if constexpr (K == 5) v[4] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, vo + at, off, 0));
+  if constexpr (K == 6) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b64(rs, vo + at, off, 0);
+    v[4] = __uint_as_float(x[0]);
+    v[5] = __uint_as_float(x[1]);
+  }
 }
 
 // One band record with step pattern PAT: the band rows that its node rows
@@ -2565,9 +2585,12 @@ __device__ __forceinline__ void pt_sensor_wide(const float* vsens, int nc, const
 // WIDE: the instantiation with the wide-pair path (more registers), launched
 // only for plans that have wide pairs.  SPLIT (RPT = kBandRows): a tile is one
 // band record's kBandRows node rows x 64 columns, and its sensor list is
-// split over the 4 waves (sensor i to wave i mod 4), whose sums are added in
-// LDS in wave order: a quarter of the serial sensor chain per wave, for
-// launches with few tiles (single frames).
+// split over the 4 waves (sensor i to wave i mod 4): a quarter of the serial
+// sensor chain per wave, for launches with few tiles.  Every sensor's sums
+// go to LDS by themselves (kSplitRounds sensors per wave between barriers)
+// and are added in sensor order, so a split tile's values are bitwise those
+// of an unsplit one and the plan may take either (kPtSplitTiles in api.cpp).
+constexpr int kSplitRounds = 4;
 template <int RPT, bool WIDE, bool SPLIT>
 __global__ __launch_bounds__(256) void k_pT(const ProbDev* P, const LayerDev* LD, const WfsDev* WD, const IoDev* IO,
                                             const Tile* tiles, const HatEnt* __restrict__ hats, int n_hats,
@@ -2648,23 +2671,35 @@ __global__ __launch_bounds__(256) void k_pT(const ProbDev* P, const LayerDev* LD
   BandHdr hd, hdn;
   constexpr int step = SPLIT ? 4 : 1;
   const int i0 = SPLIT ? wv : 0;
+  __shared__ float red[SPLIT ? kSplitRounds * 4 : 1][SPLIT ? kBandRows : 1][SPLIT ? 64 : 1];
+  float sum = 0.f;  // SPLIT: node row p0 + wv
   fetch(ent(min(i0, ne)), hx, hd);
-  for (int i = i0; i < ne; i += step) {
-    fetch(ent(min(i + step, ne)), hxn, hdn);  // issued first: the waits for this sensor's loads cover it
-    sensor(ent(i), hx, hd);
-    hx = hxn;
-    hd = hdn;
+  for (int r0 = 0; r0 < ne; r0 += SPLIT ? 4 * kSplitRounds : ne) {
+    const int rn = SPLIT ? min(ne - r0, 4 * kSplitRounds) : ne;
+    for (int i = r0 + i0; i < r0 + rn; i += step) {
+      fetch(ent(min(i + step, ne)), hxn, hdn);  // issued first: the waits for this sensor's loads cover it
+      sensor(ent(i), hx, hd);
+      hx = hxn;
+      hd = hdn;
+      if constexpr (SPLIT) {
+#pragma unroll
+        for (int u = 0; u < kBandRows; ++u) {
+          red[i - r0][u][lane] = acc[u];
+          acc[u] = 0.f;
+        }
+      }
+    }
+    if constexpr (SPLIT) {
+      __syncthreads();
+      for (int i = 0; i < rn; ++i) sum += red[i][wv][lane];
+      if (r0 + rn < ne) __syncthreads();
+    }
   }
   const IoDev& io = IO[t.prob];
   const gptr_w dst = (gptr_w)((mode == PT_USER) ? io.out : pr.phiadj);
   if constexpr (SPLIT) {
-    __shared__ float red[4][kBandRows][64];
-#pragma unroll
-    for (int u = 0; u < kBandRows; ++u) red[wv][u][lane] = acc[u];
-    __syncthreads();
     const int p = p0 + wv;  // wave w stores node row p0 + w
-    if (q < n && p < n)
-      dst[loff + p * n + q] = ((red[0][wv][lane] + red[1][wv][lane]) + red[2][wv][lane]) + red[3][wv][lane];
+    if (q < n && p < n) dst[loff + p * n + q] = sum;
   } else if (q < n) {
 #pragma unroll
     for (int u = 0; u < RPT; ++u) {

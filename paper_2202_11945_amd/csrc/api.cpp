@@ -71,6 +71,10 @@ struct Plan {
   bool idwt_split = false;  // launch them instead of one workgroup per layer
   Range idwt_dir;           // the inverse transform in one launch of output tiles
   int dir_tile = 0;         // their side (0: the level-by-level kernels)
+  Range fdwt_dir, fdwt_tail;  // the first three forward levels in one launch of input tiles, and the
+                              // layers with deeper levels (the rest in one workgroup each)
+  int fdir_tile = 0;        // side of the input tiles (0: the level-by-level kernels)
+  int fres_max = kResMax;   // largest block that the forward transform leaves to one workgroup
   Range sin;  // slopes input: 2 x 2 groups of the propagation stage's subaperture tiles
   Range sin_frame, pg_pol;  // a frame's slope input: open-loop problems / closed-loop problems
   Range aug;                // augmented PCG: vector-update chunks of the problems with augmentation
@@ -406,6 +410,28 @@ int dir_tile(const std::vector<const HostModel*>& models) {
   return ok32 ? 32 : 0;
 }
 
+// The same for the forward transform's three levels per launch, whose larger
+// tile pays earlier (39 m problems, 24 tiles of 64 each: 5.3 against 5.8 us for
+// one, 6.4 against 5.9 for 4, 7.8 against 6.1 for 8, 20.3 against 11.6 for 32,
+// the rest of the levels 4.2 to 4.4 us more; the level-by-level kernels take
+// 15.0 in all for one, 15.9 for 8, 19.8 for 32).  A layer needs three levels
+// and leaves at most kResMax x kResMax to one workgroup.
+constexpr long kFwdTiles64 = 64;
+int fdir_tile(const std::vector<const HostModel*>& models) {
+  bool ok32 = true, ok64 = true;
+  long tiles64 = 0;
+  for (const HostModel* m : models)
+    for (const LayerHost& lh : m->layers) {
+      const int n = lh.d.n;
+      const bool ok = lh.d.levels >= 3 && n / 8 <= kResMax;
+      ok32 = ok32 && ok && n >= 32;
+      ok64 = ok64 && ok && n >= 64;
+      tiles64 += (long)(n / 64) * (n / 64);
+    }
+  if (ok64 && tiles64 >= kFwdTiles64) return 64;
+  return ok32 ? 32 : 0;
+}
+
 // Split propagation-adjoint tiles (one band record, the sensors over the
 // waves) up to this many of them, where the chip has fewer than 16
 // workgroups of them per CU and a launch lasts as long as its longest sensor
@@ -425,6 +451,13 @@ struct Carver {
     return o;
   }
 };
+
+// Scratch floats of a layer: the global levels' coarse blocks, or the
+// coarse block after three forward levels.
+int tmp_words(const LayerDev& ld, bool fdir) {
+  const int glob = ld.n > ld.res ? ld.n * ld.n / 4 : 0;
+  return std::max(glob, fdir ? ld.n * ld.n / 64 : 0);
+}
 
 fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models, int device, int res,
                         int pt_rows, int split, int pt_split, int glob_fuse, std::string& err) {
@@ -490,6 +523,8 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   P.fit_split = split_fit;
   P.idwt_split = split == 4;
   P.dir_tile = dir_tile(models);
+  P.fdir_tile = fdir_tile(models);
+  P.fres_max = P.fdir_tile > 0 ? 1 : 0;
   P.nprob = (int)models.size();
   P.models = models;
   HIP_TRY(hipSetDevice(device));
@@ -512,7 +547,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   std::vector<ProbLayout> lay(P.nprob);
   Carver cv;
   std::vector<Tile> t_sin, t_sinf, t_pgpol, t_aug, t_r64gt;
-  std::vector<Tile> t_idwt_dir;
+  std::vector<Tile> t_idwt_dir, t_fdwt_dir, t_fdwt_tail;
   std::vector<Tile> t_idwt_res, t_idwt_res4, t_fdwt_res, t_pg, t_gt, t_pt, t_upd, t_sinit, t_gprior, t_ghgt, t_r64wfs,
       t_r64pt;
   HatTables hats;  // hat tables and band records of every problem and fitting view, one set per plan
@@ -553,8 +588,11 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       ld.res = std::min(ld.n, res);
       ld.off = m.layer_off[l];
       ld.n_glob_levels = ilog2i(ld.n / ld.res);
+      ld.fres = P.fdir_tile > 0 ? ld.n / 8 : ld.res;
+      ld.fsteps = P.fdir_tile > 0 ? 1 : ld.n_glob_levels;
+      P.fres_max = std::max(P.fres_max, ld.fres);
       ld.tmp_off = tmp_total;
-      if (ld.n > ld.res) tmp_total += ld.n * ld.n / 4;
+      tmp_total += tmp_words(ld, P.fdir_tile > 0);
       ld.inv_delta = (float)(1.0 / lh.delta);
       for (int j = 0; j < kMaxLevelsJ; ++j) {
         ld.alpha_d[j] = (float)(m.alpha * lh.dtab[j]);
@@ -700,7 +738,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
         // with glob_fuse a layer's first two global levels are one tile at
         // step 0 (its inner coarse block goes where step 1 would put it)
         const bool ffuse = glob_fuse && ld.n_glob_levels >= 2;
-        if (!(ffuse && s == 1))
+        if (P.fdir_tile == 0 && !(ffuse && s == 1))
           for (int ty = 0; ty < tq; ++ty)
             for (int tx = 0; tx < tq; ++tx)
               t_fdwt_glob[s].push_back({k, l, ty, tx, slot++, ilog2i(mf), pd.layer0 + l, (ffuse && s == 0) ? 1 : 0});
@@ -729,7 +767,15 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       for (int ty = 0; ty < td; ++ty)
         for (int tx = 0; tx < td; ++tx) t_idwt_dir.push_back({k, l, ty, tx, 0, 0, pd.layer0 + l, 0});
       for (int q = 0; q < 4; ++q) t_idwt_res4.push_back({k, l, 0, q, 0, 0, pd.layer0 + l, 0});
-      t_fdwt_res.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
+      if (P.fdir_tile == 0) {
+        t_fdwt_res.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
+      } else {
+        const LayerDev& ld = P.hL[pd.layer0 + l];
+        const int tf = ld.n / P.fdir_tile;
+        for (int ty = 0; ty < tf; ++ty)
+          for (int tx = 0; tx < tf; ++tx) t_fdwt_dir.push_back({k, l, ty, tx, slot++, 0, pd.layer0 + l, 0});
+        if (ld.levels > 3) t_fdwt_tail.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
+      }
     }
     pd.n_slots_fdwt = slot;
     const int nupd = cdiv(pd.n_c, kUpdChunk);
@@ -1043,6 +1089,8 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   P.idwt_res = add(t_idwt_res);
   P.idwt_res4 = add(t_idwt_res4);
   P.idwt_dir = add(t_idwt_dir);
+  P.fdwt_dir = add(t_fdwt_dir);
+  P.fdwt_tail = add(t_fdwt_tail);
   P.fdwt_res = add(t_fdwt_res);
   P.pg = add(t_pg);
   P.sin = add(t_sin);
@@ -1320,7 +1368,7 @@ fewha_status setup_noalloc(Plan& P, std::string& err) {
     size_t tmp = 4, sd = 4, vadj = 4, part = 4;
     for (int l = 0; l < pd.L; ++l) {
       const LayerDev& ld = P.hL[pd.layer0 + l];
-      if (ld.n > ld.res) tmp = std::max(tmp, sizeof(float) * (size_t)(ld.tmp_off + ld.n * ld.n / 4));
+      tmp = std::max(tmp, sizeof(float) * (size_t)(ld.tmp_off + tmp_words(ld, P.fdir_tile > 0)));
     }
     for (int g = 0; g < pd.G; ++g) {
       const WfsDev& wd = P.hW[pd.wfs0 + g];
@@ -1414,6 +1462,7 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
   a.F = P.F;
   a.stream = s;
   a.res_max = P.res_max;
+  a.fres_max = P.fres_max;
   a.pt_rows = P.pt_rows;
   a.pt_wide = P.pt_wide ? 1 : 0;
   a.pt_split = P.pt_split ? 1 : 0;
@@ -1441,7 +1490,13 @@ void enq_idwt(const Plan& P, const LaunchArgs& a, int src, int out, int iter) {
   for (size_t s = 0; s < P.idwt_glob.size(); ++s)
     launch_idwt_glob(a, T(P, P.idwt_glob[s]), P.idwt_glob[s].n, src, out, iter, (int)s);
 }
-void enq_fdwt(const Plan& P, const LaunchArgs& a, int epi, int iter) {
+// from_in: the caller's io.in instead of phiadj (three-level launch only)
+void enq_fdwt(const Plan& P, const LaunchArgs& a, int epi, int iter, bool from_in = false) {
+  if (P.fdir_tile > 0) {
+    launch_fdwt_dir(a, T(P, P.fdwt_dir), P.fdwt_dir.n, P.fdir_tile, epi, iter, from_in);
+    launch_fdwt_res(a, T(P, P.fdwt_tail), P.fdwt_tail.n, epi, iter);
+    return;
+  }
   for (size_t s = 0; s < P.fdwt_glob.size(); ++s)
     launch_fdwt_glob(a, T(P, P.fdwt_glob[s]), P.fdwt_glob[s].n, epi, iter, (int)s);
   launch_fdwt_res(a, T(P, P.fdwt_res), P.fdwt_res.n, epi, iter);
@@ -1883,44 +1938,60 @@ fewha_status run_solve(Plan& P, hipStream_t st, const std::vector<const float*>&
   return FEWHA_OK;
 }
 
-// phi = W^{-1} c = delta^{-1} W^T c per layer (inverse transform to a caller buffer).
-fewha_status run_winv(Plan& P, hipStream_t st, const std::vector<const float*>& in, const std::vector<float*>& out,
-                      std::string& err) {
-  std::vector<IoDev> io(P.nprob);
+// Does any input of a transform call share memory with any of its outputs?
+bool transforms_overlap(const Plan& P, const std::vector<const float*>& in, const std::vector<float*>& out) {
+  auto apart = [&](const float* a, long na, const float* b, long nb) { return a + na <= b || b + nb <= a; };
+  const float *i0 = in[0], *i1 = in[0], *o0 = out[0], *o1 = out[0];
   for (int k = 0; k < P.nprob; ++k) {
+    i0 = std::min(i0, in[k]);
+    i1 = std::max(i1, in[k] + P.hP[k].n_c);
+    o0 = std::min(o0, (const float*)out[k]);
+    o1 = std::max(o1, (const float*)out[k] + P.hP[k].n_c);
+  }
+  if (apart(i0, i1 - i0, o0, o1 - o0)) return false;
+  for (int k = 0; k < P.nprob; ++k)
+    for (int j = 0; j < P.nprob; ++j)
+      if (!apart(in[k], P.hP[k].n_c, out[j], P.hP[j].n_c)) return true;
+  return false;
+}
+
+// The transforms of caller buffers: phi = W^{-1} c = delta^{-1} W^T c per layer
+// (inverse), c = W^{-T} phi = delta^{-1} W phi (forward).  The tiles of one
+// launch read what others write, so a call whose outputs overlap its inputs
+// works from a copy (and so does the forward transform level by level, which
+// reads phiadj).
+fewha_status run_transform(Plan& P, hipStream_t st, bool forward, const std::vector<const float*>& in,
+                           const std::vector<float*>& out, std::string& err) {
+  std::vector<IoDev> io(P.nprob);
+  for (int k = 0; k < P.nprob; ++k)
     if (!in[k] || !out[k]) {
-      err = "apply_Winv: null pointer";
+      err = forward ? "apply_WinvT: null pointer" : "apply_Winv: null pointer";
       return FEWHA_EINVAL;
     }
-    io[k].in = in[k];
+  HIP_TRY(hipSetDevice(P.device));
+  const bool copy = (forward && P.fdir_tile == 0) || transforms_overlap(P, in, out);
+  for (int k = 0; k < P.nprob; ++k) {
+    if (copy)
+      HIP_TRY(hipMemcpyAsync(P.hP[k].phiadj, in[k], sizeof(float) * P.hP[k].n_c, hipMemcpyDeviceToDevice, st));
+    io[k].in = copy ? P.hP[k].phiadj : in[k];
     io[k].out = out[k];
   }
-  HIP_TRY(hipSetDevice(P.device));
   fewha_status s = upload_io(P, io, st, P.dIO, err);
   if (s != FEWHA_OK) return s;
-  enq_idwt(P, args(P, st, P.dIO), SRC_IN, OUT_USER, 0);
+  if (forward)
+    enq_fdwt(P, args(P, st, P.dIO), EPI_PLAIN, 0, true);
+  else
+    enq_idwt(P, args(P, st, P.dIO), SRC_IN, OUT_USER, 0);
   HIP_TRY(hipGetLastError());
   return FEWHA_OK;
 }
-
-// c = W^{-T} phi = delta^{-1} W phi per layer (forward transform of a caller buffer).
+fewha_status run_winv(Plan& P, hipStream_t st, const std::vector<const float*>& in, const std::vector<float*>& out,
+                      std::string& err) {
+  return run_transform(P, st, false, in, out, err);
+}
 fewha_status run_winvT(Plan& P, hipStream_t st, const std::vector<const float*>& in, const std::vector<float*>& out,
                        std::string& err) {
-  std::vector<IoDev> io(P.nprob);
-  HIP_TRY(hipSetDevice(P.device));
-  for (int k = 0; k < P.nprob; ++k) {
-    if (!in[k] || !out[k]) {
-      err = "apply_WinvT: null pointer";
-      return FEWHA_EINVAL;
-    }
-    HIP_TRY(hipMemcpyAsync(P.hP[k].phiadj, in[k], sizeof(float) * P.hP[k].n_c, hipMemcpyDeviceToDevice, st));
-    io[k].out = out[k];
-  }
-  fewha_status s = upload_io(P, io, st, P.dIO, err);
-  if (s != FEWHA_OK) return s;
-  enq_fdwt(P, args(P, st, P.dIO), EPI_PLAIN, 0);
-  HIP_TRY(hipGetLastError());
-  return FEWHA_OK;
+  return run_transform(P, st, true, in, out, err);
 }
 
 // Gradients of a loss of the layers phi = W^{-1} c*, c* = M^{-1} b, with respect to
@@ -2819,15 +2890,22 @@ fewha_status fewha_batch_time_stage(fewha_batch* b, int stage, int reps, double*
         break;
       case FEWHA_STAGE_FDWT_GLOB:
         wg = 0;
+        if (P.fdir_tile > 0) {
+          launch_fdwt_dir(a, T(P, P.fdwt_dir), P.fdwt_dir.n, P.fdir_tile, EPI_PCG, it, false);
+          wg = P.fdwt_dir.n;
+          break;
+        }
         for (size_t st = 0; st < P.fdwt_glob.size(); ++st) {
           launch_fdwt_glob(a, T(P, P.fdwt_glob[st]), P.fdwt_glob[st].n, EPI_PCG, it, (int)st);
           wg += P.fdwt_glob[st].n;
         }
         break;
-      case FEWHA_STAGE_FDWT_RES:
-        launch_fdwt_res(a, T(P, P.fdwt_res), P.fdwt_res.n, EPI_PCG, it);
-        wg = P.fdwt_res.n;
+      case FEWHA_STAGE_FDWT_RES: {
+        const Range& r = P.fdir_tile > 0 ? P.fdwt_tail : P.fdwt_res;
+        launch_fdwt_res(a, T(P, r), r.n, EPI_PCG, it);
+        wg = r.n;
         break;
+      }
       case FEWHA_STAGE_UPDATE:
         launch_update(a, T(P, P.upd), P.upd.n, it);
         wg = P.upd.n;

@@ -64,6 +64,8 @@ struct LayerDev {
   int off;                    // offset of the layer in N_c-sized vectors
   int tmp_off;                // offset of the layer's coarse-block scratch
   int n_glob_levels;          // levels with output side > kResMax
+  int fres, fsteps;           // forward transform: side of the block left to one workgroup, and the tiled
+                              // steps before it (0: read phiadj; else scratch, the step's parity)
   int pad0;
   float inv_delta;            // 1 / delta_l
   float alpha_d[kMaxLevelsJ]; // alpha * D_j, j = log2(block side)

@@ -38,6 +38,7 @@ struct LaunchArgs {
   Filter F;
   hipStream_t stream;
   int res_max;  // largest resident transform side of the plan (32, 64 or 128)
+  int fres_max; // ... of the forward transform
   const HatEnt* hats;     // hat tables of the propagation adjoint (plan-wide)
   int n_hats;             // entries of hats
   const BandRec* bands;   // band records of the propagation adjoint (plan-wide)
@@ -60,6 +61,9 @@ void launch_idwt_res4(const LaunchArgs& a, const Tile* tiles, int ntiles, int sr
 void launch_idwt_glob(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter,
                       int step);
 void launch_fdwt_glob(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter, int step);
+// the first three forward levels in one launch of T x T input tiles (tile = T = 32 or 64);
+// from_in: the input is the caller's io.in, else phiadj
+void launch_fdwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int epi, int iter, bool from_in);
 void launch_fdwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter);
 void launch_pgamma(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode);
 // compact slopes io.in -> slope buffer + tip/tilt partials; add = 1: added to the

@@ -21,6 +21,11 @@ typedef const float __attribute__((address_space(1)))* gptr_f;
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef const v4f __attribute__((address_space(1)))* gptr_f4;
 typedef v4f __attribute__((address_space(1)))* gptr_w4;
+// The same at any 4-byte alignment (callers' buffers); the memory
+// instructions are the same ones.
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+typedef const v4fu __attribute__((address_space(1)))* gptr_f4u;
+typedef v4fu __attribute__((address_space(1)))* gptr_w4u;
 // Stores and FP64 accesses likewise.  A flat access also counts against the
 // LDS / scalar-load wait counter, so a later LDS wait or barrier would wait
 // for it to reach memory.
@@ -1086,11 +1091,7 @@ __global__ __launch_bounds__(256) void k_idwt_glob2(const ProbDev* P, const Laye
 template <int T>
 struct DirWin {
   static constexpr int kLevels = T == 64 ? 6 : 5;
-  static constexpr int a(int j) {
-    int v = 2;
-    for (int i = 1; i < j; ++i) v = (v + 1) / 2 + 2;
-    return v;
-  }
+  static constexpr int a(int j) { return j == 1 ? 2 : j == 2 ? 3 : 4; }  // a(j + 1) = (a(j) + 1) / 2 + 2
   static constexpr int w(int j) { return (T >> j) + a(j); }
   static constexpr int stride(int j) { return 2 * w(j) + 1; }
   static constexpr int pairs(int j) { return w(j) - 2; }  // output pairs per direction of level j
@@ -1127,12 +1128,12 @@ struct DirLoads<64, 7, NT> {};
 template <int T, int J>
 __device__ __forceinline__ int dir_entry(int e, int n, int off, int ty, int tx, int& lds, bool& own) {
   using W = DirWin<T>;
-  constexpr int w = W::w(J), a = W::a(J);
+  constexpr int w = W::w(J), a = W::a(J), at = W::base(J), S = W::stride(J);
   const int half = n >> J;
   const int b = e / (w * w), i = e - b * (w * w);  // bands (y, x): (0, 1), (1, 0), (1, 1), coarse (0, 0)
   const int iy = i / w, ix = i - iy * w;
   const int by = b == 1 || b == 2, bx = b == 0 || b == 2;
-  lds = W::base(J) + (by * w + iy) * W::stride(J) + bx * w + ix;
+  lds = at + (by * w + iy) * S + bx * w + ix;
   own = iy >= a && ix >= a;
   return off + (by * half + (((T >> J) * ty - a + iy) & (half - 1))) * n + bx * half +
          (((T >> J) * tx - a + ix) & (half - 1));
@@ -1220,10 +1221,10 @@ __device__ __forceinline__ void syn_run_fixed(const float* a_src, const float* d
 template <int T, int J, bool K1>
 __device__ __forceinline__ void dir_columns(const Filter& F, const float* A, float* B) {
   using W = DirWin<T>;
-  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J);
+  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J), np = W::pairs(J), at = W::base(J);
   for (int task = threadIdx.x; task < 2 * w * NR; task += blockDim.x) {
-    const int c = task % (2 * w), p0 = min((task / (2 * w)) * R, W::pairs(J) - R);
-    syn_run_fixed<R, K1>(A + W::base(J) + c, A + W::base(J) + w * S + c, S, p0, F, B + 2 * p0 * S + c, S);
+    const int c = task % (2 * w), p0 = min((task / (2 * w)) * R, np - R);
+    syn_run_fixed<R, K1>(A + at + c, A + at + w * S + c, S, p0, F, B + 2 * p0 * S + c, S);
   }
   __syncthreads();
 }
@@ -1231,11 +1232,12 @@ template <int T, int J, bool K1>
 __device__ __forceinline__ void dir_level(const Filter& F, float* A, float* B) {
   using W = DirWin<T>;
   dir_columns<T, J, K1>(F, A, B);
-  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J), up = W::w(J - 1), d = W::drop(J - 1);
+  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J), np = W::pairs(J), up = W::w(J - 1);
+  constexpr int d = W::drop(J - 1), at = W::base(J - 1), SU = W::stride(J - 1);
   for (int task = threadIdx.x; task < up * NR; task += blockDim.x) {
-    const int r = task % up, p0 = min((task / up) * R, W::pairs(J) - R);
+    const int r = task % up, p0 = min((task / up) * R, np - R);
     const float* Br = B + (r + d) * S;
-    syn_run_fixed<R, K1>(Br, Br + w, 1, p0, F, A + W::base(J - 1) + r * W::stride(J - 1) + 2 * p0 - d, 1);
+    syn_run_fixed<R, K1>(Br, Br + w, 1, p0, F, A + at + r * SU + 2 * p0 - d, 1);
   }
   __syncthreads();
 }
@@ -1250,8 +1252,7 @@ __device__ __forceinline__ void dir_levels(int n, int levels, const Filter& F, f
     dir_level<T, J, false>(F, A, B);
 }
 
-// Four consecutive outputs from position e on (16-byte stores where the
-// caller's pointers allow: vec).
+// Four consecutive outputs from position e on.
 struct OutLoad4 {
   v4f a, ap;
 };
@@ -1262,33 +1263,23 @@ __device__ __forceinline__ OutLoad4 out_fetch4(const OutDst& d, int e) {
   if (d.mode == OUTD_CLOSED) o.ap = *(gptr_f4)(d.aprev + e);
   return o;
 }
-__device__ __forceinline__ void put4(gptr_w p, int e, const v4f& v, bool vec) {
-  if (vec) {
-    *(gptr_w4)(p + e) = v;
-  } else {
-    p[e] = v.x;
-    p[e + 1] = v.y;
-    p[e + 2] = v.z;
-    p[e + 3] = v.w;
-  }
-}
-__device__ __forceinline__ void out_finish4(const OutDst& d, int e, const v4f& v, const OutLoad4& o, bool vec) {
+__device__ __forceinline__ void out_finish4(const OutDst& d, int e, const v4f& v, const OutLoad4& o) {
   if (d.mode == OUTD_PHI) {
     *(gptr_w4)(d.phi + e) = v;
   } else if (d.mode == OUTD_USER) {
-    put4(d.out, e, v, vec);
+    *(gptr_w4u)(d.out + e) = v;
   } else if (d.mode == OUTD_FITTED) {
     *(gptr_w4)(d.phi + e) = v;
-    if (d.layers_out) put4(d.layers_out, e, v, vec);
+    if (d.layers_out) *(gptr_w4u)(d.layers_out + e) = v;
   } else {
-    if (d.layers_out) put4(d.layers_out, e, v, vec);
+    if (d.layers_out) *(gptr_w4u)(d.layers_out + e) = v;
     v4f nw;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       nw[i] = d.mode == OUTD_CLOSED ? o.a[i] + d.gain * (v[i] - o.ap[i]) : (1.0f - d.gain) * o.a[i] + d.gain * v[i];
     *(gptr_w4)(d.aprev + e) = o.a;
     *(gptr_w4)(d.a + e) = nw;
-    if (d.dm_out) put4(d.dm_out, e, nw, vec);
+    if (d.dm_out) *(gptr_w4u)(d.dm_out + e) = nw;
   }
 }
 
@@ -1312,7 +1303,7 @@ __device__ __forceinline__ void dir_window(const ProbDev& pr, int n, int levels,
 // The finest level: columns, then rows four outputs per task straight to the output.
 template <int T, int NT, bool K1>
 __device__ __forceinline__ void dir_finest(const OutDst& od, int off, int n, const Tile& t, const Filter& F,
-                                           float inv_delta, bool vec, float* A, float* B) {
+                                           float inv_delta, float* A, float* B) {
   using W = DirWin<T>;
   constexpr int w = W::w(1), S = W::stride(1), kQ = T / 4, kO = T * kQ / NT;
   static_assert(T * kQ % NT == 0, "whole rounds of output quadruples");
@@ -1330,7 +1321,7 @@ __device__ __forceinline__ void dir_finest(const OutDst& od, int off, int n, con
     float x[4];
     syn_run_fixed<2, K1>(Br, Br + w, 1, 2 * c, F, x, 1);
     out_finish4(od, off + (t.ty * T + r) * n + t.tx * T + 4 * c,
-                v4f{x[0] * inv_delta, x[1] * inv_delta, x[2] * inv_delta, x[3] * inv_delta}, o[u], vec);
+                v4f{x[0] * inv_delta, x[1] * inv_delta, x[2] * inv_delta, x[3] * inv_delta}, o[u]);
   }
 }
 
@@ -1348,7 +1339,6 @@ __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDe
   const int n = ly.n, off = ly.off, levels = ly.levels;
   const float inv_delta = ly.inv_delta;
   const OutDst od = out_dst(pr, io, out_mode);
-  const bool vec = (((uintptr_t)io.out | (uintptr_t)io.layers_out | (uintptr_t)io.dm_out) & 15) == 0;
   if (ps.mode == SRC_PUPD)
     dir_window<T, NT, 3>(pr, n, levels, off, t, ps, iter, A);
   else if (ps.mode == SRC_PUPD0)
@@ -1358,9 +1348,9 @@ __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDe
   __syncthreads();
   dir_levels<T, 2>(n, levels, F, A, B);
   if (n > kResMax)
-    dir_finest<T, NT, true>(od, off, n, t, F, inv_delta, vec, A, B);
+    dir_finest<T, NT, true>(od, off, n, t, F, inv_delta, A, B);
   else
-    dir_finest<T, NT, false>(od, off, n, t, F, inv_delta, vec, A, B);
+    dir_finest<T, NT, false>(od, off, n, t, F, inv_delta, A, B);
 }
 
 // ------------------------------------------------ forward DWT, one global level
@@ -1659,6 +1649,337 @@ __global__ __launch_bounds__(256) void k_fdwt_glob2(const ProbDev* P, const Laye
   }
 }
 
+// -------------------------------------- forward DWT, three levels per tile
+// One T x T input tile (T = 32 or 64) gives its (T >> j)^2 outputs of every
+// detail band of the first three levels, and of level 3's coarse band, from a
+// (T + 28)^2 window of the input: level j needs a window of W(j) coarse
+// values per direction, two per output of the level below and 4 more (6
+// taps).  Rows go straight from global loads to LDS (four output pairs per
+// task, 12 consecutive samples as three 16-byte loads); columns give the
+// next level's window and the details with their epilogue, whose PCG operand
+// is requested with the input.  Layers of three levels are done then; of
+// deeper ones the coarse block (side n / 8) goes to scratch for k_fdwt_res.
+// The sums are those of the level-by-level kernels, in the same order.
+//
+// Bound: memory round trips and five barriers for few tiles; for many the
+// window (3.5 samples per input at T = 32, 2.1 at 64) against a quarter of
+// the workgroups.
+template <int T>
+struct FwdWin {
+  static constexpr int D(int j) { return T >> j; }                     // detail outputs per direction
+  // coarse window (W(0): the input): W(3) = T / 8, W(j) = 2 W(j + 1) + 4
+  static constexpr int W(int j) { return (T >> j) + 4 * ((8 >> j) - 1); }
+  static constexpr int SR(int j) { return W(j) + D(j) + 1; }          // LDS stride of the row pass's output
+  static constexpr int SX(int j) { return W(j) + 1; }                 // ... of the coarse window
+  static constexpr int runs(int j) { return W(j) / 4; }               // runs of four pairs
+  // column tasks, each a column and a run of four pairs, in classes of whole
+  // waves: x-high columns (both halves in y are details), x-low columns
+  // under the tile (coarse and detail), the rest of the coarse window
+  static constexpr int det(int j) { return D(j) * D(j) / 4; }
+  static constexpr int pad(int n) { return (n + 63) / 64 * 64; }
+  static constexpr int at_low(int j) { return pad(det(j)); }
+  static constexpr int at_rest(int j) { return 2 * pad(det(j)); }
+  static constexpr int rest(int j) { return W(j) * runs(j) - det(j); }
+  static constexpr int rounds(int j, int nt) {
+    return ((rest(j) > 0 ? at_rest(j) + rest(j) : at_low(j) + det(j)) + nt - 1) / nt;
+  }
+};
+
+// Epilogue of one output from its unscaled sum a, with the rounding of the
+// level-by-level kernels fixed by explicit multiply-adds: M x and q round the
+// scaled sum and add the prior's term to it in one step; the warm restart's
+// b' - b takes the scaled sum rounded (global levels, input side over
+// kResMax) or in one step with b.
+template <int EPI>
+__device__ __forceinline__ void epi_put(const EpiDst& dst, int e, float ad, float a, float inv_delta, bool glob,
+                                        const EpiLoad& l, double& acc) {
+  float v = inv_delta * a;
+  asm("" : "+v"(v));  // kept as a value of its own
+  if (EPI == EPI_APPLYM) {
+    dst.out[e] = fmaf(ad, l.x0, v);
+  } else if (EPI == EPI_PCG) {
+    const float q = fmaf(ad, l.x0, v);
+    dst.q[e] = q;
+    acc += (double)l.x0 * (double)q;
+  } else if (EPI == EPI_RHS || EPI == EPI_RHSQ) {
+    const float d = glob ? v - l.x0 : fmaf(inv_delta, a, -l.x0);
+    const float r0 = EPI == EPI_RHS ? d + l.x1 : d;
+    dst.b[e] = v;
+    dst.r[e] = r0;
+    acc += (double)r0 * (double)r0 * (double)l.x2;
+  } else {
+    dst.out[e] = v;
+  }
+}
+// The epilogue's operands (as epi_fetch), their addresses read once.
+struct EpiSrc {
+  gptr_f x0, x1, x2;
+};
+template <int EPI>
+__device__ __forceinline__ EpiSrc epi_src(const ProbDev& pr, const IoDev& io, int iter) {
+  EpiSrc s{nullptr, nullptr, nullptr};
+  if (EPI == EPI_APPLYM) s.x0 = (gptr_f)io.in;
+  if (EPI == EPI_PCG) s.x0 = (gptr_f)p_loc(pr, iter);
+  if (EPI == EPI_RHS) {
+    s.x0 = (gptr_f)(io.state + pr.n_c);
+    s.x1 = (gptr_f)(io.state + 2L * pr.n_c);
+  }
+  if (EPI == EPI_RHSQ) s.x0 = (gptr_f)pr.q;
+  if (EPI == EPI_RHS || EPI == EPI_RHSQ) s.x2 = (gptr_f)pr.jinv;
+  return s;
+}
+template <int EPI>
+__device__ __forceinline__ EpiLoad epi_load(const EpiSrc& s, int e) {
+  EpiLoad l;  // what the epilogue does not read stays unset (and takes no registers)
+  if (EPI != EPI_PLAIN) l.x0 = s.x0[e];
+  if (EPI == EPI_RHS) l.x1 = s.x1[e];
+  if (EPI == EPI_RHS || EPI == EPI_RHSQ) l.x2 = s.x2[e];
+  return l;
+}
+
+// Four outputs from 12 samples: a_k = sum_i f_i x[2k + i].
+__device__ __forceinline__ void ana_run4(const float* x, const float* f, float* a) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    a[p] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) a[p] = fmaf(f[i], x[2 * p + i], a[p]);
+  }
+}
+
+// What a tile needs of its layer, read once.
+struct FwdTile {
+  int n, off, ty, tx;
+  float inv_delta;
+  float ad[3];  // alpha D of the detail bands of levels 1 .. 3
+  bool last;    // three levels: the coarse band takes the epilogue
+  gptr_w ll;    // else: scratch of side n / 8
+  EpiDst dst;
+};
+
+// The wave's place in a round of level J's column tasks: first task of the
+// wave (uniform), its class, this thread's column and run.
+enum { FWD_HIGH, FWD_LOW, FWD_REST, FWD_NONE };
+template <int T, int J, int NT>
+struct FwdTask {
+  int cls, c, r;
+  bool on;
+  __device__ __forceinline__ FwdTask(int u) {
+    using W = FwdWin<T>;
+    constexpr int D = W::D(J), D4 = D / 4;
+    const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63) + u * NT;
+    int e = w0 + ((int)threadIdx.x & 63);
+    cls = w0 < W::at_low(J) ? FWD_HIGH : w0 < W::at_rest(J) ? FWD_LOW : FWD_REST;
+    if (cls != FWD_REST) {
+      e -= cls == FWD_LOW ? W::at_low(J) : 0;
+      on = e < W::det(J);
+      c = e % D;
+      r = on ? e / D : 0;
+    } else {
+      // columns past the tile in its runs, then every column in the runs past it
+      constexpr int side = W::W(J) - D, first = side * D4;
+      e -= W::at_rest(J);
+      on = e < W::rest(J);
+      c = e < first ? D + e % (side > 0 ? side : 1) : (e - first) % W::W(J);
+      r = !on ? 0 : e < first ? e / (side > 0 ? side : 1) : D4 + (e - first) / W::W(J);
+    }
+  }
+  // the position of the task's first output in half (hy, hx) of the level
+  __device__ __forceinline__ int pos(const FwdTile& t, int hy, int hx) const {
+    constexpr int D = FwdWin<T>::D(J);
+    const int half = t.n >> J;
+    return t.off + (hy * half + D * t.ty + 4 * r) * t.n + hx * half + D * t.tx + c;
+  }
+};
+
+// Epilogue operands of level J's tasks (eight of an x-high task; of an x-low
+// one those of its details, and of the coarse band where it is the last).
+template <int T, int J, int NT>
+struct FwdOps {
+  static constexpr int kR = FwdWin<T>::rounds(J, NT);
+  EpiLoad l[kR][8];
+};
+template <int T, int J, int NT, int EPI>
+__device__ __forceinline__ void fwd_ops(const EpiSrc& src, const FwdTile& t, FwdOps<T, J, NT>& o) {
+  if (EPI == EPI_PLAIN) return;
+#pragma unroll
+  for (int u = 0; u < FwdOps<T, J, NT>::kR; ++u) {
+    if (u * NT >= FwdWin<T>::at_rest(J)) break;
+    const FwdTask<T, J, NT> k(u);
+    if (k.cls == FWD_HIGH) {
+      const int a = k.pos(t, 0, 1), d = k.pos(t, 1, 1);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        o.l[u][p] = epi_load<EPI>(src, a + p * t.n);
+        o.l[u][4 + p] = epi_load<EPI>(src, d + p * t.n);
+      }
+    } else if (k.cls == FWD_LOW) {
+      const int d = k.pos(t, 1, 0);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o.l[u][4 + p] = epi_load<EPI>(src, d + p * t.n);
+      if (J == 3 && t.last) {
+        const int a = k.pos(t, 0, 0);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) o.l[u][p] = epi_load<EPI>(src, a + p * t.n);
+      }
+    }
+  }
+}
+
+// Columns of level J from its row-pass output R: the coarse window for the
+// next level into X (J < 3), the details with their epilogue.
+template <int T, int J, int NT, int EPI>
+__device__ __forceinline__ void fwd_columns(const FwdTile& t, const Filter& F, const float* R, float* X,
+                                            const FwdOps<T, J, NT>& o, double& acc) {
+  using W = FwdWin<T>;
+  const bool glob = (t.n >> (J - 1)) > kResMax;
+#pragma unroll
+  for (int u = 0; u < FwdOps<T, J, NT>::kR; ++u) {
+    const FwdTask<T, J, NT> k(u);
+    if (!k.on) continue;
+    const float* col = R + 8 * k.r * W::SR(J) + (k.cls == FWD_HIGH ? W::W(J) : 0) + k.c;
+    float x[12], a[4], d[4];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) x[i] = col[i * W::SR(J)];
+    ana_run4(x, F.h, a);
+    if (k.cls == FWD_HIGH) {
+      ana_run4(x, F.g, d);
+      const int pa = k.pos(t, 0, 1), pd = k.pos(t, 1, 1);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        epi_put<EPI>(t.dst, pa + p * t.n, t.ad[J - 1], a[p], t.inv_delta, glob, o.l[u][p], acc);
+        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][4 + p], acc);
+      }
+      continue;
+    }
+    if constexpr (J < 3) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) X[(4 * k.r + p) * W::SX(J) + k.c] = a[p];
+    } else if (t.last) {
+      const int pa = k.pos(t, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) epi_put<EPI>(t.dst, pa + p * t.n, t.ad[2], a[p], t.inv_delta, glob, o.l[u][p], acc);
+    } else {
+      const int s = t.n >> 3;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) t.ll[(W::D(3) * t.ty + 4 * k.r + p) * s + W::D(3) * t.tx + k.c] = a[p];
+    }
+    if (k.cls == FWD_LOW) {
+      ana_run4(x, F.g, d);
+      const int pd = k.pos(t, 1, 0);
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][4 + p], acc);
+    }
+  }
+}
+
+// Rows of level J (2 or 3) from the coarse window X of level J - 1 into R.
+template <int T, int J>
+__device__ __forceinline__ void fwd_rows(const Filter& F, const float* X, float* R) {
+  using W = FwdWin<T>;
+  constexpr int NS = W::runs(J), up = W::W(J - 1);
+  for (int e = threadIdx.x; e < up * NS; e += blockDim.x) {
+    const int y = e % up, s = e / up;
+    float x[12], a[4], d[4];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) x[i] = X[y * W::SX(J - 1) + 8 * s + i];
+    ana_run4(x, F.h, a);
+    ana_run4(x, F.g, d);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      R[y * W::SR(J) + 4 * s + p] = a[p];
+      if (4 * s + p < W::D(J)) R[y * W::SR(J) + W::W(J) + 4 * s + p] = d[p];
+    }
+  }
+}
+
+template <int T, int NT, int EPI>
+__global__ __launch_bounds__(NT) void k_fdwt_dir(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
+                                                 const Tile* tiles, Filter F, int iter, int from_in) {
+  using W = FwdWin<T>;
+  __shared__ float R[W::W(0) * W::SR(1)];
+  __shared__ float X[W::W(1) * W::SX(1)];
+  __shared__ double sh[NT / 64];
+  // the deeper levels in the place of level 1's rows once these are used up
+  constexpr int at2 = W::W(1) * W::SR(2), at3 = at2 + W::W(2) * W::SX(2);
+  float *X2 = R + at2, *R3 = R + at3;
+  static_assert(W::W(1) * W::SR(2) + W::W(2) * W::SX(2) + W::W(2) * W::SR(3) <= W::W(0) * W::SR(1),
+                "the deeper levels fit the rows of level 1");
+  const Tile tile = my_tile(tiles);
+  const ProbDev& pr = P[tile.prob];
+  const LayerDev& ly = LD[tile.mask];
+  const IoDev& io = IO[tile.prob];
+  // every record field before the first store (a store could alias the records)
+  FwdTile t;
+  const int n = t.n = ly.n;
+  t.off = ly.off;
+  t.ty = tile.ty;
+  t.tx = tile.tx;
+  t.inv_delta = ly.inv_delta;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) t.ad[j] = ly.alpha_d[ly.log2n - 1 - j];
+  t.last = ly.levels == 3;
+  t.ll = (gptr_w)(pr.tmpa + ly.tmp_off);
+  t.dst = epi_dst(pr, io, iter);
+  const EpiSrc src = epi_src<EPI>(pr, io, iter);
+  double* const dots = pr.dots;
+  const int n_dots = pr.n_dots;
+  const gptr_f in = (gptr_f)((from_in ? io.in : pr.phiadj) + t.off);
+  double acc = 0.0;
+  // the input window, then (PCG) the epilogue operands of all three levels
+  constexpr int NS = W::runs(1), kTasks = W::W(0) * NS, kR = (kTasks + NT - 1) / NT;
+  float v[kR][12];
+#pragma unroll
+  for (int u = 0; u < kR; ++u) {
+    const int e = min((int)threadIdx.x + u * NT, kTasks - 1), y = e / NS, s = e % NS;
+    const gptr_f row = in + ((T * t.ty + y) & (n - 1)) * n;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const v4fu q = *(gptr_f4u)(row + ((T * t.tx + 8 * s + 4 * i) & (n - 1)));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[u][4 * i + k] = q[k];
+    }
+  }
+  FwdOps<T, 1, NT> o1;
+  FwdOps<T, 2, NT> o2;
+  FwdOps<T, 3, NT> o3;
+  fwd_ops<T, 1, NT, EPI>(src, t, o1);
+  if (EPI == EPI_PCG) {
+    fwd_ops<T, 2, NT, EPI>(src, t, o2);
+    fwd_ops<T, 3, NT, EPI>(src, t, o3);
+  }
+#pragma unroll
+  for (int u = 0; u < kR; ++u) {
+    const int e = threadIdx.x + u * NT, y = e / NS, s = e % NS;
+    if (e >= kTasks) break;
+    float a[4], d[4];
+    ana_run4(v[u], F.h, a);
+    ana_run4(v[u], F.g, d);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      R[y * W::SR(1) + 4 * s + p] = a[p];
+      if (4 * s + p < W::D(1)) R[y * W::SR(1) + W::W(1) + 4 * s + p] = d[p];
+    }
+  }
+  __syncthreads();
+  fwd_columns<T, 1, NT, EPI>(t, F, R, X, o1, acc);
+  if (EPI != EPI_PCG) fwd_ops<T, 2, NT, EPI>(src, t, o2);
+  __syncthreads();
+  fwd_rows<T, 2>(F, X, R);
+  __syncthreads();
+  fwd_columns<T, 2, NT, EPI>(t, F, R, X2, o2, acc);
+  if (EPI != EPI_PCG) fwd_ops<T, 3, NT, EPI>(src, t, o3);
+  __syncthreads();
+  fwd_rows<T, 3>(F, X2, R3);
+  __syncthreads();
+  fwd_columns<T, 3, NT, EPI>(t, F, R3, nullptr, o3, acc);
+  if (EPI == EPI_PCG || EPI == EPI_RHS || EPI == EPI_RHSQ) {
+    const double s = block_sum(acc, sh, NT);
+    if (threadIdx.x == 0) ((gptr_wd)dots)[(long)dot_group_of(EPI, iter) * n_dots + tile.slot] = s;
+  }
+}
+
 // ------------------------------------------------ forward DWT, resident part
 // One line of an analysis pass: output pairs K0 .. K0 + NP - 1 of a periodic
 // line of side m read at src[x str]:
@@ -1797,10 +2118,10 @@ __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const Layer
   const ProbDev& pr = P[t.prob];
   const LayerDev& ly = LD[t.mask];  // the global layer index, carried by the tile
   const IoDev& io = IO[t.prob];
-  const int n = ly.n, R = ly.res, lr = __builtin_ctz(R), off = ly.off;
+  const int n = ly.n, R = ly.fres, lr = __builtin_ctz(R), off = ly.off;
   constexpr int S = RMAX + 1;
   const int nt = blockDim.x;
-  const int ng = ly.n_glob_levels;
+  const int ng = ly.fsteps;
   const gptr_f in = (gptr_f)((ng == 0) ? pr.phiadj + off : ((((ng - 1) & 1) ? pr.tmpb : pr.tmpa) + ly.tmp_off));
   const int istride = (ng == 0) ? n : R;
   const int m0 = n >> ly.levels;
@@ -3491,11 +3812,30 @@ static void launch_fdwt_res_r(const LaunchArgs& a, const Tile* tiles, int ntiles
     default: k_fdwt_res<RMAX, EPI_PLAIN><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
   }
 }
+template <int T, int NT>
+static void launch_fdwt_dir_t(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter, int from_in) {
+#define FEWHA_FD(E) k_fdwt_dir<T, NT, E><<<ntiles, NT, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter, from_in)
+  switch (epi) {
+    case EPI_APPLYM: FEWHA_FD(EPI_APPLYM); break;
+    case EPI_PCG: FEWHA_FD(EPI_PCG); break;
+    case EPI_RHS: FEWHA_FD(EPI_RHS); break;
+    case EPI_RHSQ: FEWHA_FD(EPI_RHSQ); break;
+    default: FEWHA_FD(EPI_PLAIN); break;
+  }
+#undef FEWHA_FD
+}
+void launch_fdwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int epi, int iter, bool from_in) {
+  if (ntiles <= 0) return;
+  if (tile == 64)
+    launch_fdwt_dir_t<64, 512>(a, tiles, ntiles, epi, iter, from_in ? 1 : 0);
+  else
+    launch_fdwt_dir_t<32, 512>(a, tiles, ntiles, epi, iter, from_in ? 1 : 0);
+}
 void launch_fdwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter) {
   if (ntiles <= 0) return;
-  if (a.res_max <= 32)
+  if (a.fres_max <= 32)
     launch_fdwt_res_r<32>(a, tiles, ntiles, epi, iter);
-  else if (a.res_max <= 64)
+  else if (a.fres_max <= 64)
     launch_fdwt_res_r<64>(a, tiles, ntiles, epi, iter);
   else
     launch_fdwt_res_r<128>(a, tiles, ntiles, epi, iter);

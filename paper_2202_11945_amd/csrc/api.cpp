@@ -74,7 +74,7 @@ struct Plan {
   Range fdwt_dir, fdwt_tail;  // the first three forward levels in one launch of input tiles, and the
                               // layers with deeper levels (the rest in one workgroup each)
   int fdir_tile = 0;        // side of the input tiles (0: the level-by-level kernels)
-  int fres_max = kResMax;   // largest block that the forward transform leaves to one workgroup
+  int ires_max = 1, fres_max = 1;  // largest blocks of one workgroup, inverse and forward
   Range sin;  // slopes input: 2 x 2 groups of the propagation stage's subaperture tiles
   Range sin_frame, pg_pol;  // a frame's slope input: open-loop problems / closed-loop problems
   Range aug;                // augmented PCG: vector-update chunks of the problems with augmentation
@@ -415,19 +415,24 @@ int dir_tile(const std::vector<const HostModel*>& models) {
 // one, 6.4 against 5.9 for 4, 7.8 against 6.1 for 8, 20.3 against 11.6 for 32,
 // the rest of the levels 4.2 to 4.4 us more; the level-by-level kernels take
 // 15.0 in all for one, 15.9 for 8, 19.8 for 32).  A layer needs three levels
-// and leaves at most kResMax x kResMax to one workgroup.
+// and leaves at most kResMax x kResMax to one workgroup.  Layers of at most 64
+// x 64 with deeper levels are one launch of one workgroup per layer the other
+// way (5 layers of 64 x 64, four levels: 6.2 against 5.2 + 3.7 us).
 constexpr long kFwdTiles64 = 64;
 int fdir_tile(const std::vector<const HostModel*>& models) {
-  bool ok32 = true, ok64 = true;
+  bool ok32 = true, ok64 = true, small = true, deep = false;
   long tiles64 = 0;
   for (const HostModel* m : models)
     for (const LayerHost& lh : m->layers) {
       const int n = lh.d.n;
+      small = small && n <= 64;
+      deep = deep || lh.d.levels > 3;
       const bool ok = lh.d.levels >= 3 && n / 8 <= kResMax;
       ok32 = ok32 && ok && n >= 32;
       ok64 = ok64 && ok && n >= 64;
       tiles64 += (long)(n / 64) * (n / 64);
     }
+  if (small && deep) return 0;
   if (ok64 && tiles64 >= kFwdTiles64) return 64;
   return ok32 ? 32 : 0;
 }
@@ -524,7 +529,6 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   P.idwt_split = split == 4;
   P.dir_tile = dir_tile(models);
   P.fdir_tile = fdir_tile(models);
-  P.fres_max = P.fdir_tile > 0 ? 1 : 0;
   P.nprob = (int)models.size();
   P.models = models;
   HIP_TRY(hipSetDevice(device));
@@ -590,6 +594,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       ld.n_glob_levels = ilog2i(ld.n / ld.res);
       ld.fres = P.fdir_tile > 0 ? ld.n / 8 : ld.res;
       ld.fsteps = P.fdir_tile > 0 ? 1 : ld.n_glob_levels;
+      P.ires_max = std::max(P.ires_max, ld.res);
       P.fres_max = std::max(P.fres_max, ld.fres);
       ld.tmp_off = tmp_total;
       tmp_total += tmp_words(ld, P.fdir_tile > 0);
@@ -1461,7 +1466,7 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
   a.IO = io;
   a.F = P.F;
   a.stream = s;
-  a.res_max = P.res_max;
+  a.res_max = P.ires_max;
   a.fres_max = P.fres_max;
   a.pt_rows = P.pt_rows;
   a.pt_wide = P.pt_wide ? 1 : 0;

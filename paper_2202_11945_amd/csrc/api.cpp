@@ -29,6 +29,7 @@ constexpr int kMaxIters = 256;    // PCG iterations per reconstruct call (graph-
 constexpr int kMaxSolveIters = 1 << 24;  // PCG iterations of one solve
 constexpr int kSolveCheck = 16;   // iterations between two convergence checks of a solve
 constexpr int kMaxSweeps = 32;    // refinement sweeps of one solve
+static_assert(kSolveCheck == kDotRing, "a captured block of steps replays on the ring's own period");
 static_assert(sizeof(GradIo) <= sizeof(IoDev), "per-call tables share the staging ring");
 
 int ilog2i(int n) {
@@ -96,8 +97,10 @@ struct Plan {
   const int2* dGtr = nullptr;                // window rows of the Shack-Hartmann adjoint tiles
   const int2* dPgr = nullptr;                // tables of the propagation-stage tiles
   std::vector<float*> sstate;                // per problem: [x | unused | r] of a solve
-  double* rho_host = nullptr;                // pinned readback: 2 n_dots doubles per problem
-  std::vector<long> rho_off;
+  double* rho_host = nullptr;                // a solve's sums, one per problem (host-mapped pinned memory)
+  double* rho_dev = nullptr;                 // its device address
+  hipGraphExec_t solve_block = nullptr;      // kSolveCheck steps of a solve (after the first ones)
+  hipGraph_t solve_block_def = nullptr;
   int nprob_all = 0;                         // problems plus two fitting views per fitted problem
   FitDev* dF = nullptr;
   int max_fit_iters = 0;
@@ -133,7 +136,8 @@ struct Plan {
   bool coarse_ready = false;
   void* coarse_mem = nullptr;                // E^{-1}, indices, zc, slots, descriptors, tiles
   const CoarseDev* dC = nullptr;
-  const Tile* dCT = nullptr;
+  const CoarseTile* dCT = nullptr;
+  const CoarseDev* dCM = nullptr;            // records of its tiles' problems
   int n_coarse_tiles = 0;
   std::vector<int> coarse_m;                 // per problem: coarse unknowns (0: not corrected)
 };
@@ -146,6 +150,13 @@ struct Plan {
       return FEWHA_EDEVICE;                                                    \
     }                                                                          \
   } while (0)
+
+void drop_solve_block(Plan* p) {
+  if (p->solve_block) (void)hipGraphExecDestroy(p->solve_block);
+  if (p->solve_block_def) (void)hipGraphDestroy(p->solve_block_def);
+  p->solve_block = nullptr;
+  p->solve_block_def = nullptr;
+}
 
 void destroy_plan(Plan* p) {
   if (!p) return;
@@ -168,6 +179,7 @@ void destroy_plan(Plan* p) {
   if (p->t1) (void)hipEventDestroy(p->t1);
   if (p->rho_host) (void)hipHostFree(p->rho_host);
   if (p->numflag) (void)hipHostFree(p->numflag);
+  drop_solve_block(p);
   if (p->coarse_mem) (void)hipFree(p->coarse_mem);
   if (p->arena) (void)hipFree(p->arena);
   delete p;
@@ -1305,14 +1317,8 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
     HIP_TRY(hipHostMalloc((void**)&P.pinned[i], sizeof(IoDev) * P.nprob_all, hipHostMallocDefault));
     HIP_TRY(hipEventCreateWithFlags(&P.ev[i], hipEventDisableTiming));
   }
-  {
-    long tot = 0;
-    for (int k = 0; k < P.nprob; ++k) {
-      P.rho_off.push_back(tot);
-      tot += 2 * P.hP[k].n_dots;  // a dot group, or the residual pairs (2 per update slot)
-    }
-    HIP_TRY(hipHostMalloc((void**)&P.rho_host, sizeof(double) * std::max(tot, 1L), hipHostMallocDefault));
-  }
+  HIP_TRY(hipHostMalloc((void**)&P.rho_host, sizeof(double) * P.nprob, hipHostMallocMapped | hipHostMallocCoherent));
+  HIP_TRY(hipHostGetDevicePointer((void**)&P.rho_dev, P.rho_host, 0));
   HIP_TRY(hipStreamCreateWithFlags(&P.cap_stream, hipStreamNonBlocking));
   HIP_TRY(hipEventCreate(&P.t0));
   HIP_TRY(hipEventCreate(&P.t1));
@@ -1483,9 +1489,10 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
 
 const Tile* T(const Plan& P, const Range& r) { return P.dT + r.off; }
 
-void enq_idwt(const Plan& P, const LaunchArgs& a, int src, int out, int iter) {
+// C: p_k with the coarse-level correction (one-launch transform only)
+void enq_idwt(const Plan& P, const LaunchArgs& a, int src, int out, int iter, const CoarseDev* C = nullptr) {
   if (P.dir_tile > 0) {
-    launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, P.dir_tile, src, out, iter);
+    launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, P.dir_tile, src, out, iter, C);
     return;
   }
   if (P.idwt_split)
@@ -1572,22 +1579,13 @@ void enq_frame_body(const Plan& P, const LaunchArgs& a, int iters, bool refresh)
   }
 }
 
-// Fixed-order sum of dot group `grp` of every problem, read back to the host.
-fewha_status read_rho(Plan& P, hipStream_t st, int grp, int count_k, std::vector<double>& out, std::string& err) {
-  for (int k = 0; k < P.nprob; ++k) {
-    const ProbDev& pd = P.hP[k];
-    HIP_TRY(hipMemcpyAsync(P.rho_host + P.rho_off[k], pd.dots + (long)grp * pd.n_dots, sizeof(double) * pd.n_dots,
-                           hipMemcpyDeviceToHost, st));
-  }
-  HIP_TRY(hipStreamSynchronize(st));
-  out.assign(P.nprob, 0.0);
-  for (int k = 0; k < P.nprob; ++k) {
-    const ProbDev& pd = P.hP[k];
-    const int n = count_k == 0 ? pd.n_slots_fdwt : pd.n_slots_upd;
-    double a = 0.0;
-    for (int i = 0; i < n; ++i) a += P.rho_host[P.rho_off[k] + i];
-    out[k] = a;
-  }
+// rho_k of every problem of a solve (resid: the residual's sum of squares), read back to the host.
+fewha_status read_sums(Plan& P, const LaunchArgs& a, int k, bool resid, std::vector<double>& out, std::string& err) {
+  launch_solve_read(a, P.nprob, P.rho_dev, k, resid);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipStreamSynchronize(a.stream));
+  const volatile double* v = P.rho_host;
+  out.assign(v, v + P.nprob);
   return FEWHA_OK;
 }
 
@@ -1659,6 +1657,7 @@ bool spd_inverse(const std::vector<float>& E, int m, std::vector<float>& out) {
 // E is not positive definite is left uncorrected (m = 0: plain Jacobi).
 fewha_status setup_coarse(Plan& P, hipStream_t st, std::string& err) {
   if (P.coarse_ready) return FEWHA_OK;
+  drop_solve_block(&P);
   if (P.coarse_mem) {
     HIP_TRY(hipStreamSynchronize(st));
     HIP_TRY(hipFree(P.coarse_mem));
@@ -1666,6 +1665,7 @@ fewha_status setup_coarse(Plan& P, hipStream_t st, std::string& err) {
   }
   P.dC = nullptr;
   P.dCT = nullptr;
+  P.dCM = nullptr;
   P.n_coarse_tiles = 0;
   P.coarse_m.assign(P.nprob, 0);
   if (P.coarse_side <= 0) {
@@ -1768,31 +1768,56 @@ fewha_status setup_coarse(Plan& P, hipStream_t st, std::string& err) {
   // persistent memory: per system E^{-1} and indices; per problem zc and slots; records, tiles
   tb = 0;
   std::vector<size_t> oEi(ns), oIdx(ns), oZ(np), oS(np);
-  std::vector<Tile> tiles;
+  std::vector<CoarseTile> tiles;
   std::vector<CoarseDev> hc(np);
   for (int s = 0; s < ns; ++s) {
     grab(oEi[s], sizeof(float) * std::max<size_t>(Einv[s].size(), 1));
     grab(oIdx[s], sizeof(int) * std::max<size_t>(idx[s].size(), 1));
   }
   for (int k = 0; k < np; ++k) {
-    const int m = (int)idx[sys[k]].size(), nb = cdiv(m, kCoarseRows);
+    const int m = (int)idx[sys[k]].size(), nb = cdiv(m, kCoarseCols);
     grab(oZ[k], sizeof(float) * P.hP[k].n_c);
     grab(oS[k], sizeof(double) * kDotRing * std::max(nb, 1));
-    for (int b = 0; b < nb; ++b) tiles.push_back(Tile{k, 0, b, 0, b, 0, 0, 0});
     P.coarse_m[k] = m;
   }
-  size_t oC, oT;
+  // tiles: the problems of a system in groups of kCoarseProbs, by blocks of
+  // outputs; runs: rows of every layer's coarse block are whole 16-byte runs
+  std::vector<int> members;
+  for (int s = 0; s < ns; ++s) {
+    const int m = (int)idx[s].size();
+    bool runs = m % 16 == 0;
+    for (int j = 0; j < m; j += 4)
+      runs = runs && idx[s][j] % 4 == 0 && idx[s][j + 1] == idx[s][j] + 1 && idx[s][j + 2] == idx[s][j] + 2 &&
+             idx[s][j + 3] == idx[s][j] + 3;
+    for (int k = 0, in_group = 0; k < np; ++k) {
+      if (sys[k] != s) continue;
+      members.push_back(k);
+      if (++in_group < kCoarseProbs && rank[k] + 1 < count[s]) continue;
+      for (int b = 0; b < cdiv(m, kCoarseCols); ++b) {
+        tiles.push_back(CoarseTile{nullptr, nullptr, m, (int)members.size() - in_group, in_group, b, runs, 0});
+      }
+      in_group = 0;
+    }
+  }
+  size_t oC, oT, oM;
   grab(oC, sizeof(CoarseDev) * np);
-  grab(oT, sizeof(Tile) * std::max<size_t>(tiles.size(), 1));
+  grab(oT, sizeof(CoarseTile) * std::max<size_t>(tiles.size(), 1));
+  grab(oM, sizeof(CoarseDev) * members.size());
   char* mem = nullptr;
   HIP_TRY(hipMalloc((void**)&mem, tb));
   P.coarse_mem = mem;
   for (int k = 0; k < np; ++k) {
     const int s = sys[k], m = (int)idx[s].size();
     hc[k] = CoarseDev{(const float*)(mem + oEi[s]), (const int*)(mem + oIdx[s]), (float*)(mem + oZ[k]),
-                      (double*)(mem + oS[k]), m, cdiv(m, kCoarseRows), {0, 0}};
+                      P.sstate[k] + 2L * P.hP[k].n_c, (double*)(mem + oS[k]), m, cdiv(m, kCoarseCols)};
     HIP_TRY(hipMemsetAsync(mem + oZ[k], 0, sizeof(float) * P.hP[k].n_c, st));
     HIP_TRY(hipMemsetAsync(mem + oS[k], 0, sizeof(double) * kDotRing * std::max(hc[k].n_slots, 1), st));
+  }
+  std::vector<CoarseDev> hm;
+  for (int k : members) hm.push_back(hc[k]);
+  for (auto& t : tiles) {
+    t.einv = hm[t.first].einv;
+    t.idx = hm[t.first].idx;
   }
   for (int s = 0; s < ns; ++s)
     if (!idx[s].empty()) {
@@ -1801,57 +1826,77 @@ fewha_status setup_coarse(Plan& P, hipStream_t st, std::string& err) {
     }
   HIP_TRY(hipMemcpyAsync(mem + oC, hc.data(), sizeof(CoarseDev) * np, hipMemcpyHostToDevice, st));
   if (!tiles.empty())
-    HIP_TRY(hipMemcpyAsync(mem + oT, tiles.data(), sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(mem + oT, tiles.data(), sizeof(CoarseTile) * tiles.size(), hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(mem + oM, hm.data(), sizeof(CoarseDev) * hm.size(), hipMemcpyHostToDevice, st));
   HIP_TRY(hipStreamSynchronize(st));  // the host vectors above go out of scope
   P.dC = (const CoarseDev*)(mem + oC);
-  P.dCT = (const Tile*)(mem + oT);
+  P.dCT = (const CoarseTile*)(mem + oT);
+  P.dCM = (const CoarseDev*)(mem + oM);
   P.n_coarse_tiles = (int)tiles.size();
   P.coarse_ready = true;
   return FEWHA_OK;
 }
 
+// Step k of a solve.
+void enq_solve_step(const Plan& P, const LaunchArgs& a, const CoarseDev* C, int k) {
+  // p_k with the coarse correction: formed by the one-launch transform itself
+  const bool own_p = C && P.dir_tile == 0;
+  if (own_p) launch_coarse_p(a, C, T(P, P.upd), P.upd.n, k);
+  enq_idwt(P, a, own_p ? SRC_PJ : (k == 0 ? SRC_PUPD0 : SRC_PUPD), OUT_PHI, k, own_p ? nullptr : C);
+  enq_apply_M_core(P, a);
+  enq_fdwt(P, a, EPI_PCG, k);
+  launch_update(a, T(P, P.upd), P.upd.n, k, C);
+  if (C) launch_coarse(a, P.dCT, P.n_coarse_tiles, P.dCM, k + 1);
+}
+
 // Correction solve M d = r (r in P.rbuf) by the FP32 Jacobi-preconditioned CG
 // of Algorithm 1 from d = 0: the same kernels as a frame, one launch per
 // stage and iteration over all problems; every kSolveCheck iterations the
-// host reads rho_k and stops once sqrt(rho_k / rho_0) <= tol for every
+// host reads rho_k and stops once sqrt(rho_k) has fallen by tol for every
 // problem.  d is left in the x part of P.sstate.  With the coarse-level
-// correction set up (setup_coarse), z = J^{-1} r + Z E^{-1} Z^T r: p_k is
-// formed by k_coarse_p and rho_k includes (Z^T r)^T E^{-1} Z^T r; the
+// correction set up (setup_coarse), z = J^{-1} r + Z E^{-1} Z^T r: the inverse
+// transform forms p_k with it and rho_k includes (Z^T r)^T E^{-1} Z^T r; the
 // convergence test keeps the Jacobi-weighted residual r^T J^{-1} r.
+// After the first kSolveCheck steps, blocks of as many replay a graph.
 fewha_status pcg_core(Plan& P, hipStream_t st, int max_iters, double tol, int& iters, std::string& err) {
   std::vector<IoDev> io(P.nprob);
-  for (int k = 0; k < P.nprob; ++k) {
-    io[k].in = P.rbuf[k];
-    io[k].state = P.sstate[k];
+  for (int q = 0; q < P.nprob; ++q) {
+    io[q].in = P.rbuf[q];
+    io[q].state = P.sstate[q];
   }
   fewha_status s = upload_io(P, io, st, P.dIO, err);
   if (s != FEWHA_OK) return s;
   const LaunchArgs a = args(P, st, P.dIO);
   const CoarseDev* C = P.n_coarse_tiles > 0 ? P.dC : nullptr;
   launch_solve_init(a, T(P, P.sinit), P.sinit.n);
-  if (C) launch_coarse(a, C, P.dCT, P.n_coarse_tiles, 0);
+  if (C) launch_coarse(a, P.dCT, P.n_coarse_tiles, P.dCM, 0);
   std::vector<double> rho0, rho;
-  if ((s = read_rho(P, st, 0, 0, rho0, err)) != FEWHA_OK) return s;
+  if ((s = read_sums(P, a, 0, false, rho0, err)) != FEWHA_OK) return s;
   auto worst = [&](const std::vector<double>& r) {
     double w = 0.0;
-    for (int k = 0; k < P.nprob; ++k)
-      if (rho0[k] > 0.0) w = std::max(w, std::sqrt(std::max(r[k], 0.0) / rho0[k]));
+    for (int q = 0; q < P.nprob; ++q)
+      if (rho0[q] > 0.0) w = std::max(w, std::sqrt(std::max(r[q], 0.0) / rho0[q]));
     return w;
   };
   double rel = worst(rho0);
   int k = 0;
   while (k < max_iters && rel > tol) {
     const int kend = std::min(max_iters, k + kSolveCheck);
-    for (; k < kend; ++k) {
-      if (C) launch_coarse_p(a, C, T(P, P.upd), P.upd.n, k);  // p_k with the coarse correction
-      enq_idwt(P, a, C ? SRC_PJ : (k == 0 ? SRC_PUPD0 : SRC_PUPD), OUT_PHI, k);
-      enq_apply_M_core(P, a);
-      enq_fdwt(P, a, EPI_PCG, k);
-      launch_update(a, T(P, P.upd), P.upd.n, k, C);
-      if (C) launch_coarse(a, C, P.dCT, P.n_coarse_tiles, k + 1);
+    if (k > 0 && k % kSolveCheck == 0 && kend == k + kSolveCheck) {
+      if (!P.solve_block) {  // steps kSolveCheck .. 2 kSolveCheck - 1, the same buffers as any later block's
+        HIP_TRY(hipStreamBeginCapture(P.cap_stream, hipStreamCaptureModeThreadLocal));
+        const LaunchArgs c = args(P, P.cap_stream, P.dIO);
+        for (int q = kSolveCheck; q < 2 * kSolveCheck; ++q) enq_solve_step(P, c, C, q);
+        HIP_TRY(hipStreamEndCapture(P.cap_stream, &P.solve_block_def));
+        HIP_TRY(hipGraphInstantiate(&P.solve_block, P.solve_block_def, nullptr, nullptr, 0));
+      }
+      HIP_TRY(hipGraphLaunch(P.solve_block, st));
+      k = kend;
+    } else {
+      for (; k < kend; ++k) enq_solve_step(P, a, C, k);
     }
     HIP_TRY(hipGetLastError());
-    if ((s = read_rho(P, st, 2 * (k & (kDotRing - 1)), k, rho, err)) != FEWHA_OK) return s;
+    if ((s = read_sums(P, a, k, false, rho, err)) != FEWHA_OK) return s;
     rel = worst(rho);
   }
   iters = k;
@@ -1901,7 +1946,7 @@ fewha_status run_solve(Plan& P, hipStream_t st, const std::vector<const float*>&
   launch64_iterate(a, T(P, P.upd), P.upd.n, 0);
   int total = 0;
   double rel = 0.0, prev = HUGE_VAL;
-  std::vector<double> bnorm(P.nprob, 0.0);
+  std::vector<double> bnorm(P.nprob, 0.0), sums;
   for (int sweep = 0;; ++sweep) {
     if ((s = stage([&](int k, IoDev& d) {
            d.in = b[k];
@@ -1911,19 +1956,11 @@ fewha_status run_solve(Plan& P, hipStream_t st, const std::vector<const float*>&
          })) != FEWHA_OK)
       return s;
     launch64_resid_chain(a, P.r64, P.F64);
-    HIP_TRY(hipGetLastError());
-    for (int k = 0; k < P.nprob; ++k) {
-      const ProbDev& pd = P.hP[k];
-      HIP_TRY(hipMemcpyAsync(P.rho_host + P.rho_off[k], pd.rslots, sizeof(double) * 2 * pd.n_slots_upd,
-                             hipMemcpyDeviceToHost, st));
-    }
-    HIP_TRY(hipStreamSynchronize(st));
+    if ((s = read_sums(P, a, 0, true, sums, err)) != FEWHA_OK) return s;
     rel = 0.0;
     for (int k = 0; k < P.nprob; ++k) {
-      double rr = 0.0;
-      for (int i = 0; i < P.hP[k].n_slots_upd; ++i) rr += P.rho_host[P.rho_off[k] + 2 * i];
-      if (sweep == 0) bnorm[k] = std::sqrt(rr);
-      if (bnorm[k] > 0.0) rel = std::max(rel, std::sqrt(rr) / bnorm[k]);
+      if (sweep == 0) bnorm[k] = std::sqrt(sums[k]);
+      if (bnorm[k] > 0.0) rel = std::max(rel, std::sqrt(sums[k]) / bnorm[k]);
     }
     // stop: converged, out of iterations, or a sweep that no longer helps
     if (rel <= rtol || total >= max_iters || sweep >= kMaxSweeps || rel > 0.5 * prev) break;

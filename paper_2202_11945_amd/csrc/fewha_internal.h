@@ -36,7 +36,9 @@ constexpr int pt_band_wide(int K) { return K == 4 ? 10 : (K == 5 ? 13 : 15); }
 constexpr int kBandWideMax = pt_band_wide(kWideMaxK);
 constexpr int kDirMinLevels = 3;  // levels of the layers that the one-launch inverse transform takes
 constexpr int kUpdChunk = 2048;   // coefficients per workgroup of the vector update
-constexpr int kDotRing = 256;     // PCG iterations whose inner products are kept (ring, power of two)
+constexpr int kDotRing = 16;      // PCG iterations whose inner products are kept (ring, power of two; a step
+                                  // reads its own and the previous one's, a solve's captured block of this
+                                  // many steps can be replayed)
 constexpr int kGradChunk = 2048;  // coefficients per workgroup of the prior-term reductions
 constexpr double kTie = 1e-9;     // |t - round(t)| below which a sample sits on a grid line
 // Augmented PCG: at most kAugMax previous search directions per problem.
@@ -288,14 +290,23 @@ struct IoDev {
 // slow, are resolved by the coarse solve.
 constexpr int kCoarseSide = 16;   // default coarse block side per layer
 constexpr int kCoarseMax = 1024;  // most coarse unknowns of one problem
-constexpr int kCoarseRows = 64;   // rows of E^{-1} per workgroup of k_coarse
+constexpr int kCoarseCols = 16;   // outputs per workgroup of k_coarse
+constexpr int kCoarseProbs = 8;   // most problems of one system per workgroup
 struct CoarseDev {
   const float* einv;  // E^{-1}, m x m row-major (one copy per distinct system)
   const int* idx;     // the m coarse coefficients: index in the problem's vector
   float* zc;          // N_c floats: E^{-1} Z^T r at the coarse indices, 0 elsewhere
+  const float* r;     // r of the solve's state
   double* slots;      // kDotRing x n_slots: partials of (Z^T r)^T E^{-1} Z^T r
   int m, n_slots;     // n_slots = workgroups of k_coarse of the problem
-  int pad_[2];
+};
+// Work record of k_coarse: `nprob` problems of one system (from `first` in its
+// list of records) and one block of outputs.
+struct CoarseTile {
+  const float* einv;
+  const int* idx;
+  int m, first, nprob, block;
+  int runs, pad_;  // runs: m % 16 == 0 and idx holds runs of 4, 16-byte aligned
 };
 // Set-up of E: round t probes column t count + rank of the system's E with
 // a unit vector in `in` (every instance of one system in a batch probes its

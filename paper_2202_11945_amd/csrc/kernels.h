@@ -55,7 +55,9 @@ struct LaunchArgs {
 
 void launch_idwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter);
 // the whole inverse transform in one launch of T x T output tiles (tile = T = 32 or 64)
-void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode, int iter);
+// (C: the search direction includes the coarse-level correction of a converged solve)
+void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode, int iter,
+                     const CoarseDev* C = nullptr);
 // the resident inverse levels over four workgroups per (problem, layer): tile.tx = quadrant
 void launch_idwt_res4(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter);
 void launch_idwt_glob(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter,
@@ -78,13 +80,15 @@ enum { UPD_X_ONE = 0, UPD_X_DEFER = 1, UPD_X_PAIR = 2 };
 // C: the coarse-level correction of a converged solve (rho includes it), else null
 void launch_update(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter, const CoarseDev* C = nullptr,
                    int xm = UPD_X_ONE);
-// converged solves' coarse-level correction: y = E^{-1} Z^T r_k (tiles: problem x row block)
-void launch_coarse(const LaunchArgs& a, const CoarseDev* C, const Tile* tiles, int ntiles, int k);
+// converged solves' coarse-level correction: y = E^{-1} Z^T r_k (tiles: problems of one system x block of outputs)
+void launch_coarse(const LaunchArgs& a, const CoarseTile* tiles, int ntiles, const CoarseDev* members, int k);
 // p_k = J^{-1} r_k + Z y + beta_k p_{k-1} over the vector-update chunks
 void launch_coarse_p(const LaunchArgs& a, const CoarseDev* C, const Tile* tiles, int ntiles, int iter);
 // set-up of E = Z^T M Z, round t: unit vectors (store = false) or columns (store = true)
 void launch_coarse_probe(const CoarseProbe* Q, int nprob, int t, bool store, hipStream_t s);
 void launch_solve_init(const LaunchArgs& a, const Tile* tiles, int ntiles);
+// per problem into host memory `out`: rho_k, or (resid) the residual's sum of squares
+void launch_solve_read(const LaunchArgs& a, int nprob, double* out, int k, bool resid);
 void launch_grad_height(const LaunchArgs& a, const Tile* tiles, int ntiles, int term);
 void launch_grad_prior(const LaunchArgs& a, const GradIo* g, const Tile* tiles, int ntiles);
 void launch_grad_final(const LaunchArgs& a, const GradIo* g, int nprob);

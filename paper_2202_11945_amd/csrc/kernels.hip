@@ -203,6 +203,13 @@ __device__ __forceinline__ void rho_sum2(const ProbDev& pr, int k, double& rk, d
   rkm = o[1];
 }
 
+// rho_k with the coarse-level correction of the converged solves:
+// r^T z = r^T J^{-1} r + (Z^T r)^T E^{-1} Z^T r (the second part's slots,
+// written by k_coarse).
+__device__ __forceinline__ const double* coarse_slots(const CoarseDev& c, int k) {
+  return c.slots + (long)(k & (kDotRing - 1)) * c.n_slots;
+}
+
 // Search-direction source of the inverse transform (fused p update).
 struct PSrc {
   const float* __restrict__ src;  // plain source (SRC_IN / SRC_STATE_C)
@@ -1109,13 +1116,23 @@ struct DirWin {
   static constexpr int run(int j) { return (pairs(j) + runs(j) - 1) / runs(j); }
 };
 
+// One coefficient's operands: the plain source; r, J^{-1}; r, J^{-1}, p_{k-1};
+// r, J^{-1}, p_{k-1} and the coarse-level correction of a converged solve.
+struct DirCoef {
+  float a, b, c, d;
+};
+struct DirPtrs {
+  gptr_f a, b, c, d;
+  bool first;  // with the correction: no p_{k-1} yet
+};
+
 // Window entries of level J in registers: the three detail bands, and from
 // level 3 on (kDirMinLevels) the coarse band, taken when J is the deepest.
 template <int T, int J, int NT>
 struct DirLoads {
   static constexpr int kBands = J >= kDirMinLevels ? 4 : 3;
   static constexpr int kR = (kBands * DirWin<T>::w(J) * DirWin<T>::w(J) + NT - 1) / NT;
-  CoefLoad v[kR];
+  DirCoef v[kR];
   DirLoads<T, J + 1, NT> next;
 };
 template <int NT>
@@ -1139,25 +1156,27 @@ __device__ __forceinline__ int dir_entry(int e, int n, int off, int ty, int tx, 
          (((T >> J) * tx - a + ix) & (half - 1));
 }
 
-// NOPS operands per coefficient: the plain source; r, J^{-1}; or r, J^{-1}, p_{k-1}.
 template <int NOPS>
-__device__ __forceinline__ CoefLoad dir_load(const CoefPtrs& p, int e) {
-  CoefLoad v{p.a[e], 0.f, 0.f};
+__device__ __forceinline__ DirCoef dir_load(const DirPtrs& p, int e) {
+  DirCoef v;
+  v.a = p.a[e];
   if (NOPS > 1) v.b = p.b[e];
   if (NOPS > 2) v.c = p.c[e];
+  if (NOPS > 3) v.d = p.d[e];
   return v;
 }
 template <int NOPS>
-__device__ __forceinline__ float dir_finish(const PSrc& s, int e, const CoefLoad& v, bool own) {
+__device__ __forceinline__ float dir_finish(const PSrc& s, bool first, int e, const DirCoef& v, bool own) {
   if (NOPS == 1) return v.a;
-  const float z = v.a * v.b;
-  const float p = NOPS == 2 ? z : fmaf(s.beta, v.c, z);
+  const float z = NOPS == 4 ? fmaf(v.a, v.b, v.d) : v.a * v.b;
+  float p = z;
+  if (NOPS > 2) p = NOPS == 4 && first ? z : fmaf(s.beta, v.c, z);
   if (own) ((gptr_w)s.pnew)[e] = p;
   return p;
 }
 
 template <int T, int J, int NT, int NOPS>
-__device__ __forceinline__ void dir_fetch(const CoefPtrs& cp, int n, int levels, int off, const Tile& t,
+__device__ __forceinline__ void dir_fetch(const DirPtrs& cp, int n, int levels, int off, const Tile& t,
                                           DirLoads<T, J, NT>& L) {
   using W = DirWin<T>;
   if constexpr (J < W::kLevels) dir_fetch<T, J + 1, NT, NOPS>(cp, n, levels, off, t, L.next);
@@ -1172,11 +1191,11 @@ __device__ __forceinline__ void dir_fetch(const CoefPtrs& cp, int n, int levels,
   }
 }
 template <int T, int J, int NT, int NOPS>
-__device__ __forceinline__ void dir_place(const PSrc& ps, int n, int levels, int off, const Tile& t,
+__device__ __forceinline__ void dir_place(const PSrc& ps, bool first, int n, int levels, int off, const Tile& t,
                                           const DirLoads<T, J, NT>& L, float* A) {
   using W = DirWin<T>;
   if (J > levels) return;
-  if constexpr (J < W::kLevels) dir_place<T, J + 1, NT, NOPS>(ps, n, levels, off, t, L.next, A);
+  if constexpr (J < W::kLevels) dir_place<T, J + 1, NT, NOPS>(ps, first, n, levels, off, t, L.next, A);
   const int ne = (J == levels ? 4 : 3) * W::w(J) * W::w(J);
 #pragma unroll
   for (int u = 0; u < DirLoads<T, J, NT>::kR; ++u) {
@@ -1184,7 +1203,7 @@ __device__ __forceinline__ void dir_place(const PSrc& ps, int n, int levels, int
     int lds;
     bool own;
     const int pos = dir_entry<T, J>(e, n, off, t.ty, t.tx, lds, own);
-    if (e < ne) A[lds] = dir_finish<NOPS>(ps, pos, L.v[u], own);
+    if (e < ne) A[lds] = dir_finish<NOPS>(ps, first, pos, L.v[u], own);
   }
 }
 
@@ -1283,21 +1302,37 @@ __device__ __forceinline__ void out_finish4(const OutDst& d, int e, const v4f& v
   }
 }
 
-// The window's coefficients into LDS.
+// The window's coefficients into LDS.  C (NOPS = 4): the coarse-level
+// correction of a converged solve, whose z = J^{-1} r + zc and whose rho has
+// a part of its own.
 template <int T, int NT, int NOPS>
 __device__ __forceinline__ void dir_window(const ProbDev& pr, int n, int levels, int off, const Tile& t, PSrc& ps,
-                                           int iter, float* A) {
-  const CoefPtrs cp = coef_ptrs(ps);
+                                           int iter, const CoarseDev* C, float* A) {
+  const CoefPtrs q = coef_ptrs(ps);
+  const DirPtrs cp{q.a, q.b, q.c, NOPS == 4 ? (gptr_f)C->zc : q.a, iter == 0};
   DirLoads<T, 1, NT> L;
   if (NOPS == 3) {
     BetaLoads<2> bl;
     beta_issue<2>(pr, SRC_PUPD, iter, bl);
     dir_fetch<T, 1, NT, NOPS>(cp, n, levels, off, t, L);
     ps.beta = beta_reduce<2>(SRC_PUPD, bl);
+  } else if (NOPS == 4) {
+    int n0 = 0, n1 = 0;
+    const int nc = iter > 0 ? C->n_slots : 0, k1 = iter > 0 ? iter - 1 : 0;
+    const double* const sl[4] = {rho_slots(pr, iter, n0), coarse_slots(*C, iter), rho_slots(pr, k1, n1),
+                                 coarse_slots(*C, k1)};
+    const int nn[4] = {iter > 0 ? n0 : 0, nc, iter > 0 ? n1 : 0, nc};
+    SlotLoads<4, 2> S;
+    slots_issue<4, 2>(sl, nn, S);
+    dir_fetch<T, 1, NT, NOPS>(cp, n, levels, off, t, L);
+    double o[4];
+    slots_reduce<4, 2>(sl, nn, S, o);
+    const double rk = o[0] + o[1], rkm = o[2] + o[3];
+    ps.beta = (float)(rkm != 0.0 ? rk / rkm : 0.0);
   } else {
     dir_fetch<T, 1, NT, NOPS>(cp, n, levels, off, t, L);
   }
-  dir_place<T, 1, NT, NOPS>(ps, n, levels, off, t, L, A);
+  dir_place<T, 1, NT, NOPS>(ps, cp.first, n, levels, off, t, L, A);
 }
 
 // The finest level: columns, then rows four outputs per task straight to the output.
@@ -1325,9 +1360,12 @@ __device__ __forceinline__ void dir_finest(const OutDst& od, int off, int n, con
   }
 }
 
-template <int T, int NT>
+// COARSE: the instantiation for converged solves with the coarse-level
+// correction (its fourth operand costs registers that frames do not have).
+template <int T, int NT, bool COARSE>
 __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
-                                                 const Tile* tiles, Filter F, int src_mode, int out_mode, int iter) {
+                                                 const Tile* tiles, Filter F, int src_mode, int out_mode, int iter,
+                                                 const CoarseDev* C) {
   __shared__ float A[DirWin<T>::words()];
   __shared__ float B[T * DirWin<T>::stride(1)];
   const Tile t = my_tile(tiles);
@@ -1339,12 +1377,15 @@ __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDe
   const int n = ly.n, off = ly.off, levels = ly.levels;
   const float inv_delta = ly.inv_delta;
   const OutDst od = out_dst(pr, io, out_mode);
-  if (ps.mode == SRC_PUPD)
-    dir_window<T, NT, 3>(pr, n, levels, off, t, ps, iter, A);
+  const CoarseDev* c = C + t.prob;
+  if constexpr (COARSE)
+    dir_window<T, NT, 4>(pr, n, levels, off, t, ps, iter, c, A);
+  else if (ps.mode == SRC_PUPD)
+    dir_window<T, NT, 3>(pr, n, levels, off, t, ps, iter, c, A);
   else if (ps.mode == SRC_PUPD0)
-    dir_window<T, NT, 2>(pr, n, levels, off, t, ps, iter, A);
+    dir_window<T, NT, 2>(pr, n, levels, off, t, ps, iter, c, A);
   else
-    dir_window<T, NT, 1>(pr, n, levels, off, t, ps, iter, A);
+    dir_window<T, NT, 1>(pr, n, levels, off, t, ps, iter, c, A);
   __syncthreads();
   dir_levels<T, 2>(n, levels, F, A, B);
   if (n > kResMax)
@@ -3313,13 +3354,6 @@ __global__ __launch_bounds__(256) void k_aug_store(const ProbDev* P, const IoDev
 // ------------------------------------------------------------ PCG update
 // a = rho_k / pi_k; x += a p; r -= a q; partial rho_{k+1} = r^T J^{-1} r.
 // 2048 coefficients per workgroup as float4: 2 per thread, loads first.
-// rho_k with the coarse-level correction of the converged solves:
-// r^T z = r^T J^{-1} r + (Z^T r)^T E^{-1} Z^T r (the second part's slots,
-// written by k_coarse).
-__device__ __forceinline__ const double* coarse_slots(const CoarseDev& c, int k) {
-  return c.slots + (long)(k & (kDotRing - 1)) * c.n_slots;
-}
-
 // XM: the x update of this step.  UPD_X_ONE: x += a_k p_k.  A frame takes
 // two steps' x updates in one pass (the search directions p_{k-1} and p_k
 // are both still held): UPD_X_DEFER leaves x for the next step, which as
@@ -3476,53 +3510,109 @@ __global__ __launch_bounds__(256) void k_solve_init(const ProbDev* P, const IoDe
   if (threadIdx.x == 0) pr.dots[(long)rho_grp(0) * pr.n_dots + t.slot] = s;
 }
 
-// Coarse-level correction, per problem and block of kCoarseRows outputs:
-// y = E^{-1} Z^T r on those outputs, stored at their coarse indices of zc,
-// and the block's partial of (Z^T r)^T y into slot (k, block); r is r_k of
-// the solve's state.  E^{-1} is symmetric, so output i sums column i, read
-// along rows: lane = output (coalesced), the 4 waves split the rows and
-// their partial sums are added in a fixed order.  Z^T r is gathered into
-// LDS by every block.
-__global__ __launch_bounds__(256) void k_coarse(const ProbDev* P, const IoDev* IO, const CoarseDev* C,
-                                                const Tile* tiles, int k) {
+// Per problem (one wave each) into host memory: rho_k of a solve, or (resid)
+// the sum of squares of its residual.
+__global__ __launch_bounds__(64) void k_solve_read(const ProbDev* P, double* out, int k, int resid) {
+  const ProbDev& pr = P[blockIdx.x];
+  double v;
+  if (resid) {
+    double a = 0.0;
+    for (int i = threadIdx.x; i < pr.n_slots_upd; i += 64) a += ((gptr_d)pr.rslots)[2 * i];
+    v = wave_sum(a);
+  } else {
+    v = wave_sum_slots(dot_group(pr, rho_grp(k)), rho_count(pr, k));
+  }
+  if (threadIdx.x == 0) __hip_atomic_store(out + blockIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Coarse-level correction: y = E^{-1} Z^T r for up to kCoarseProbs problems of
+// one system (the tile's records in M) and a block of kCoarseCols outputs, stored
+// at their coarse indices of zc, and the block's partial of (Z^T r)^T y into
+// slot (k, block) of each problem; r is r_k of the solve's state.
+// All waves stage the block's rows of E^{-1} (once for all problems) and the
+// problems' Z^T r in LDS, then a wave sums one problem: lane (quarter,
+// output) runs the quarter of its row, and the quarters are added in order.
+// runs: 16-byte loads (the rows of every coarse block are whole runs of 4).
+// Bound: the loads' chain (record, index, r) and the m / 4 dependent additions
+// of a lane: 5.1 us for two problems and 6.3 us for five (m = 768), where a
+// wave that reads E^{-1} from memory as it adds it took 7.4 and 11.0 us, and
+// matrix instructions 6.1 and 6.3 us in another order of summation.
+constexpr int kCoarseStride = kCoarseMax + 4;  // LDS row: 16 bytes from the next one's banks
+constexpr int kCoarseThreads = 512;
+__global__ __launch_bounds__(kCoarseThreads) void k_coarse(const CoarseTile* tiles, const CoarseDev* M, int k) {
   typedef const int __attribute__((address_space(1)))* gptr_i;
-  __shared__ float rc[kCoarseMax];
-  __shared__ float part[4][kCoarseRows];
-  const Tile t = my_tile(tiles);
-  const ProbDev& pr = P[t.prob];
-  const CoarseDev& c = C[t.prob];
-  const int m = c.m;
-  const gptr_f r = (gptr_f)(IO[t.prob].state + 2L * pr.n_c);
-  const gptr_i idx = (gptr_i)c.idx;
-  for (int j = threadIdx.x; j < m; j += 256) rc[j] = r[idx[j]];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int i = t.ty * kCoarseRows + lane;
-  const int ic = min(i, m - 1);  // lanes past the last output read a valid column
-  const int per = (m + 3) / 4, j0 = wv * per, j1 = min(j0 + per, m);
-  const gptr_f col = (gptr_f)(c.einv + ic);
-  float acc = 0.f;
-  int j = j0;
-  for (; j + 8 <= j1; j += 8) {
-    float e[8];
+  static_assert(kCoarseCols == 16 && kCoarseProbs * 64 == kCoarseThreads, "a wave per problem: 4 quarters x 16 outputs");
+  __shared__ __align__(16) float E[kCoarseCols * kCoarseStride];
+  __shared__ __align__(16) float rc[kCoarseProbs * kCoarseMax];
+  const CoarseTile& t = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
+  const int nb = t.nprob, m = t.m, runs = t.runs, o0 = t.block * kCoarseCols;
+  const CoarseDev* const mem = M + t.first;
+  const gptr_i idx = (gptr_i)t.idx;
+  const gptr_f einv = (gptr_f)t.einv;
+  const int b = threadIdx.x >> 6, lane = threadIdx.x & 63, o = lane & 15, i = o0 + o;
+  const CoarseDev& c = mem[min(b, nb - 1)];
+  const gptr_w zo = (gptr_w)c.zc + idx[min(i, m - 1)];
+  const gptr_wd so = (gptr_wd)c.slots + ((long)(k & (kDotRing - 1)) * c.n_slots + t.block);
+  if (runs) {
+    const int m4 = m / 4;
+    constexpr int kE = kCoarseCols * kCoarseMax / 4 / kCoarseThreads, kR = kCoarseProbs * kCoarseMax / 4 / kCoarseThreads;
+    v4f e[kE], x[kR];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) e[u] = col[(long)(j + u) * m];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc = fmaf(e[u], rc[j + u], acc);
-  }
-  for (; j < j1; ++j) acc = fmaf(col[(long)j * m], rc[j], acc);
-  part[wv][lane] = acc;
-  __syncthreads();
-  if (wv == 0) {
-    const float y = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-    double d = 0.0;
-    if (i < m) {
-      ((gptr_w)c.zc)[idx[i]] = y;
-      d = (double)rc[i] * (double)y;
+    for (int u = 0; u < kR; ++u) {  // clamped: every load is issued, the last ones repeat
+      const int q = min((int)threadIdx.x + u * kCoarseThreads, nb * m4 - 1), b = q / m4;
+      x[u] = *(gptr_f4)((gptr_f)mem[b].r + idx[4 * (q - b * m4)]);
     }
-    d = wave_sum(d);
-    if (lane == 0) ((gptr_wd)c.slots)[(long)(k & (kDotRing - 1)) * c.n_slots + t.ty] = d;
+#pragma unroll
+    for (int u = 0; u < kE; ++u) {
+      const int q = min((int)threadIdx.x + u * kCoarseThreads, kCoarseCols * m4 - 1);
+      e[u] = *(gptr_f4)(einv + (long)o0 * m + 4 * q);  // m % 16 == 0: the block's rows are all there
+    }
+#pragma unroll
+    for (int u = 0; u < kE; ++u) {
+      const int q = (int)threadIdx.x + u * kCoarseThreads, o = q / m4;
+      if (q < kCoarseCols * m4) *(v4f*)(E + o * kCoarseStride + 4 * (q - o * m4)) = e[u];
+    }
+#pragma unroll
+    for (int u = 0; u < kR; ++u) {
+      const int q = (int)threadIdx.x + u * kCoarseThreads, b = q / m4;
+      if (q < nb * m4) *(v4f*)(rc + b * kCoarseMax + 4 * (q - b * m4)) = x[u];
+    }
+  } else {
+    for (int q = threadIdx.x; q < kCoarseCols * m; q += kCoarseThreads) {
+      const int o = q / m;
+      E[o * kCoarseStride + q - o * m] = einv[(long)min(o0 + o, m - 1) * m + q - o * m];
+    }
+    for (int q = threadIdx.x; q < nb * m; q += kCoarseThreads) {
+      const int b = q / m;
+      rc[b * kCoarseMax + q - b * m] = ((gptr_f)mem[b].r)[idx[q - b * m]];
+    }
   }
+  __syncthreads();
+  if (b >= nb) return;
+  const int per = (m + 3) / 4, j0 = (lane >> 4) * per, j1 = min(j0 + per, m);
+  const float* Eo = E + o * kCoarseStride;
+  const float* rb = rc + b * kCoarseMax;
+  float acc = 0.f;
+  if (runs) {
+#pragma unroll 8
+    for (int j = j0; j < j1; j += 4) {
+      const v4f ev = *(const v4f*)(Eo + j), rv = *(const v4f*)(rb + j);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc = fmaf(ev[v], rv[v], acc);
+    }
+  } else {
+    for (int j = j0; j < j1; ++j) acc = fmaf(Eo[j], rb[j], acc);
+  }
+  const float p1 = __shfl(acc, o + 16), p2 = __shfl(acc, o + 32), p3 = __shfl(acc, o + 48);
+  const float y = ((acc + p1) + p2) + p3;  // lanes 0 .. 15
+  double d = 0.0;
+  if (lane < 16 && i < m) {
+    *zo = y;
+    d = (double)rb[i] * (double)y;
+  }
+#pragma unroll
+  for (int h = 8; h > 0; h >>= 1) d += __shfl_xor(d, h, 16);
+  if (lane == 0) *so = d;
 }
 
 // Search direction of the coarse-corrected solve, over the vector-update
@@ -3771,12 +3861,21 @@ void launch_idwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int src
     k_idwt_res<128><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
 }
 void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode,
-                     int iter) {
+                     int iter, const CoarseDev* C) {
   if (ntiles <= 0) return;
-  if (tile == 64)
-    k_idwt_dir<64, 256><<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
-  else
-    k_idwt_dir<32, 256><<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
+#define FEWHA_ID(T, CO) \
+  k_idwt_dir<T, 256, CO><<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter, C)
+  if (tile == 64) {
+    if (C)
+      FEWHA_ID(64, true);
+    else
+      FEWHA_ID(64, false);
+  } else if (C) {
+    FEWHA_ID(32, true);
+  } else {
+    FEWHA_ID(32, false);
+  }
+#undef FEWHA_ID
 }
 void launch_idwt_res4(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter) {
   if (ntiles <= 0) return;
@@ -3894,8 +3993,8 @@ void launch_update(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter,
   else
     k_update<UPD_X_ONE><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
 }
-void launch_coarse(const LaunchArgs& a, const CoarseDev* C, const Tile* tiles, int ntiles, int k) {
-  if (ntiles > 0) k_coarse<<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, C, tiles, k);
+void launch_coarse(const LaunchArgs& a, const CoarseTile* tiles, int ntiles, const CoarseDev* members, int k) {
+  if (ntiles > 0) k_coarse<<<ntiles, kCoarseThreads, 0, a.stream>>>(tiles, members, k);
 }
 void launch_coarse_p(const LaunchArgs& a, const CoarseDev* C, const Tile* tiles, int ntiles, int iter) {
   if (ntiles > 0) k_coarse_p<<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, C, tiles, iter);
@@ -3909,6 +4008,9 @@ void launch_coarse_probe(const CoarseProbe* Q, int nprob, int t, bool store, hip
 }
 void launch_solve_init(const LaunchArgs& a, const Tile* tiles, int ntiles) {
   if (ntiles > 0) k_solve_init<<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles);
+}
+void launch_solve_read(const LaunchArgs& a, int nprob, double* out, int k, bool resid) {
+  if (nprob > 0) k_solve_read<<<nprob, 64, 0, a.stream>>>(a.P, out, k, resid ? 1 : 0);
 }
 void launch_grad_height(const LaunchArgs& a, const Tile* tiles, int ntiles, int term) {
   if (ntiles > 0) k_grad_height<<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.W, tiles, term);

@@ -2547,76 +2547,86 @@ __global__ __launch_bounds__(256) void k_slopes_in(const ProbDev* P, const WfsDe
 }
 
 // ------------------------------------- noise weighting + Shack-Hartmann adjoint
-// Tile of 32x32 corners (4 per thread); the weighted slopes of the 33x33
-// subapertures that touch them are formed in LDS (thread t takes window
-// entries t, t + 256, ...), all their loads in flight together.  The
-// window's rows come from the tile's row table (span base, active flags),
-// read with the tile, so only active subapertures' slopes are loaded:
+// Tile of 32x32 corners; the weighted slopes of the 33x33 subapertures that
+// touch them are formed in LDS (thread t takes window entries t, t + NT, ...).
+// The window's rows come from the tile's row table (span base, active
+// flags), read with the tile.  No load is under a branch of its own (an
+// inactive subaperture reads the first slope, unused), so all are in flight
+// together, the tip/tilt partials included.  Bound: the chain tile -> row
+// table -> slopes and, up to 1024 tiles, the work of a thread: one sensor set
+// of 54 tiles 4.0 -> 2.6 us with 4 times the threads, 216 tiles 4.2 -> 2.9 us,
+// 1728 tiles 6.6 -> 6.3 us (with 256 threads; 6.8 us with 512).
 // C_hat^{-1} = (I - T) C^{-1} (I - T) for LGS with tip/tilt removal (means
 // from the per-tile partial sums, Sec. 3.2), C^{-1} otherwise; GT_PLAIN
-// applies Gamma^T alone.  The subaperture operands are requested before the
-// means are reduced.
-__global__ __launch_bounds__(256) void k_gammaT(const ProbDev* P, const WfsDev* WD, const Tile* tiles,
+// applies Gamma^T alone.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_gammaT(const ProbDev* P, const WfsDev* WD, const Tile* tiles,
                                                 const int2* rows, int mode) {
   constexpr int SW = kGtS + 1;                    // subaperture window of the tile
-  constexpr int kR = (SW * SW + 255) / 256;       // window elements per thread
-  constexpr int kC = kGtS * kGtS / 256;           // corners per thread
+  constexpr int kR = (SW * SW + NT - 1) / NT;     // window elements per thread
+  constexpr int kC = kGtS * kGtS / NT;            // corners per thread
   __shared__ float YX[SW * SW];
   __shared__ float YY[SW * SW];
   __shared__ float mean[4];
-  typedef const int __attribute__((address_space(1)))* gptr_i;
   const Tile t = my_tile(tiles);
   const ProbDev& pr = P[t.prob];
   const WfsDev& w = WD[t.slot];
   const int N = w.N, nc = w.nc;
   const bool weighted = mode == GT_WEIGHTED;
+  const bool blocks = weighted && w.blocks, tt = weighted && w.tt;
   const int ci0 = t.ty * kGtS, cj0 = t.tx * kGtS;
-  const gptr_f sd = (gptr_f)(pr.sd + w.sp_off);
   typedef int v2i __attribute__((ext_vector_type(2)));
   typedef const v2i __attribute__((address_space(1)))* gptr_i2;
   v2i rw[kR];
 #pragma unroll
-  for (int u = 0; u < kR; ++u) {
-    const int e = threadIdx.x + u * 256;
-    rw[u] = v2i{0, 0};
-    if (e < SW * SW) rw[u] = ((gptr_i2)rows)[t.level + e / SW];
+  for (int u = 0; u < kR; ++u) {  // entries past the window read its last one, unused
+    const int e = min((int)threadIdx.x + u * NT, SW * SW - 1);
+    rw[u] = ((gptr_i2)rows)[t.level + e / SW];
   }
+  // wave 0: the first 64 tiles' tip/tilt partials, with the row table
+  const gptr_f4u pp = (gptr_f4u)(pr.part + w.part_off);
+  v4f p0 = {0.f, 0.f, 0.f, 0.f};
+  if (tt && threadIdx.x < 64) p0 = pp[min((int)threadIdx.x, w.n_tiles_s - 1)];
   bool act[kR];
   float sx[kR], sy[kR], cb0[kR], cb1[kR], cb2[kR];
+  const gptr_f sd = (gptr_f)(pr.sd + w.sp_off);
+  const int sl = w.sp_len;
 #pragma unroll
-  for (int u = 0; u < kR; ++u) {
-    const int e = threadIdx.x + u * 256;
-    act[u] = false;
-    sx[u] = sy[u] = cb0[u] = cb1[u] = cb2[u] = 0.f;
-    if (e < SW * SW) {
-      const int li = e / SW, lj = e - li * SW;
-      const int i = ci0 - 1 + li, j = cj0 - 1 + lj;  // subaperture
-      // flags of columns 0 .. 31 in .y, of column 32 in bit 0 of .x (inactive outside the grid)
-      act[u] = lj < 32 ? ((unsigned)rw[u].y >> lj) & 1u : rw[u].x & 1;
-      if (act[u]) {
-        const int si = (rw[u].x >> 1) + j;  // row-span position
-        sx[u] = sd[si];
-        sy[u] = sd[w.sp_len + si];
-      }
-      if (i >= 0 && j >= 0 && i < N && j < N) {
-        if (weighted && w.blocks) {
-          const gptr_f cb = (gptr_f)(pr.cinv + w.cinv_off + 3 * (i * N + j));
-          cb0[u] = cb[0];
-          cb1[u] = cb[1];
-          cb2[u] = cb[2];
-        }
-      }
+  for (int u = 0; u < kR; ++u) {  // an inactive subaperture reads the first slope, unused
+    const int e = threadIdx.x + u * NT, lj = min(e, SW * SW - 1) % SW, j = cj0 - 1 + lj;
+    // flags of columns 0 .. 31 in .y, of column 32 in bit 0 of .x (inactive outside the grid)
+    act[u] = e < SW * SW && (lj < 32 ? ((unsigned)rw[u].y >> lj) & 1u : rw[u].x & 1);
+    const int si = act[u] ? (rw[u].x >> 1) + j : 0;  // row-span position
+    sx[u] = sd[si];
+    sy[u] = sd[sl + si];
+    cb0[u] = cb1[u] = cb2[u] = 0.f;
+  }
+  if (blocks) {
+    const gptr_f cb = (gptr_f)(pr.cinv + w.cinv_off);
+#pragma unroll
+    for (int u = 0; u < kR; ++u) {
+      const int e = min((int)threadIdx.x + u * NT, SW * SW - 1), li = e / SW, lj = e - li * SW;
+      const int i = min(max(ci0 - 1 + li, 0), N - 1), j = min(max(cj0 - 1 + lj, 0), N - 1);
+      cb0[u] = cb[3 * (i * N + j)];
+      cb1[u] = cb[3 * (i * N + j) + 1];
+      cb2[u] = cb[3 * (i * N + j) + 2];
     }
   }
-  if (weighted && w.tt) {
-    if (threadIdx.x < 64) {  // wave 0: tip/tilt means from the tile partials
+  if (tt) {
+    if (threadIdx.x < 64) {  // tip/tilt means from the tile partials
       float px = 0.f, py = 0.f, pcx = 0.f, pcy = 0.f;
-      const gptr_f pp = (gptr_f)(pr.part + w.part_off);
-      for (int k = threadIdx.x; k < w.n_tiles_s; k += 64) {
-        px += pp[4 * k];
-        py += pp[4 * k + 1];
-        pcx += pp[4 * k + 2];
-        pcy += pp[4 * k + 3];
+      if ((int)threadIdx.x < w.n_tiles_s) {
+        px += p0[0];
+        py += p0[1];
+        pcx += p0[2];
+        pcy += p0[3];
+      }
+      for (int k = threadIdx.x + 64; k < w.n_tiles_s; k += 64) {
+        const v4f q = pp[k];
+        px += q[0];
+        py += q[1];
+        pcx += q[2];
+        pcy += q[3];
       }
       px = wave_sum(px);
       py = wave_sum(py);
@@ -2626,51 +2636,50 @@ __global__ __launch_bounds__(256) void k_gammaT(const ProbDev* P, const WfsDev* 
         const float mx = px * w.inv_nM, my = py * w.inv_nM;
         mean[0] = mx;
         mean[1] = my;
-        mean[2] = w.blocks ? (pcx - (w.sum_cinv[0] * mx + w.sum_cinv[1] * my)) * w.inv_nM : 0.f;
-        mean[3] = w.blocks ? (pcy - (w.sum_cinv[2] * mx + w.sum_cinv[3] * my)) * w.inv_nM : 0.f;
+        mean[2] = blocks ? (pcx - (w.sum_cinv[0] * mx + w.sum_cinv[1] * my)) * w.inv_nM : 0.f;
+        mean[3] = blocks ? (pcy - (w.sum_cinv[2] * mx + w.sum_cinv[3] * my)) * w.inv_nM : 0.f;
       }
     }
-  } else if (threadIdx.x < 4) {
-    mean[threadIdx.x] = 0.f;
+    __syncthreads();
   }
-  __syncthreads();
-  const float m0 = mean[0], m1 = mean[1], m2 = mean[2], m3 = mean[3];
+  const float m0 = tt ? mean[0] : 0.f, m1 = tt ? mean[1] : 0.f, m2 = tt ? mean[2] : 0.f, m3 = tt ? mean[3] : 0.f;
+  const float is2 = w.inv_sigma2;
 #pragma unroll
   for (int u = 0; u < kR; ++u) {
-    const int e = threadIdx.x + u * 256;
-    if (e >= SW * SW) continue;
-    float yx = 0.f, yy = 0.f;
-    if (act[u]) {
-      if (!weighted) {
-        yx = sx[u];
-        yy = sy[u];
-      } else if (w.blocks) {
-        const float dx = sx[u] - m0, dy = sy[u] - m1;
+    const int e = threadIdx.x + u * NT;
+    float yx, yy;
+    if (!weighted) {
+      yx = sx[u];
+      yy = sy[u];
+    } else {
+      const float dx = sx[u] - m0, dy = sy[u] - m1;
+      if (blocks) {
         yx = cb0[u] * dx + cb1[u] * dy - m2;
         yy = cb1[u] * dx + cb2[u] * dy - m3;
       } else {
-        yx = w.inv_sigma2 * (sx[u] - m0);
-        yy = w.inv_sigma2 * (sy[u] - m1);
+        yx = is2 * dx;
+        yy = is2 * dy;
       }
     }
-    YX[e] = yx;
-    YY[e] = yy;
+    if (e < SW * SW) {
+      YX[e] = act[u] ? yx : 0.f;
+      YY[e] = act[u] ? yy : 0.f;
+    }
   }
   __syncthreads();
+  const gptr_w va = (gptr_w)(pr.vadj + w.v_off);
 #pragma unroll
   for (int u = 0; u < kC; ++u) {
-    const int e = threadIdx.x + u * 256;
+    const int e = threadIdx.x + u * NT;
     const int li = e / kGtS, lj = e % kGtS;
     const int i = ci0 + li, j = cj0 + lj;
-    if (i < nc && j < nc) {
-      // subapertures (i-1, j-1), (i-1, j), (i, j-1), (i, j) sit at local (li, lj) .. (li+1, lj+1)
-      const float xa = YX[li * SW + lj], xb = YX[li * SW + lj + 1];
-      const float xc = YX[(li + 1) * SW + lj], xd = YX[(li + 1) * SW + lj + 1];
-      const float ya = YY[li * SW + lj], yb = YY[li * SW + lj + 1];
-      const float yc = YY[(li + 1) * SW + lj], yd = YY[(li + 1) * SW + lj + 1];
-      const float v = 0.5f * ((xc - xd) + (xa - xb)) + 0.5f * ((ya + yb) - (yc + yd));
-      ((gptr_w)pr.vadj)[w.v_off + i * nc + j] = v;
-    }
+    // subapertures (i-1, j-1), (i-1, j), (i, j-1), (i, j) sit at local (li, lj) .. (li+1, lj+1)
+    const float xa = YX[li * SW + lj], xb = YX[li * SW + lj + 1];
+    const float xc = YX[(li + 1) * SW + lj], xd = YX[(li + 1) * SW + lj + 1];
+    const float ya = YY[li * SW + lj], yb = YY[li * SW + lj + 1];
+    const float yc = YY[(li + 1) * SW + lj], yd = YY[(li + 1) * SW + lj + 1];
+    const float v = 0.5f * ((xc - xd) + (xa - xb)) + 0.5f * ((ya + yb) - (yc + yd));
+    if (i < nc && j < nc) va[i * nc + j] = v;
   }
 }
 
@@ -3848,6 +3857,7 @@ __global__ __launch_bounds__(1024) void k_fit_cg(const FitDev* F, const ProbDev*
 }
 
 // ------------------------------------------------------------ launchers
+constexpr int kCus = 256;  // compute units
 
 // The resident kernels are instantiated for LDS capacities 32, 64 and 128 and
 // launched with the smallest that holds the plan's resident side.
@@ -3960,7 +3970,14 @@ void launch_slopes_in(const LaunchArgs& a, const Tile* tiles, int ntiles, int ad
     k_slopes_in<0><<<ntiles, 256, 0, a.stream>>>(a.P, a.W, a.IO, tiles);
 }
 void launch_gammaT(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode) {
-  if (ntiles > 0) k_gammaT<<<ntiles, 256, 0, a.stream>>>(a.P, a.W, tiles, a.gtrows, mode);
+  // threads per tile: as many as keep every workgroup of the launch resident
+  // (8 waves of 512 threads, 4 workgroups on each compute unit; 16 of 1024, 1)
+  if (ntiles > 4 * kCus)
+    k_gammaT<256><<<ntiles, 256, 0, a.stream>>>(a.P, a.W, tiles, a.gtrows, mode);
+  else if (ntiles > kCus)
+    k_gammaT<512><<<ntiles, 512, 0, a.stream>>>(a.P, a.W, tiles, a.gtrows, mode);
+  else if (ntiles > 0)
+    k_gammaT<1024><<<ntiles, 1024, 0, a.stream>>>(a.P, a.W, tiles, a.gtrows, mode);
 }
 void launch_pT(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode) {
   if (ntiles <= 0) return;

@@ -1111,9 +1111,20 @@ struct DirWin {
     return o;
   }
   static constexpr int words() { return base(kLevels + 1); }
-  // pairs of a run: about 4, the runs of a line of nearly equal length
-  static constexpr int runs(int j) { return (pairs(j) + 3) / 4; }
-  static constexpr int run(int j) { return (pairs(j) + runs(j) - 1) / runs(j); }
+};
+
+// Output pairs of a task of level J: about 4, the runs of a line of nearly
+// equal length; in the small tile 1 where the level then has no more tasks
+// than the workgroup threads, 2 at the finest level of the wide workgroup (a
+// pass there costs its latency, and a run of 4 has 4 times the chain: 0.6 us
+// of an inverse transform of 5 levels).
+template <int T, int J, int NT>
+struct DirRun {
+  using W = DirWin<T>;
+  static constexpr int np = W::pairs(J), lines = 2 * W::w(J), up = J > 1 ? W::w(J > 1 ? J - 1 : 1) : 0;
+  static constexpr bool single = T == 32 && lines * np <= NT && up * np <= NT;
+  static constexpr int runs = single ? np : T == 32 && J == 1 && NT > 256 ? 8 : (np + 3) / 4;
+  static constexpr int run = (np + runs - 1) / runs;
 };
 
 // One coefficient's operands: the plain source; r, J^{-1}; r, J^{-1}, p_{k-1};
@@ -1237,38 +1248,38 @@ __device__ __forceinline__ void syn_run_fixed(const float* a_src, const float* d
 }
 
 // Levels J .. 2: columns of the window into B, rows into the coarse band of level J - 1.
-template <int T, int J, bool K1>
+template <int T, int J, int NT, bool K1>
 __device__ __forceinline__ void dir_columns(const Filter& F, const float* A, float* B) {
   using W = DirWin<T>;
-  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J), np = W::pairs(J), at = W::base(J);
-  for (int task = threadIdx.x; task < 2 * w * NR; task += blockDim.x) {
+  constexpr int w = W::w(J), S = W::stride(J), R = DirRun<T, J, NT>::run, NR = DirRun<T, J, NT>::runs, np = W::pairs(J), at = W::base(J);
+  for (int task = threadIdx.x; task < 2 * w * NR; task += NT) {
     const int c = task % (2 * w), p0 = min((task / (2 * w)) * R, np - R);
     syn_run_fixed<R, K1>(A + at + c, A + at + w * S + c, S, p0, F, B + 2 * p0 * S + c, S);
   }
   __syncthreads();
 }
-template <int T, int J, bool K1>
+template <int T, int J, int NT, bool K1>
 __device__ __forceinline__ void dir_level(const Filter& F, float* A, float* B) {
   using W = DirWin<T>;
-  dir_columns<T, J, K1>(F, A, B);
-  constexpr int w = W::w(J), S = W::stride(J), R = W::run(J), NR = W::runs(J), np = W::pairs(J), up = W::w(J - 1);
+  dir_columns<T, J, NT, K1>(F, A, B);
+  constexpr int w = W::w(J), S = W::stride(J), R = DirRun<T, J, NT>::run, NR = DirRun<T, J, NT>::runs, np = W::pairs(J), up = W::w(J - 1);
   constexpr int d = W::drop(J - 1), at = W::base(J - 1), SU = W::stride(J - 1);
-  for (int task = threadIdx.x; task < up * NR; task += blockDim.x) {
+  for (int task = threadIdx.x; task < up * NR; task += NT) {
     const int r = task % up, p0 = min((task / up) * R, np - R);
     const float* Br = B + (r + d) * S;
     syn_run_fixed<R, K1>(Br, Br + w, 1, p0, F, A + at + r * SU + 2 * p0 - d, 1);
   }
   __syncthreads();
 }
-template <int T, int J>
+template <int T, int J, int NT>
 __device__ __forceinline__ void dir_levels(int n, int levels, const Filter& F, float* A, float* B) {
   using W = DirWin<T>;
-  if constexpr (J < W::kLevels) dir_levels<T, J + 1>(n, levels, F, A, B);
+  if constexpr (J < W::kLevels) dir_levels<T, J + 1, NT>(n, levels, F, A, B);
   if (J > levels) return;
   if (J > 3 && n >> (J - 1) <= 4)
-    dir_level<T, J, true>(F, A, B);
+    dir_level<T, J, NT, true>(F, A, B);
   else
-    dir_level<T, J, false>(F, A, B);
+    dir_level<T, J, NT, false>(F, A, B);
 }
 
 // Four consecutive outputs from position e on.
@@ -1340,18 +1351,19 @@ template <int T, int NT, bool K1>
 __device__ __forceinline__ void dir_finest(const OutDst& od, int off, int n, const Tile& t, const Filter& F,
                                            float inv_delta, float* A, float* B) {
   using W = DirWin<T>;
-  constexpr int w = W::w(1), S = W::stride(1), kQ = T / 4, kO = T * kQ / NT;
-  static_assert(T * kQ % NT == 0, "whole rounds of output quadruples");
+  constexpr int w = W::w(1), S = W::stride(1), kQ = T / 4, kO = (T * kQ + NT - 1) / NT;
+  static_assert(T * kQ % NT == 0 || NT % (T * kQ) == 0, "whole rounds of output quadruples");
   OutLoad4 o[kO];
 #pragma unroll
   for (int u = 0; u < kO; ++u) {
-    const int q = threadIdx.x + u * NT;
+    const int q = ((int)threadIdx.x + u * NT) % (T * kQ);
     o[u] = out_fetch4(od, off + (t.ty * T + q / kQ) * n + t.tx * T + 4 * (q % kQ));
   }
-  dir_columns<T, 1, K1>(F, A, B);
+  dir_columns<T, 1, NT, K1>(F, A, B);
 #pragma unroll
   for (int u = 0; u < kO; ++u) {
     const int q = threadIdx.x + u * NT, r = q / kQ, c = q % kQ;
+    if (q >= T * kQ) break;
     const float* Br = B + r * S;
     float x[4];
     syn_run_fixed<2, K1>(Br, Br + w, 1, 2 * c, F, x, 1);
@@ -1387,7 +1399,7 @@ __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDe
   else
     dir_window<T, NT, 1>(pr, n, levels, off, t, ps, iter, c, A);
   __syncthreads();
-  dir_levels<T, 2>(n, levels, F, A, B);
+  dir_levels<T, 2, NT>(n, levels, F, A, B);
   if (n > kResMax)
     dir_finest<T, NT, true>(od, off, n, t, F, inv_delta, A, B);
   else
@@ -1712,11 +1724,14 @@ struct FwdWin {
   static constexpr int W(int j) { return (T >> j) + 4 * ((8 >> j) - 1); }
   static constexpr int SR(int j) { return W(j) + D(j) + 1; }          // LDS stride of the row pass's output
   static constexpr int SX(int j) { return W(j) + 1; }                 // ... of the coarse window
-  static constexpr int runs(int j) { return W(j) / 4; }               // runs of four pairs
-  // column tasks, each a column and a run of four pairs, in classes of whole
+  // output pairs of a task: four at the finest level; below, as few as the
+  // threads allow (a pass there costs its latency, not its reads)
+  static constexpr int run(int j) { return j == 1 ? 4 : T == 64 && j == 2 ? 2 : 1; }
+  static constexpr int runs(int j) { return W(j) / run(j); }
+  // column tasks, each a column and a run of pairs, in classes of whole
   // waves: x-high columns (both halves in y are details), x-low columns
   // under the tile (coarse and detail), the rest of the coarse window
-  static constexpr int det(int j) { return D(j) * D(j) / 4; }
+  static constexpr int det(int j) { return D(j) * D(j) / run(j); }
   static constexpr int pad(int n) { return (n + 63) / 64 * 64; }
   static constexpr int at_low(int j) { return pad(det(j)); }
   static constexpr int at_rest(int j) { return 2 * pad(det(j)); }
@@ -1778,10 +1793,11 @@ __device__ __forceinline__ EpiLoad epi_load(const EpiSrc& s, int e) {
   return l;
 }
 
-// Four outputs from 12 samples: a_k = sum_i f_i x[2k + i].
-__device__ __forceinline__ void ana_run4(const float* x, const float* f, float* a) {
+// R outputs from 2 R + 4 samples: a_k = sum_i f_i x[2k + i].
+template <int R>
+__device__ __forceinline__ void ana_run(const float* x, const float* f, float* a) {
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < R; ++p) {
     a[p] = 0.f;
 #pragma unroll
     for (int i = 0; i < 6; ++i) a[p] = fmaf(f[i], x[2 * p + i], a[p]);
@@ -1807,7 +1823,7 @@ struct FwdTask {
   bool on;
   __device__ __forceinline__ FwdTask(int u) {
     using W = FwdWin<T>;
-    constexpr int D = W::D(J), D4 = D / 4;
+    constexpr int D = W::D(J), D4 = D / W::run(J);
     const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63) + u * NT;
     int e = w0 + ((int)threadIdx.x & 63);
     cls = w0 < W::at_low(J) ? FWD_HIGH : w0 < W::at_rest(J) ? FWD_LOW : FWD_REST;
@@ -1829,20 +1845,21 @@ struct FwdTask {
   __device__ __forceinline__ int pos(const FwdTile& t, int hy, int hx) const {
     constexpr int D = FwdWin<T>::D(J);
     const int half = t.n >> J;
-    return t.off + (hy * half + D * t.ty + 4 * r) * t.n + hx * half + D * t.tx + c;
+    return t.off + (hy * half + D * t.ty + FwdWin<T>::run(J) * r) * t.n + hx * half + D * t.tx + c;
   }
 };
 
-// Epilogue operands of level J's tasks (eight of an x-high task; of an x-low
+// Epilogue operands of level J's tasks (two per pair of an x-high task; of an x-low
 // one those of its details, and of the coarse band where it is the last).
 template <int T, int J, int NT>
 struct FwdOps {
   static constexpr int kR = FwdWin<T>::rounds(J, NT);
-  EpiLoad l[kR][8];
+  EpiLoad l[kR][2 * FwdWin<T>::run(J)];
 };
 template <int T, int J, int NT, int EPI>
 __device__ __forceinline__ void fwd_ops(const EpiSrc& src, const FwdTile& t, FwdOps<T, J, NT>& o) {
   if (EPI == EPI_PLAIN) return;
+  constexpr int RL = FwdWin<T>::run(J);
 #pragma unroll
   for (int u = 0; u < FwdOps<T, J, NT>::kR; ++u) {
     if (u * NT >= FwdWin<T>::at_rest(J)) break;
@@ -1850,18 +1867,18 @@ __device__ __forceinline__ void fwd_ops(const EpiSrc& src, const FwdTile& t, Fwd
     if (k.cls == FWD_HIGH) {
       const int a = k.pos(t, 0, 1), d = k.pos(t, 1, 1);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
+      for (int p = 0; p < RL; ++p) {
         o.l[u][p] = epi_load<EPI>(src, a + p * t.n);
-        o.l[u][4 + p] = epi_load<EPI>(src, d + p * t.n);
+        o.l[u][RL + p] = epi_load<EPI>(src, d + p * t.n);
       }
     } else if (k.cls == FWD_LOW) {
       const int d = k.pos(t, 1, 0);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) o.l[u][4 + p] = epi_load<EPI>(src, d + p * t.n);
+      for (int p = 0; p < RL; ++p) o.l[u][RL + p] = epi_load<EPI>(src, d + p * t.n);
       if (J == 3 && t.last) {
         const int a = k.pos(t, 0, 0);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) o.l[u][p] = epi_load<EPI>(src, a + p * t.n);
+        for (int p = 0; p < RL; ++p) o.l[u][p] = epi_load<EPI>(src, a + p * t.n);
       }
     }
   }
@@ -1873,64 +1890,65 @@ template <int T, int J, int NT, int EPI>
 __device__ __forceinline__ void fwd_columns(const FwdTile& t, const Filter& F, const float* R, float* X,
                                             const FwdOps<T, J, NT>& o, double& acc) {
   using W = FwdWin<T>;
+  constexpr int RL = W::run(J);
   const bool glob = (t.n >> (J - 1)) > kResMax;
 #pragma unroll
   for (int u = 0; u < FwdOps<T, J, NT>::kR; ++u) {
     const FwdTask<T, J, NT> k(u);
     if (!k.on) continue;
-    const float* col = R + 8 * k.r * W::SR(J) + (k.cls == FWD_HIGH ? W::W(J) : 0) + k.c;
-    float x[12], a[4], d[4];
+    const float* col = R + 2 * RL * k.r * W::SR(J) + (k.cls == FWD_HIGH ? W::W(J) : 0) + k.c;
+    float x[2 * RL + 4], a[RL], d[RL];
 #pragma unroll
-    for (int i = 0; i < 12; ++i) x[i] = col[i * W::SR(J)];
-    ana_run4(x, F.h, a);
+    for (int i = 0; i < 2 * RL + 4; ++i) x[i] = col[i * W::SR(J)];
+    ana_run<RL>(x, F.h, a);
     if (k.cls == FWD_HIGH) {
-      ana_run4(x, F.g, d);
+      ana_run<RL>(x, F.g, d);
       const int pa = k.pos(t, 0, 1), pd = k.pos(t, 1, 1);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
+      for (int p = 0; p < RL; ++p) {
         epi_put<EPI>(t.dst, pa + p * t.n, t.ad[J - 1], a[p], t.inv_delta, glob, o.l[u][p], acc);
-        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][4 + p], acc);
+        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][RL + p], acc);
       }
       continue;
     }
     if constexpr (J < 3) {
 #pragma unroll
-      for (int p = 0; p < 4; ++p) X[(4 * k.r + p) * W::SX(J) + k.c] = a[p];
+      for (int p = 0; p < RL; ++p) X[(RL * k.r + p) * W::SX(J) + k.c] = a[p];
     } else if (t.last) {
       const int pa = k.pos(t, 0, 0);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) epi_put<EPI>(t.dst, pa + p * t.n, t.ad[2], a[p], t.inv_delta, glob, o.l[u][p], acc);
+      for (int p = 0; p < RL; ++p) epi_put<EPI>(t.dst, pa + p * t.n, t.ad[2], a[p], t.inv_delta, glob, o.l[u][p], acc);
     } else {
       const int s = t.n >> 3;
 #pragma unroll
-      for (int p = 0; p < 4; ++p) t.ll[(W::D(3) * t.ty + 4 * k.r + p) * s + W::D(3) * t.tx + k.c] = a[p];
+      for (int p = 0; p < RL; ++p) t.ll[(W::D(3) * t.ty + RL * k.r + p) * s + W::D(3) * t.tx + k.c] = a[p];
     }
     if (k.cls == FWD_LOW) {
-      ana_run4(x, F.g, d);
+      ana_run<RL>(x, F.g, d);
       const int pd = k.pos(t, 1, 0);
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
-        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][4 + p], acc);
+      for (int p = 0; p < RL; ++p)
+        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][RL + p], acc);
     }
   }
 }
 
 // Rows of level J (2 or 3) from the coarse window X of level J - 1 into R.
-template <int T, int J>
+template <int T, int J, int NT>
 __device__ __forceinline__ void fwd_rows(const Filter& F, const float* X, float* R) {
   using W = FwdWin<T>;
-  constexpr int NS = W::runs(J), up = W::W(J - 1);
-  for (int e = threadIdx.x; e < up * NS; e += blockDim.x) {
+  constexpr int RL = W::run(J), NS = W::runs(J), up = W::W(J - 1);
+  for (int e = threadIdx.x; e < up * NS; e += NT) {
     const int y = e % up, s = e / up;
-    float x[12], a[4], d[4];
+    float x[2 * RL + 4], a[RL], d[RL];
 #pragma unroll
-    for (int i = 0; i < 12; ++i) x[i] = X[y * W::SX(J - 1) + 8 * s + i];
-    ana_run4(x, F.h, a);
-    ana_run4(x, F.g, d);
+    for (int i = 0; i < 2 * RL + 4; ++i) x[i] = X[y * W::SX(J - 1) + 2 * RL * s + i];
+    ana_run<RL>(x, F.h, a);
+    ana_run<RL>(x, F.g, d);
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      R[y * W::SR(J) + 4 * s + p] = a[p];
-      if (4 * s + p < W::D(J)) R[y * W::SR(J) + W::W(J) + 4 * s + p] = d[p];
+    for (int p = 0; p < RL; ++p) {
+      R[y * W::SR(J) + RL * s + p] = a[p];
+      if (RL * s + p < W::D(J)) R[y * W::SR(J) + W::W(J) + RL * s + p] = d[p];
     }
   }
 }
@@ -1995,8 +2013,8 @@ __global__ __launch_bounds__(NT) void k_fdwt_dir(const ProbDev* P, const LayerDe
     const int e = threadIdx.x + u * NT, y = e / NS, s = e % NS;
     if (e >= kTasks) break;
     float a[4], d[4];
-    ana_run4(v[u], F.h, a);
-    ana_run4(v[u], F.g, d);
+    ana_run<4>(v[u], F.h, a);
+    ana_run<4>(v[u], F.g, d);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       R[y * W::SR(1) + 4 * s + p] = a[p];
@@ -2007,12 +2025,12 @@ __global__ __launch_bounds__(NT) void k_fdwt_dir(const ProbDev* P, const LayerDe
   fwd_columns<T, 1, NT, EPI>(t, F, R, X, o1, acc);
   if (EPI != EPI_PCG) fwd_ops<T, 2, NT, EPI>(src, t, o2);
   __syncthreads();
-  fwd_rows<T, 2>(F, X, R);
+  fwd_rows<T, 2, NT>(F, X, R);
   __syncthreads();
   fwd_columns<T, 2, NT, EPI>(t, F, R, X2, o2, acc);
   if (EPI != EPI_PCG) fwd_ops<T, 3, NT, EPI>(src, t, o3);
   __syncthreads();
-  fwd_rows<T, 3>(F, X2, R3);
+  fwd_rows<T, 3, NT>(F, X2, R3);
   __syncthreads();
   fwd_columns<T, 3, NT, EPI>(t, F, R3, nullptr, o3, acc);
   if (EPI == EPI_PCG || EPI == EPI_RHS || EPI == EPI_RHSQ) {
@@ -2097,17 +2115,25 @@ __device__ __forceinline__ void epi_fetch_levels(const ProbDev& pr, const IoDev&
   if constexpr (M > 2) epi_fetch_levels<M / 2, EPI>(pr, io, iter, off, n, R, m0, o.next);
 }
 
+// What the resident levels need of their layer, read once (behind a store the
+// compiler would read the record again).
+struct ResLayer {
+  int n, off;
+  float inv_delta;
+  float ad[7];  // alpha D by block side 1 .. 64
+};
+
 // One analysis level of side M in LDS (A and B with row stride S), NP output
 // pairs per thread and line: rows A -> B (lanes on rows), then columns B -> A
 // (lanes on consecutive columns) with the epilogue of every detail output
 // from operands already in registers; the coarse block stays in A for the
 // next level.
 template <int M, int S, int EPI>
-__device__ __forceinline__ void epi_level(const LayerDev& ly, const EpiDst& dst, float* A, float* B, const Filter& F,
+__device__ __forceinline__ void epi_level(const ResLayer& ly, const EpiDst& dst, float* A, float* B, const Filter& F,
                                           const EpiLoad* el, double& acc) {
   constexpr int NP = ana_np(M), half = M / 2, lm = ilog2c(M);
   const int n = ly.n, off = ly.off;
-  const float ad = ly.alpha_d[lm - 1], inv_delta = ly.inv_delta;
+  const float ad = ly.ad[lm - 1], inv_delta = ly.inv_delta;
   const bool mine = (int)threadIdx.x < M * (half / NP);
   const int c = threadIdx.x & (M - 1), K0 = ((int)threadIdx.x >> lm) * NP;
   if (mine) {  // rows
@@ -2135,7 +2161,7 @@ __device__ __forceinline__ void epi_level(const LayerDev& ly, const EpiDst& dst,
 }
 
 template <int M, int S, int EPI>
-__device__ __forceinline__ void epi_levels(const LayerDev& ly, const EpiDst& dst, float* A, float* B, int R, int m0,
+__device__ __forceinline__ void epi_levels(const ResLayer& ly, const EpiDst& dst, float* A, float* B, int R, int m0,
                                            const Filter& F, const LevelOps<M>& o, double& acc) {
   if (M <= R && M > m0) epi_level<M, S, EPI>(ly, dst, A, B, F, o.l, acc);
   if constexpr (M > 2) epi_levels<M / 2, S, EPI>(ly, dst, A, B, R, m0, F, o.next, acc);
@@ -2157,17 +2183,25 @@ __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const Layer
   __shared__ double sh[16];
   const Tile t = my_tile(tiles);
   const ProbDev& pr = P[t.prob];
-  const LayerDev& ly = LD[t.mask];  // the global layer index, carried by the tile
+  const LayerDev& ld = LD[t.mask];  // the global layer index, carried by the tile
   const IoDev& io = IO[t.prob];
-  const int n = ly.n, R = ly.fres, lr = __builtin_ctz(R), off = ly.off;
+  const int n = ld.n, R = ld.fres, lr = __builtin_ctz(R), off = ld.off;
   constexpr int S = RMAX + 1;
-  const int nt = blockDim.x;
-  const int ng = ly.fsteps;
-  const gptr_f in = (gptr_f)((ng == 0) ? pr.phiadj + off : ((((ng - 1) & 1) ? pr.tmpb : pr.tmpa) + ly.tmp_off));
+  constexpr int nt = 1024;
+  const int ng = ld.fsteps;
+  ResLayer ly;
+  ly.n = n;
+  ly.off = off;
+  ly.inv_delta = ld.inv_delta;
+#pragma unroll
+  for (int j = 0; j < 7; ++j) ly.ad[j] = ld.alpha_d[j];
+  double* const dots = pr.dots;
+  const int n_dots = pr.n_dots;
+  const gptr_f in = (gptr_f)((ng == 0) ? pr.phiadj + off : ((((ng - 1) & 1) ? pr.tmpb : pr.tmpa) + ld.tmp_off));
   const int istride = (ng == 0) ? n : R;
-  const int m0 = n >> ly.levels;
-  // the whole block's loads in flight together, kUL per thread at 1024
-  // threads per workgroup (the launch shape), without branches (indices
+  const int m0 = n >> ld.levels;
+  const float ad_ll = ld.alpha_d[__builtin_ctz(m0)];
+  // the whole block's loads in flight together, kUL per thread, without branches (indices
   // past the block clamped): with a load under a condition the compiler
   // waited for each before the next
   constexpr int kUL = RMAX * RMAX / 1024 > 0 ? RMAX * RMAX / 1024 : 1;
@@ -2183,8 +2217,6 @@ __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const Layer
       const int e = threadIdx.x + u * nt;
       if (e < R * R) A[(e >> lr) * S + (e & (R - 1))] = v[u];
     }
-    for (int e = threadIdx.x + kUL * nt; e < R * R; e += nt)  // workgroups under 1024 threads only
-      A[(e >> lr) * S + (e & (R - 1))] = in[(e >> lr) * istride + (e & (R - 1))];
   };
   double acc = 0.0;
   const EpiDst dst = epi_dst(pr, io, iter);
@@ -2209,7 +2241,7 @@ __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const Layer
       epi_levels<RMAX / 2, S, EPI>(ly, dst, A, B, R, m0, F, rest, acc);
     }
   }
-  const float adll = ly.alpha_d[__builtin_ctz(m0)];
+  const float adll = ad_ll;
   for (int e = threadIdx.x; e < m0 * m0; e += nt) {
     const int r = e / m0, c = e - r * m0;
     const int pos = off + r * n + c;
@@ -2218,7 +2250,7 @@ __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const Layer
   }
   if (EPI == EPI_PCG || EPI == EPI_RHS || EPI == EPI_RHSQ) {
     const double s = block_sum(acc, sh, nt);
-    if (threadIdx.x == 0) ((gptr_wd)pr.dots)[(long)dot_group_of(EPI, iter) * pr.n_dots + t.slot] = s;
+    if (threadIdx.x == 0) ((gptr_wd)dots)[(long)dot_group_of(EPI, iter) * n_dots + t.slot] = s;
   }
 }
 
@@ -2275,6 +2307,10 @@ __global__ __launch_bounds__(kSensThreads) __attribute__((amdgpu_waves_per_eu(8)
                      : (mode == PG_POL_IN || mode == PG_APREV) ? io.state + 3L * pr.n_c
                                                                : io.in;
   const int N = w.N, nc = w.nc;
+  // the outputs' places, read before the first store
+  const gptr_w sdo = (gptr_w)(pr.sd + w.sp_off);
+  const int sdl = w.sp_len;
+  const gptr_w pp = (gptr_w)(pr.part + w.part_off + 4 * (t.ty * w.tiles_side + t.tx));
   const int i0 = t.ty * kTileS, j0 = t.tx * kTileS;
   // subaperture owned by this thread and its operands
   const int li = threadIdx.x >> 4, lj = threadIdx.x & 15;
@@ -2429,13 +2465,12 @@ __global__ __launch_bounds__(kSensThreads) __attribute__((amdgpu_waves_per_eu(8)
     return;
   }
   if (act) {
-    ((gptr_w)pr.sd)[w.sp_off + si] = sx;
-    ((gptr_w)pr.sd)[w.sp_off + w.sp_len + si] = sy;
+    sdo[si] = sx;
+    sdo[sdl + si] = sy;
   }
   float a[4] = {sx, sy, cx, cy};
   block_sum4(a, sh, kSensThreads / 64);
   if (threadIdx.x == 0) {
-    const gptr_w pp = (gptr_w)(pr.part + w.part_off + 4 * (t.ty * w.tiles_side + t.tx));
     pp[0] = a[0];
     pp[1] = a[1];
     pp[2] = a[2];
@@ -2464,7 +2499,8 @@ __global__ __launch_bounds__(256) void k_slopes_in(const ProbDev* P, const WfsDe
   const gptr_f cinv = (gptr_f)(pr.cinv + w.cinv_off);
   const gptr_w sd = (gptr_w)(pr.sd + w.sp_off);
   const gptr_i srow = (gptr_i)(pr.srow + w.rb_off);
-  const int cs0 = w.cs_off, cs1 = w.cs_off + w.n_active;
+  const int cs0 = w.cs_off, cs1 = w.cs_off + w.n_active, sl = w.sp_len;
+  const gptr_w part = (gptr_w)(pr.part + w.part_off);
   // Loads without per-subaperture branches (indices past the grid or of an
   // inactive subaperture clamped, their values unused), so that the
   // compiler's waits do not hold each map load before the next is requested.
@@ -2528,7 +2564,7 @@ __global__ __launch_bounds__(256) void k_slopes_in(const ProbDev* P, const WfsDe
     a[4 * u + 3] = c1[u] * sx[u] + c2[u] * sy[u];
     if (ci[u] >= 0) {
       sd[si[u]] = sx[u];
-      sd[w.sp_len + si[u]] = sy[u];
+      sd[sl + si[u]] = sy[u];
     }
   }
   block_sumk<16>(a, sh, 4);
@@ -2537,7 +2573,7 @@ __global__ __launch_bounds__(256) void k_slopes_in(const ProbDev* P, const WfsDe
     for (int u = 0; u < 4; ++u) {
       const int ty = 2 * t.ty + (u >> 1), tx = 2 * t.tx + (u & 1);
       if (ty < ts && tx < ts) {
-        const gptr_w pp = (gptr_w)(pr.part + w.part_off + 4 * (ty * ts + tx));
+        const gptr_w pp = part + 4 * (ty * ts + tx);
         pp[0] = a[4 * u];
         pp[1] = a[4 * u + 1];
         pp[2] = a[4 * u + 2];
@@ -3370,7 +3406,7 @@ __global__ __launch_bounds__(256) void k_aug_store(const ProbDev* P, const IoDev
 // rounded products and sums in the same order (bitwise the same x), with
 // a_{k-1} summed again from the same slots; 8 of every 56 bytes per
 // coefficient less over the pair.
-template <int XM>
+template <int XM, bool COARSE>
 __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* IO, const Tile* tiles, int iter,
                                                 const CoarseDev* C) {
   __shared__ double sh[4];
@@ -3395,11 +3431,26 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
   int nr, nrm = 0;
   const double* sr = rho_slots(pr, iter, nr);
   const double* srm = XM == UPD_X_PAIR ? rho_slots(pr, iter - 1, nrm) : sr;
-  const double* const sl[5] = {sr, dot_group(pr, pi_grp(iter)), C ? coarse_slots(C[t.prob], iter) : sr, srm,
-                               XM == UPD_X_PAIR ? dot_group(pr, pi_grp(iter - 1)) : sr};
-  const int nn[5] = {nr, pr.n_slots_fdwt, C ? C[t.prob].n_slots : 0, nrm, XM == UPD_X_PAIR ? pr.n_slots_fdwt : 0};
-  SlotLoads<5, 2> sloads;
-  slots_issue<5, 2>(sl, nn, sloads);
+  // the second two: of the coarse part (a converged solve's steps form no pairs), or of the pair
+  constexpr int G = COARSE ? 3 : XM == UPD_X_PAIR ? 4 : 2;
+  static_assert(!COARSE || XM == UPD_X_ONE, "no pairs with the coarse part");
+  const double* sl[G];
+  int nn[G];
+  sl[0] = sr;
+  nn[0] = nr;
+  sl[1] = dot_group(pr, pi_grp(iter));
+  nn[1] = pr.n_slots_fdwt;
+  if constexpr (COARSE) {
+    sl[2] = coarse_slots(C[t.prob], iter);
+    nn[2] = C[t.prob].n_slots;
+  } else if constexpr (XM == UPD_X_PAIR) {
+    sl[2] = srm;
+    nn[2] = nrm;
+    sl[3] = dot_group(pr, pi_grp(iter - 1));
+    nn[3] = pr.n_slots_fdwt;
+  }
+  SlotLoads<G, 2> sloads;
+  slots_issue<G, 2>(sl, nn, sloads);
   // loads without branches (indices clamped to the chunk), so that the slot
   // sums below wait only for the slots
 #pragma unroll
@@ -3415,12 +3466,12 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
     jj[u] = jv[e];
   }
   // alpha = rho_k / pi_k
-  double o[5];
-  slots_reduce<5, 2>(sl, nn, sloads, o);
-  const double rho = o[0] + o[2], pi = o[1];
+  double o[G];
+  slots_reduce<G, 2>(sl, nn, sloads, o);
+  const double rho = COARSE ? o[0] + o[G - 1] : o[0], pi = o[1];
   const float a = (float)((pi > 0.0) ? rho / pi : 0.0);
   // a_{k-1} as the previous step formed it (a frame's steps have no coarse part)
-  const double rhom = o[3] + 0.0, pim = o[4];
+  const double rhom = o[G - 2], pim = o[G - 1];
   const float am = (float)((pim > 0.0) ? rhom / pim : 0.0);
   // breakdown: a nonzero residual with p^T M p <= 0 (M is positive definite,
   // so only rounding or non-finite inputs get here), or a negative or
@@ -3459,7 +3510,7 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
     }
   }
   if (pr.aug_keep == 0) {
-    const double s = block_sum(acc, sh, blockDim.x);
+    const double s = block_sum(acc, sh, 256);
     if (threadIdx.x == 0) ((gptr_wd)pr.dots)[(long)rho_grp(iter + 1) * pr.n_dots + t.slot] = s;
     return;
   }
@@ -3481,7 +3532,7 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
     }
   }
   __shared__ double shk[(kAugMax + 1) * 4];
-  block_sumk_d<kAugMax + 1>(tk, shk, blockDim.x >> 6);
+  block_sumk_d<kAugMax + 1>(tk, shk, 4);
   if (threadIdx.x == 0) {
     ((gptr_wd)pr.dots)[(long)rho_grp(iter + 1) * pr.n_dots + t.slot] = tk[0];
 #pragma unroll
@@ -3515,7 +3566,7 @@ __global__ __launch_bounds__(256) void k_solve_init(const ProbDev* P, const IoDe
     acc += (double)v.x * (double)v.x * (double)j.x + (double)v.y * (double)v.y * (double)j.y +
            (double)v.z * (double)v.z * (double)j.z + (double)v.w * (double)v.w * (double)j.w;
   }
-  const double s = block_sum(acc, sh, blockDim.x);
+  const double s = block_sum(acc, sh, 256);
   if (threadIdx.x == 0) pr.dots[(long)rho_grp(0) * pr.n_dots + t.slot] = s;
 }
 
@@ -3714,7 +3765,7 @@ __global__ __launch_bounds__(256) void k_grad_height(const ProbDev* P, const Lay
     const float d = dtx * ddx + dty * ddy;
     acc = (double)pr.vadj[w.v_off + i * nc + j] * (double)d;
   }
-  const double s = block_sum(acc, sh, blockDim.x);
+  const double s = block_sum(acc, sh, 256);
   if (threadIdx.x == 0) pr.gslots[pr.n_gp + term * pr.n_gh + t.slot] = s;
 }
 
@@ -3735,7 +3786,7 @@ __global__ __launch_bounds__(256) void k_grad_prior(const ProbDev* P, const Laye
     const int j = (mx < m0) ? jmin : 31 - __clz(mx);
     acc += (double)g.lam[ly.off + e] * (double)g.c[ly.off + e] * ly.d64[j];
   }
-  const double s = block_sum(acc, sh, blockDim.x);
+  const double s = block_sum(acc, sh, 256);
   if (threadIdx.x == 0) pr.gslots[ly.gp_off + t.ty] = s;
 }
 
@@ -3873,17 +3924,26 @@ void launch_idwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int src
 void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode,
                      int iter, const CoarseDev* C) {
   if (ntiles <= 0) return;
-#define FEWHA_ID(T, CO) \
-  k_idwt_dir<T, 256, CO><<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter, C)
+#define FEWHA_ID(T, NT, CO) \
+  k_idwt_dir<T, NT, CO><<<ntiles, NT, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter, C)
+  // no more workgroups than compute units: twice the threads each (96 tiles of
+  // the 39 m system 6.4 -> 6.0 us; 336 tiles of nine layers 7.8 -> 8.1 us)
+  const bool wide = ntiles <= kCus;
   if (tile == 64) {
     if (C)
-      FEWHA_ID(64, true);
+      FEWHA_ID(64, 256, true);
     else
-      FEWHA_ID(64, false);
+      FEWHA_ID(64, 256, false);
   } else if (C) {
-    FEWHA_ID(32, true);
+    if (wide)
+      FEWHA_ID(32, 512, true);
+    else
+      FEWHA_ID(32, 256, true);
   } else {
-    FEWHA_ID(32, false);
+    if (wide)
+      FEWHA_ID(32, 512, false);
+    else
+      FEWHA_ID(32, 256, false);
   }
 #undef FEWHA_ID
 }
@@ -4004,11 +4064,13 @@ void launch_pT(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode) {
 void launch_update(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter, const CoarseDev* C, int xm) {
   if (ntiles <= 0) return;
   if (xm == UPD_X_DEFER)
-    k_update<UPD_X_DEFER><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    k_update<UPD_X_DEFER, false><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
   else if (xm == UPD_X_PAIR)
-    k_update<UPD_X_PAIR><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    k_update<UPD_X_PAIR, false><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+  else if (C)
+    k_update<UPD_X_ONE, true><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
   else
-    k_update<UPD_X_ONE><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    k_update<UPD_X_ONE, false><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
 }
 void launch_coarse(const LaunchArgs& a, const CoarseTile* tiles, int ntiles, const CoarseDev* members, int k) {
   if (ntiles > 0) k_coarse<<<ntiles, kCoarseThreads, 0, a.stream>>>(tiles, members, k);

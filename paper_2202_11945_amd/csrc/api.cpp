@@ -24,13 +24,11 @@ using namespace fewha;
 
 namespace {
 
-constexpr int kRing = 8;          // pinned staging slots for per-call I/O tables
 constexpr int kMaxIters = 256;    // PCG iterations per reconstruct call (graph-captured frames)
 constexpr int kMaxSolveIters = 1 << 24;  // PCG iterations of one solve
 constexpr int kSolveCheck = 16;   // iterations between two convergence checks of a solve
 constexpr int kMaxSweeps = 32;    // refinement sweeps of one solve
 static_assert(kSolveCheck == kDotRing, "a captured block of steps replays on the ring's own period");
-static_assert(sizeof(GradIo) <= sizeof(IoDev), "per-call tables share the staging ring");
 
 int ilog2i(int n) {
   int k = 0;
@@ -105,10 +103,6 @@ struct Plan {
   FitDev* dF = nullptr;
   int max_fit_iters = 0;
   Filter F{};
-  IoDev* pinned[kRing] = {nullptr};
-  hipEvent_t ev[kRing] = {nullptr};
-  bool ev_used[kRing] = {false};
-  int ring = 0;
   std::map<int, hipGraphExec_t> graphs;
   std::map<int, hipGraph_t> graph_defs;
   hipStream_t cap_stream = nullptr;
@@ -163,10 +157,6 @@ void destroy_plan(Plan* p) {
   if (p->device >= 0) (void)hipSetDevice(p->device);
   for (auto& kv : p->graphs) (void)hipGraphExecDestroy(kv.second);
   for (auto& kv : p->graph_defs) (void)hipGraphDestroy(kv.second);
-  for (int i = 0; i < kRing; ++i) {
-    if (p->ev[i]) (void)hipEventDestroy(p->ev[i]);
-    if (p->pinned[i]) (void)hipHostFree(p->pinned[i]);
-  }
   for (float* s : p->prof_state)
     if (s) (void)hipFree(s);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
@@ -1313,10 +1303,6 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   HIP_TRY(hipMemcpy(P.dL, P.hL.data(), sizeof(LayerDev) * P.hL.size(), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(P.dW, P.hW.data(), sizeof(WfsDev) * P.hW.size(), hipMemcpyHostToDevice));
   if (!P.hT.empty()) HIP_TRY(hipMemcpy(P.dT, P.hT.data(), sizeof(Tile) * P.hT.size(), hipMemcpyHostToDevice));
-  for (int i = 0; i < kRing; ++i) {
-    HIP_TRY(hipHostMalloc((void**)&P.pinned[i], sizeof(IoDev) * P.nprob_all, hipHostMallocDefault));
-    HIP_TRY(hipEventCreateWithFlags(&P.ev[i], hipEventDisableTiming));
-  }
   HIP_TRY(hipHostMalloc((void**)&P.rho_host, sizeof(double) * P.nprob, hipHostMallocMapped | hipHostMallocCoherent));
   HIP_TRY(hipHostGetDevicePointer((void**)&P.rho_dev, P.rho_host, 0));
   HIP_TRY(hipStreamCreateWithFlags(&P.cap_stream, hipStreamNonBlocking));
@@ -1421,19 +1407,14 @@ fewha_status setup_streamed(Plan& P, long n_slopes, int G, std::string& err) {
   return FEWHA_OK;
 }
 
-// Stage a per-call table (nprob entries, zero-padded to nprob_all) and copy
-// it to the device, stream ordered.  The pinned slot is reused only after the
-// copy that read it has completed.
+// A per-call table (nprob entries, zero-padded to nprob_all) into device
+// memory, stream ordered: the entries travel as kernel arguments.
 template <typename T>
 fewha_status upload_table(Plan& P, const std::vector<T>& v, hipStream_t s, T* dst, std::string& err) {
-  const int slot = P.ring;
-  P.ring = (P.ring + 1) % kRing;
-  if (P.ev_used[slot]) HIP_TRY(hipEventSynchronize(P.ev[slot]));
-  std::memset(P.pinned[slot], 0, sizeof(T) * P.nprob_all);
-  std::memcpy(P.pinned[slot], v.data(), sizeof(T) * P.nprob);
-  HIP_TRY(hipMemcpyAsync(dst, P.pinned[slot], sizeof(T) * P.nprob_all, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipEventRecord(P.ev[slot], s));
-  P.ev_used[slot] = true;
+  static_assert(sizeof(T) % sizeof(uint64_t) == 0 && alignof(T) <= alignof(uint64_t), "whole words");
+  launch_table((const uint64_t*)v.data(), (int)(sizeof(T) / sizeof(uint64_t)) * P.nprob, (uint64_t*)dst,
+               (int)(sizeof(T) / sizeof(uint64_t)) * P.nprob_all, s);
+  HIP_TRY(hipGetLastError());
   return FEWHA_OK;
 }
 fewha_status upload_io(Plan& P, const std::vector<IoDev>& io, hipStream_t s, IoDev* dst, std::string& err) {
@@ -2529,21 +2510,13 @@ fewha_status fewha_reconstruct_noalloc(fewha_ctx* c, const float* slopes, float*
   if (P.na_bytes > kNoAllocBytes)
     return fail(c, FEWHA_EINVAL, "reconstruct_noalloc: the frame needs " + std::to_string(P.na_bytes) +
                                      " bytes of scratch; the static scratch holds " + std::to_string(kNoAllocBytes));
-  // the per-call table through a pinned slot of the ring (no host or device allocation)
-  const int slot = P.ring;
-  P.ring = (P.ring + 1) % kRing;
-  if (P.ev_used[slot] && hipEventSynchronize(P.ev[slot]) != hipSuccess)
-    return fail(c, FEWHA_EDEVICE, "reconstruct_noalloc: staging event failed");
-  IoDev* io = P.pinned[slot];
-  std::memset(io, 0, sizeof(IoDev) * P.nprob_all);
-  io[0].in = slopes;
-  io[0].state = state;
-  io[0].layers_out = layers_out;
-  io[0].dm_out = dm_out;
-  if (hipMemcpyAsync(P.na_io, io, sizeof(IoDev) * P.nprob_all, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-      hipEventRecord(P.ev[slot], c->stream) != hipSuccess)
-    return fail(c, FEWHA_EDEVICE, "reconstruct_noalloc: staging copy failed");
-  P.ev_used[slot] = true;
+  IoDev io{};
+  io.in = slopes;
+  io.state = state;
+  io.layers_out = layers_out;
+  io.dm_out = dm_out;
+  constexpr int kWords = (int)(sizeof(IoDev) / sizeof(uint64_t));
+  launch_table((const uint64_t*)&io, kWords, (uint64_t*)P.na_io, kWords * P.nprob_all, c->stream);
   LaunchArgs a = args(P, c->stream, P.na_io);
   a.P = P.dPna;
   enq_reconstruct(P, a, iters);

@@ -56,6 +56,8 @@ struct LaunchArgs {
 void launch_idwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int src_mode, int out_mode, int iter);
 // the whole inverse transform in one launch of T x T output tiles (tile = T = 32 or 64)
 // (C: the search direction includes the coarse-level correction of a converged solve)
+// words of v, then zeros up to n_dst, to dst
+void launch_table(const uint64_t* v, int n, uint64_t* dst, int n_dst, hipStream_t stream);
 void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode, int iter,
                      const CoarseDev* C = nullptr);
 // the resident inverse levels over four workgroups per (problem, layer): tile.tx = quadrant

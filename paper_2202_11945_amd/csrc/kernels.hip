@@ -9,6 +9,9 @@
 // pairs), so a thread keeps several global loads in flight.
 #include "kernels.h"
 
+#include <algorithm>
+#include <cstring>
+
 namespace fewha {
 
 // ---------------------------------------------------------------- helpers
@@ -3907,6 +3910,28 @@ __global__ __launch_bounds__(1024) void k_fit_cg(const FitDev* F, const ProbDev*
   }
 }
 
+// ------------------------------------------------------- per-call tables
+// N words of a table from the kernel's own arguments (zeros from word n on):
+// the caller's pointers reach the device with the launch itself, where a copy
+// from pinned memory cost its own start and an event (one normal operator of
+// the 39 m system 31.1 -> 27.7 us, one propagation of the 8 m system 14 ->
+// 10.5 us).  Arguments hold 480 words (68 records) beside the rest; one
+// problem's take the small kernel, whose argument copy is a tenth.
+template <int N>
+struct TableArg {
+  uint64_t v[N];
+};
+constexpr int kTableMax = 480;
+template <int N>
+__global__ __launch_bounds__(64) void k_table(const TableArg<N> a, uint64_t* dst, int n, int n_dst) {
+  typedef uint64_t __attribute__((address_space(1)))* gptr_w64;
+#pragma unroll
+  for (int u = 0; u < (N + 63) / 64; ++u) {
+    const int i = threadIdx.x + 64 * u;
+    if (i < n_dst) ((gptr_w64)dst)[i] = i < n ? a.v[min(i, N - 1)] : 0;
+  }
+}
+
 // ------------------------------------------------------------ launchers
 constexpr int kCus = 256;  // compute units
 
@@ -3920,6 +3945,21 @@ void launch_idwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int src
     k_idwt_res<64><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
   else
     k_idwt_res<128><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter);
+}
+template <int N>
+static void launch_table_n(const uint64_t* v, int n, uint64_t* dst, int n_dst, hipStream_t stream) {
+  TableArg<N> a;
+  std::memcpy(a.v, v, sizeof(uint64_t) * n);
+  k_table<N><<<1, 64, 0, stream>>>(a, dst, n, n_dst);
+}
+void launch_table(const uint64_t* v, int n, uint64_t* dst, int n_dst, hipStream_t stream) {
+  for (int o = 0; o < n_dst; o += kTableMax) {
+    const int m = std::min(n_dst - o, kTableMax), w = std::min(std::max(n - o, 0), m);
+    if (m <= 32)
+      launch_table_n<32>(v + std::min(o, n), w, dst + o, m, stream);
+    else
+      launch_table_n<kTableMax>(v + std::min(o, n), w, dst + o, m, stream);
+  }
 }
 void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode,
                      int iter, const CoarseDev* C) {

@@ -102,6 +102,7 @@ struct Plan {
   int nprob_all = 0;                         // problems plus two fitting views per fitted problem
   FitDev* dF = nullptr;
   int max_fit_iters = 0;
+  int aug_max = 0;                           // most directions kept by a problem (augmented PCG)
   Filter F{};
   std::map<int, hipGraphExec_t> graphs;
   std::map<int, hipGraph_t> graph_defs;
@@ -583,6 +584,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
     pd.fitted = m.fit.on ? 1 : 0;
     pd.closed = m.closed ? 1 : 0;
     pd.aug_keep = m.aug_keep;
+    P.aug_max = std::max(P.aug_max, m.aug_keep);
     pd.gain = (float)m.gain;
     int tmp_total = 0;
     for (int l = 0; l < L; ++l) {
@@ -1455,6 +1457,7 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
   a.stream = s;
   a.res_max = P.ires_max;
   a.fres_max = P.fres_max;
+  a.aug_max = P.aug_max;
   a.pt_rows = P.pt_rows;
   a.pt_wide = P.pt_wide ? 1 : 0;
   a.pt_split = P.pt_split ? 1 : 0;

@@ -3219,184 +3219,279 @@ __device__ __forceinline__ void aug_solve(const AugFactor& f, int m, const doubl
       x[k] = (y[k] - a) / f.L[k][k];
     }
 }
-__device__ __forceinline__ double aug_group_sum(const ProbDev& pr, int g) {
-  return wave_sum_slots(pr.aug_slots + (long)g * pr.n_slots_upd, pr.n_slots_upd);
+// The kernels below are instantiated for at most KM = 2 or kAugMax kept
+// directions (the plan's most); a workgroup takes one vector-update chunk as
+// two 16-byte pieces per thread.  All vector loads are requested before the
+// slot sums, those of a kept direction whether or not it is valid yet (it
+// lies in the state; unused then).  Bound: the launch and one memory round
+// trip.  One 37 m problem with two directions: gram 8.6 -> 3.1, start 9.3 -> 4.2,
+// direction 8.1 -> 3.1, store 5.4 -> 2.1 us, against scalar loads that waited
+// for the sums and these for one another.
+constexpr int kAugV = kUpdChunk / 4 / 256;  // pieces per thread
+template <int KM>
+struct AugVec {
+  v4f v[KM][kAugV];
+  // directions (or images) src + k n, k < keep, pieces ei of the chunk
+  __device__ __forceinline__ void load(const float* src, long n, int keep, const int (&ei)[kAugV]) {
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+      const gptr_f s = (gptr_f)(src + min(k, keep - 1) * n);
+#pragma unroll
+      for (int u = 0; u < kAugV; ++u) v[k][u] = *(gptr_f4u)(s + 4 * ei[u]);
+    }
+  }
+};
+// this thread's pieces of chunk ty of n coefficients: the index (clamped to
+// the chunk's last piece) and whether it is there
+__device__ __forceinline__ void aug_pieces(int ty, int n, int (&ei)[kAugV], bool (&on)[kAugV]) {
+  const int e0 = ty * (kUpdChunk / 4), e1 = min(e0 + kUpdChunk / 4, n / 4);
+#pragma unroll
+  for (int u = 0; u < kAugV; ++u) {
+    const int e = e0 + (int)threadIdx.x + u * 256;
+    on[u] = e < e1;
+    ei[u] = min(e, e1 - 1);
+  }
 }
 
 // Partial sums of W^T r_0 and of the lower triangle of W^T A W over one
 // chunk of coefficients (r_0: the warm-start residual in the state).
+template <int KM>
 __global__ __launch_bounds__(256) void k_aug_gram(const ProbDev* P, const IoDev* IO, const Tile* tiles) {
-  __shared__ double sh[(kAugMax + kAugMax * (kAugMax + 1) / 2) * 4];
+  constexpr int NG = KM + KM * (KM + 1) / 2;
+  __shared__ double sh[NG * 4];
   const Tile t = my_tile(tiles);
   const ProbDev& pr = P[t.prob];
   const IoDev& io = IO[t.prob];
   const AugView w = aug_view(pr, io);
-  constexpr int NG = kAugMax + kAugMax * (kAugMax + 1) / 2;
+  const int keep = pr.aug_keep;
+  double* const slots = pr.aug_slots;
+  const int ns = pr.n_slots_upd;
+  const gptr_f4u r = (gptr_f4u)(io.state + 2L * pr.n_c);
+  int ei[kAugV];
+  bool on[kAugV];
+  aug_pieces(t.ty, pr.n_c, ei, on);
+  AugVec<KM> wp, wq;
+  v4f rr[kAugV];
+  wp.load(w.P, pr.n_c, keep, ei);
+  wq.load(w.Q, pr.n_c, keep, ei);
+#pragma unroll
+  for (int u = 0; u < kAugV; ++u) rr[u] = r[ei[u]];
   double a[NG];
 #pragma unroll
   for (int k = 0; k < NG; ++k) a[k] = 0.0;
-  const int e0 = t.ty * kUpdChunk, e1 = min(e0 + kUpdChunk, pr.n_c);
-  const gptr_f r = (gptr_f)(io.state + 2L * pr.n_c);
-  for (int e = e0 + (int)threadIdx.x; e < e1; e += 256) {
-    const double re = r[e];
-    double qv[kAugMax];
 #pragma unroll
-    for (int l = 0; l < kAugMax; ++l) qv[l] = l < w.m ? (double)((gptr_f)(w.Q + (long)l * pr.n_c))[e] : 0.0;
+  for (int u = 0; u < kAugV; ++u)
 #pragma unroll
-    for (int k = 0; k < kAugMax; ++k) {
-      if (k >= w.m) break;
-      const double pk = ((gptr_f)(w.P + (long)k * pr.n_c))[e];
-      a[kAugD + k] += pk * re;
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int l = 0; l <= k; ++l) a[kAugMax + k * (k + 1) / 2 + l] += pk * qv[l];  // row k, column l
-    }
-  }
+      for (int k = 0; k < KM; ++k) {
+        if (!on[u] || k >= w.m) break;
+        const double pk = wp.v[k][u][i];
+        a[k] += pk * (double)rr[u][i];
+#pragma unroll
+        for (int l = 0; l <= k; ++l) a[KM + k * (k + 1) / 2 + l] += pk * (double)wq.v[l][u][i];  // row k, column l
+      }
   block_sumk_d<NG>(a, sh, 4);
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int k = 0; k < NG; ++k) ((gptr_wd)pr.aug_slots)[(long)(kAugD + k) * pr.n_slots_upd + t.slot] = a[k];
+    for (int k = 0; k < NG; ++k) ((gptr_wd)slots)[(long)(k < KM ? kAugD + k : kAugG + k - KM) * ns + t.slot] = a[k];
 }
 
 // The projected start of the augmented PCG: y = G^{-1} W^T r_0,
 // x_0 = c + W y, r_0 <- r_0 - (A W) y (in the state), and the partial sums
 // of rho_0 = r_0^T J^{-1} r_0 and of (A W)^T J^{-1} r_0.  The first chunk also
-// stores the factor of G for the direction kernel.
+// stores the factor of G for the direction kernel.  Every wave solves the
+// small system itself.
+template <int KM>
 __global__ __launch_bounds__(256) void k_aug_init(const ProbDev* P, const IoDev* IO, const Tile* tiles) {
-  __shared__ double sh[(kAugMax + 1) * 4];
-  __shared__ double ys[kAugMax];
+  constexpr int NG = KM + KM * (KM + 1) / 2;
+  __shared__ double sh[(KM + 1) * 4];
   const Tile t = my_tile(tiles);
   const ProbDev& pr = P[t.prob];
   const IoDev& io = IO[t.prob];
   const AugView w = aug_view(pr, io);
-  if (threadIdx.x < 64) {  // wave 0: the small system (every lane the same)
-    double g[kAugMax][kAugMax], d[kAugMax], y[kAugMax];
+  double* const slots = pr.aug_slots;
+  const gptr_wd fac = (gptr_wd)pr.aug_fac;
+  const int ns = pr.n_slots_upd;
+  const gptr_w4u x = (gptr_w4u)io.state;
+  const gptr_w4u r = (gptr_w4u)(io.state + 2L * pr.n_c);
+  const gptr_f4u jv = (gptr_f4u)pr.jinv;
+  const double* sl[NG];
+  int nn[NG];
+#pragma unroll
+  for (int k = 0; k < NG; ++k) {
+    sl[k] = slots + (long)(k < KM ? kAugD + k : kAugG + k - KM) * ns;
+    nn[k] = ns;
+  }
+  SlotLoads<NG, 1> S;
+  slots_issue<NG, 1>(sl, nn, S);
+  int ei[kAugV];
+  bool on[kAugV];
+  aug_pieces(t.ty, pr.n_c, ei, on);
+  AugVec<KM> wp, wq;
+  v4f xx[kAugV], rr[kAugV], jj[kAugV];
+#pragma unroll
+  for (int u = 0; u < kAugV; ++u) {
+    xx[u] = x[ei[u]];
+    rr[u] = r[ei[u]];
+    jj[u] = jv[ei[u]];
+  }
+  wp.load(w.P, pr.n_c, pr.aug_keep, ei);
+  wq.load(w.Q, pr.n_c, pr.aug_keep, ei);
+  double o[NG];
+  slots_reduce<NG, 1>(sl, nn, S, o);
+  double g[kAugMax][kAugMax], d[kAugMax], y[kAugMax];
+#pragma unroll
+  for (int k = 0; k < kAugMax; ++k) {
+    d[k] = k < KM && k < w.m ? o[k < KM ? k : 0] : 0.0;
+#pragma unroll
+    for (int l = 0; l < kAugMax; ++l)
+      g[k][l] = k < KM && l <= k && k < w.m ? o[k < KM && l <= k ? KM + k * (k + 1) / 2 + l : 0] : 0.0;
+  }
+  AugFactor f;
+  aug_factor(g, w.m, f);
+  aug_solve(f, w.m, d, y);
+  float yk[KM];
+#pragma unroll
+  for (int k = 0; k < KM; ++k) yk[k] = (float)y[k];
+  if (t.ty == 0 && threadIdx.x == 0) {
 #pragma unroll
     for (int k = 0; k < kAugMax; ++k) {
-      d[k] = k < w.m ? aug_group_sum(pr, kAugD + k) : 0.0;
 #pragma unroll
-      for (int l = 0; l < kAugMax; ++l) g[k][l] = (l <= k && k < w.m) ? aug_group_sum(pr, kAugG + k * (k + 1) / 2 + l) : 0.0;
+      for (int l = 0; l < kAugMax; ++l) fac[k * kAugMax + l] = f.L[k][l];
+      fac[kAugMax * kAugMax + k] = (double)f.kept[k];
     }
-    AugFactor f;
-    aug_factor(g, w.m, f);
-    aug_solve(f, w.m, d, y);
-    if (threadIdx.x == 0) {
+  }
+  double a[KM + 1];
 #pragma unroll
-      for (int k = 0; k < kAugMax; ++k) ys[k] = y[k];
-      if (t.ty == 0) {
+  for (int k = 0; k <= KM; ++k) a[k] = 0.0;
 #pragma unroll
-        for (int k = 0; k < kAugMax; ++k) {
+  for (int u = 0; u < kAugV; ++u) {
+    if (!on[u]) continue;
 #pragma unroll
-          for (int l = 0; l < kAugMax; ++l) ((gptr_wd)pr.aug_fac)[k * kAugMax + l] = f.L[k][l];
-          ((gptr_wd)pr.aug_fac)[kAugMax * kAugMax + k] = (double)f.kept[k];
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int k = 0; k < KM; ++k)
+        if (k < w.m) {
+          xx[u][i] = fmaf(yk[k], wp.v[k][u][i], xx[u][i]);
+          rr[u][i] = fmaf(-yk[k], wq.v[k][u][i], rr[u][i]);
         }
-      }
+      const double z = (double)rr[u][i] * (double)jj[u][i];
+      a[0] += (double)rr[u][i] * z;
+#pragma unroll
+      for (int k = 0; k < KM; ++k)
+        if (k < w.m) a[1 + k] += (double)wq.v[k][u][i] * z;
     }
+    x[ei[u]] = xx[u];
+    r[ei[u]] = rr[u];
   }
-  __syncthreads();
-  const int e0 = t.ty * kUpdChunk, e1 = min(e0 + kUpdChunk, pr.n_c);
-  const gptr_w x = (gptr_w)io.state;
-  const gptr_w r = (gptr_w)(io.state + 2L * pr.n_c);
-  const gptr_f jv = (gptr_f)pr.jinv;
-  float yk[kAugMax];
-#pragma unroll
-  for (int k = 0; k < kAugMax; ++k) yk[k] = (float)ys[k];
-  double a[kAugMax + 1] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int e = e0 + (int)threadIdx.x; e < e1; e += 256) {
-    float xe = x[e], re = r[e];
-    float qv[kAugMax];
-#pragma unroll
-    for (int k = 0; k < kAugMax; ++k) {
-      qv[k] = 0.f;
-      if (k < w.m) {
-        qv[k] = ((gptr_f)(w.Q + (long)k * pr.n_c))[e];
-        xe = fmaf(yk[k], ((gptr_f)(w.P + (long)k * pr.n_c))[e], xe);
-        re = fmaf(-yk[k], qv[k], re);
-      }
-    }
-    x[e] = xe;
-    r[e] = re;
-    const double z = (double)re * (double)jv[e];
-    a[0] += (double)re * z;
-#pragma unroll
-    for (int k = 0; k < kAugMax; ++k)
-      if (k < w.m) a[1 + k] += (double)qv[k] * z;
-  }
-  block_sumk_d<kAugMax + 1>(a, sh, 4);
+  block_sumk_d<KM + 1>(a, sh, 4);
   if (threadIdx.x == 0) {
-    ((gptr_wd)pr.aug_slots)[(long)kAugRho0 * pr.n_slots_upd + t.slot] = a[0];
+    ((gptr_wd)slots)[(long)kAugRho0 * ns + t.slot] = a[0];
 #pragma unroll
-    for (int k = 0; k < kAugMax; ++k)
-      if (k < w.m) ((gptr_wd)pr.aug_slots)[(long)(kAugT + k) * pr.n_slots_upd + t.slot] = a[1 + k];
+    for (int k = 0; k < KM; ++k)
+      if (k < w.m) ((gptr_wd)slots)[(long)(kAugT + k) * ns + t.slot] = a[1 + k];
   }
 }
 
 // Direction j of the augmented PCG: z_j = J^{-1} r_j, beta = rho_j / rho_{j-1}
 // (0 at j = 0), mu = G^{-1} (A W)^T z_j, p_j = z_j + beta p_{j-1} - W mu.
+template <int KM>
 __global__ __launch_bounds__(256) void k_aug_p(const ProbDev* P, const IoDev* IO, const Tile* tiles, int iter) {
-  __shared__ float cs[kAugMax + 1];
   const Tile t = my_tile(tiles);
   const ProbDev& pr = P[t.prob];
   const IoDev& io = IO[t.prob];
   const AugView w = aug_view(pr, io);
-  if (threadIdx.x < 64) {
-    AugFactor f;
+  const int ns = pr.n_slots_upd;
+  const gptr_f4u r = (gptr_f4u)(io.state + 2L * pr.n_c);
+  const gptr_f4u jv = (gptr_f4u)pr.jinv;
+  const gptr_f4u pold = (gptr_f4u)p_loc(pr, iter - 1);
+  const gptr_w4u pnew = (gptr_w4u)p_loc(pr, iter);
+  // (A W)^T z_j, then rho_j and rho_{j-1}
+  int n0 = 0, n1 = 0;
+  const double* sl[KM + 2];
+  int nn[KM + 2];
 #pragma unroll
-    for (int k = 0; k < kAugMax; ++k) {
-#pragma unroll
-      for (int l = 0; l < kAugMax; ++l) f.L[k][l] = ((gptr_d)pr.aug_fac)[k * kAugMax + l];
-      f.kept[k] = ((gptr_d)pr.aug_fac)[kAugMax * kAugMax + k] != 0.0;
-    }
-    double tv[kAugMax], mu[kAugMax];
-#pragma unroll
-    for (int k = 0; k < kAugMax; ++k) tv[k] = k < w.m ? aug_group_sum(pr, kAugT + (iter & 1) * kAugMax + k) : 0.0;
-    aug_solve(f, w.m, tv, mu);
-    double beta = 0.0;
-    if (iter > 0) {
-      double rk, rkm;
-      rho_sum2(pr, iter, rk, rkm);
-      beta = rkm != 0.0 ? rk / rkm : 0.0;
-    }
-    if (threadIdx.x == 0) {
-      cs[0] = (float)beta;
-#pragma unroll
-      for (int k = 0; k < kAugMax; ++k) cs[1 + k] = (float)mu[k];
-    }
+  for (int k = 0; k < KM; ++k) {
+    sl[k] = pr.aug_slots + (long)(kAugT + (iter & 1) * kAugMax + min(k, pr.aug_keep - 1)) * ns;
+    nn[k] = ns;
   }
-  __syncthreads();
-  const float beta = cs[0];
-  const int e0 = t.ty * kUpdChunk, e1 = min(e0 + kUpdChunk, pr.n_c);
-  const gptr_f r = (gptr_f)(io.state + 2L * pr.n_c);
-  const gptr_f jv = (gptr_f)pr.jinv;
-  const gptr_f pold = (gptr_f)p_loc(pr, iter - 1);
-  const gptr_w pnew = (gptr_w)p_loc(pr, iter);
-  for (int e = e0 + (int)threadIdx.x; e < e1; e += 256) {
-    const float z = r[e] * jv[e];
-    float pe = iter > 0 ? fmaf(beta, pold[e], z) : z;
+  sl[KM] = rho_slots(pr, iter, n0);
+  sl[KM + 1] = iter > 0 ? rho_slots(pr, iter - 1, n1) : sl[KM];
+  nn[KM] = iter > 0 ? n0 : 0;
+  nn[KM + 1] = iter > 0 ? n1 : 0;
+  SlotLoads<KM + 2, 1> S;
+  slots_issue<KM + 2, 1>(sl, nn, S);
+  AugFactor f;
 #pragma unroll
-    for (int k = 0; k < kAugMax; ++k)
-      if (k < w.m) pe = fmaf(-cs[1 + k], ((gptr_f)(w.P + (long)k * pr.n_c))[e], pe);
-    pnew[e] = pe;
+  for (int k = 0; k < kAugMax; ++k) {
+#pragma unroll
+    for (int l = 0; l < kAugMax; ++l) f.L[k][l] = k < KM && l <= k ? ((gptr_d)pr.aug_fac)[k * kAugMax + l] : 0.0;
+    f.kept[k] = k < KM && ((gptr_d)pr.aug_fac)[kAugMax * kAugMax + k] != 0.0;
+  }
+  int ei[kAugV];
+  bool on[kAugV];
+  aug_pieces(t.ty, pr.n_c, ei, on);
+  AugVec<KM> wp;
+  v4f rr[kAugV], jj[kAugV], pp[kAugV];
+#pragma unroll
+  for (int u = 0; u < kAugV; ++u) {
+    rr[u] = r[ei[u]];
+    jj[u] = jv[ei[u]];
+    pp[u] = v4f{0.f, 0.f, 0.f, 0.f};
+    if (iter > 0) pp[u] = pold[ei[u]];
+  }
+  wp.load(w.P, pr.n_c, pr.aug_keep, ei);
+  double o[KM + 2];
+  slots_reduce<KM + 2, 1>(sl, nn, S, o);
+  double tv[kAugMax], mu[kAugMax];
+#pragma unroll
+  for (int k = 0; k < kAugMax; ++k) tv[k] = k < KM && k < w.m ? o[k < KM ? k : 0] : 0.0;
+  aug_solve(f, w.m, tv, mu);
+  const float beta = (float)(o[KM + 1] != 0.0 ? o[KM] / o[KM + 1] : 0.0);
+  float mk[KM];
+#pragma unroll
+  for (int k = 0; k < KM; ++k) mk[k] = (float)mu[k];
+#pragma unroll
+  for (int u = 0; u < kAugV; ++u) {
+    v4f pe;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float z = rr[u][i] * jj[u][i];
+      pe[i] = iter > 0 ? fmaf(beta, pp[u][i], z) : z;
+#pragma unroll
+      for (int k = 0; k < KM; ++k)
+        if (k < w.m) pe[i] = fmaf(-mk[k], wp.v[k][u][i], pe[i]);
+    }
+    if (on[u]) pnew[ei[u]] = pe;
   }
 }
 
 // The frame's first min(iters, aug_keep) directions and images become the
 // state's W and A W for the next frame (count after them).
+template <int KM>
 __global__ __launch_bounds__(256) void k_aug_store(const ProbDev* P, const IoDev* IO, const Tile* tiles, int iters) {
   const Tile t = my_tile(tiles);
   const ProbDev& pr = P[t.prob];
   const IoDev& io = IO[t.prob];
-  const int kd = min(iters, pr.aug_keep);
-  float* base = io.state + 3L * pr.n_c + 2L * pr.n_act;
-  const int e0 = t.ty * kUpdChunk, e1 = min(e0 + kUpdChunk, pr.n_c);
-  for (int k = 0; k < kd; ++k) {
-    const gptr_f ps = (gptr_f)(pr.aug_pdir + (long)k * pr.n_c), qs = (gptr_f)(pr.aug_qdir + (long)k * pr.n_c);
-    const gptr_w pd = (gptr_w)(base + (long)k * pr.n_c), qd = (gptr_w)(base + (long)(pr.aug_keep + k) * pr.n_c);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += 256) {
-      pd[e] = ps[e];
-      qd[e] = qs[e];
-    }
-  }
-  if (t.ty == 0 && threadIdx.x == 0) ((gptr_w)(base + 2L * pr.aug_keep * pr.n_c))[0] = (float)kd;
+  const int keep = pr.aug_keep, kd = min(iters, keep);
+  const long n = pr.n_c;
+  float* const base = io.state + 3L * n + 2L * pr.n_act;
+  int ei[kAugV];
+  bool on[kAugV];
+  aug_pieces(t.ty, pr.n_c, ei, on);
+  AugVec<KM> ps, qs;
+  ps.load(pr.aug_pdir, n, keep, ei);
+  qs.load(pr.aug_qdir, n, keep, ei);
+#pragma unroll
+  for (int k = 0; k < KM; ++k)
+#pragma unroll
+    for (int u = 0; u < kAugV; ++u)
+      if (k < kd && on[u]) {
+        *(gptr_w4u)((gptr_w)(base + k * n) + 4 * ei[u]) = ps.v[k][u];
+        *(gptr_w4u)((gptr_w)(base + (keep + k) * n) + 4 * ei[u]) = qs.v[k][u];
+      }
+  if (t.ty == 0 && threadIdx.x == 0) ((gptr_w)(base + 2L * keep * n))[0] = (float)kd;
 }
 
 // ------------------------------------------------------------ PCG update
@@ -3409,7 +3504,9 @@ __global__ __launch_bounds__(256) void k_aug_store(const ProbDev* P, const IoDev
 // rounded products and sums in the same order (bitwise the same x), with
 // a_{k-1} summed again from the same slots; 8 of every 56 bytes per
 // coefficient less over the pair.
-template <int XM, bool COARSE>
+// KM: most directions kept by a problem of an augmented plan (2 or kAugMax;
+// 0: plain), whose images are requested with the other vectors.
+template <int XM, bool COARSE, int KM>
 __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* IO, const Tile* tiles, int iter,
                                                 const CoarseDev* C) {
   __shared__ double sh[4];
@@ -3468,6 +3565,19 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
     qq[u] = q[e];
     jj[u] = jv[e];
   }
+  AugView w{nullptr, nullptr, 0};
+  AugVec<(KM > 0 ? KM : 1)> wq;
+  const int keep = KM > 0 ? pr.aug_keep : 0;
+  if (KM > 0 && keep > 0) {
+    w = aug_view(pr, io);
+    int ei[kAugV];
+#pragma unroll
+    for (int u = 0; u < kAugV; ++u) ei[u] = min(e0 + (int)threadIdx.x + u * 256, e1 - 1);
+    wq.load(w.Q, pr.n_c, keep, ei);
+  }
+  double* const dots = pr.dots;
+  double* const aslots = pr.aug_slots;
+  const int n_dots = pr.n_dots, nsu = pr.n_slots_upd;
   // alpha = rho_k / pi_k
   double o[G];
   slots_reduce<G, 2>(sl, nn, sloads, o);
@@ -3512,36 +3622,35 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
       acc += (double)rn.w * (double)rn.w * (double)jj[u].w;
     }
   }
-  if (pr.aug_keep == 0) {
+  if (keep == 0) {
     const double s = block_sum(acc, sh, 256);
-    if (threadIdx.x == 0) ((gptr_wd)pr.dots)[(long)rho_grp(iter + 1) * pr.n_dots + t.slot] = s;
+    if (threadIdx.x == 0) ((gptr_wd)dots)[(long)rho_grp(iter + 1) * n_dots + t.slot] = s;
     return;
   }
-  // augmented PCG: also (A W)^T z_{j+1}, z = J^{-1} r, for the next direction
-  const AugView w = aug_view(pr, io);
-  double tk[kAugMax + 1] = {acc, 0.0, 0.0, 0.0, 0.0};
+  if constexpr (KM > 0) {
+    // augmented PCG: also (A W)^T z_{j+1}, z = J^{-1} r, for the next direction
+    double tk[KM + 1];
+    tk[0] = acc;
 #pragma unroll
-  for (int k = 0; k < kAugMax; ++k) {
-    if (k >= w.m) break;
-    const gptr_f4 qk = (gptr_f4)(w.Q + (long)k * pr.n_c);
+    for (int k = 0; k < KM; ++k) {
+      tk[1 + k] = 0.0;
+      if (k >= w.m) continue;
 #pragma unroll
-    for (int u = 0; u < V; ++u) {
-      const int e = e0 + threadIdx.x + u * 256;
-      if (e < e1) {
-        const v4f a4 = qk[e], r4 = rnv[u];
-        tk[1 + k] += (double)a4.x * ((double)r4.x * (double)jj[u].x) + (double)a4.y * ((double)r4.y * (double)jj[u].y) +
-                     (double)a4.z * ((double)r4.z * (double)jj[u].z) + (double)a4.w * ((double)r4.w * (double)jj[u].w);
-      }
+      for (int u = 0; u < V; ++u)
+        if (e0 + (int)threadIdx.x + u * 256 < e1) {
+          const v4f a4 = wq.v[k][u], r4 = rnv[u];
+          tk[1 + k] += (double)a4.x * ((double)r4.x * (double)jj[u].x) + (double)a4.y * ((double)r4.y * (double)jj[u].y) +
+                       (double)a4.z * ((double)r4.z * (double)jj[u].z) + (double)a4.w * ((double)r4.w * (double)jj[u].w);
+        }
     }
-  }
-  __shared__ double shk[(kAugMax + 1) * 4];
-  block_sumk_d<kAugMax + 1>(tk, shk, 4);
-  if (threadIdx.x == 0) {
-    ((gptr_wd)pr.dots)[(long)rho_grp(iter + 1) * pr.n_dots + t.slot] = tk[0];
+    __shared__ double shk[(KM + 1) * 4];
+    block_sumk_d<KM + 1>(tk, shk, 4);
+    if (threadIdx.x == 0) {
+      ((gptr_wd)dots)[(long)rho_grp(iter + 1) * n_dots + t.slot] = tk[0];
 #pragma unroll
-    for (int k = 0; k < kAugMax; ++k)
-      if (k < w.m)
-        ((gptr_wd)pr.aug_slots)[(long)(kAugT + ((iter + 1) & 1) * kAugMax + k) * pr.n_slots_upd + t.slot] = tk[1 + k];
+      for (int k = 0; k < KM; ++k)
+        if (k < w.m) ((gptr_wd)aslots)[(long)(kAugT + ((iter + 1) & 1) * kAugMax + k) * nsu + t.slot] = tk[1 + k];
+    }
   }
 }
 
@@ -4101,16 +4210,25 @@ void launch_pT(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode) {
   }
 #undef FEWHA_PT
 }
+template <int KM>
+static void launch_update_n(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter, const CoarseDev* C, int xm) {
+  if (xm == UPD_X_DEFER)
+    k_update<UPD_X_DEFER, false, KM><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+  else if (xm == UPD_X_PAIR)
+    k_update<UPD_X_PAIR, false, KM><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+  else if (C)  // converged solves: never with augmentation
+    k_update<UPD_X_ONE, true, 0><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+  else
+    k_update<UPD_X_ONE, false, KM><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+}
 void launch_update(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter, const CoarseDev* C, int xm) {
   if (ntiles <= 0) return;
-  if (xm == UPD_X_DEFER)
-    k_update<UPD_X_DEFER, false><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
-  else if (xm == UPD_X_PAIR)
-    k_update<UPD_X_PAIR, false><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
-  else if (C)
-    k_update<UPD_X_ONE, true><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+  if (a.aug_max == 0)
+    launch_update_n<0>(a, tiles, ntiles, iter, C, xm);
+  else if (a.aug_max <= 2)
+    launch_update_n<2>(a, tiles, ntiles, iter, C, xm);
   else
-    k_update<UPD_X_ONE, false><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    launch_update_n<kAugMax>(a, tiles, ntiles, iter, C, xm);
 }
 void launch_coarse(const LaunchArgs& a, const CoarseTile* tiles, int ntiles, const CoarseDev* members, int k) {
   if (ntiles > 0) k_coarse<<<ntiles, kCoarseThreads, 0, a.stream>>>(tiles, members, k);
@@ -4141,16 +4259,28 @@ void launch_grad_final(const LaunchArgs& a, const GradIo* g, int nprob) {
   if (nprob > 0) k_grad_final<<<nprob, 64, 0, a.stream>>>(a.P, a.L, g);
 }
 void launch_aug_gram(const LaunchArgs& a, const Tile* tiles, int ntiles) {
-  if (ntiles > 0) k_aug_gram<<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles);
+  if (ntiles > 0 && a.aug_max <= 2)
+    k_aug_gram<2><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles);
+  else if (ntiles > 0)
+    k_aug_gram<kAugMax><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles);
 }
 void launch_aug_init(const LaunchArgs& a, const Tile* tiles, int ntiles) {
-  if (ntiles > 0) k_aug_init<<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles);
+  if (ntiles > 0 && a.aug_max <= 2)
+    k_aug_init<2><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles);
+  else if (ntiles > 0)
+    k_aug_init<kAugMax><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles);
 }
 void launch_aug_p(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter) {
-  if (ntiles > 0) k_aug_p<<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter);
+  if (ntiles > 0 && a.aug_max <= 2)
+    k_aug_p<2><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter);
+  else if (ntiles > 0)
+    k_aug_p<kAugMax><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter);
 }
 void launch_aug_store(const LaunchArgs& a, const Tile* tiles, int ntiles, int iters) {
-  if (ntiles > 0) k_aug_store<<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iters);
+  if (ntiles > 0 && a.aug_max <= 2)
+    k_aug_store<2><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iters);
+  else if (ntiles > 0)
+    k_aug_store<kAugMax><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iters);
 }
 void launch_fit_fwd(const LaunchArgs& a, const Tile* tiles, int ntiles) {
   if (ntiles > 0) k_fit_fwd<<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.W, tiles);

@@ -2995,14 +2995,14 @@ __device__ __forceinline__ void pt_sensor_wide(const float* vsens, int nc, const
 // WIDE: the instantiation with the wide-pair path (more registers), launched
 // only for plans that have wide pairs.  SPLIT (RPT = kBandRows): a tile is one
 // band record's kBandRows node rows x 64 columns, and its sensor list is
-// split over the 4 waves (sensor i to wave i mod 4): a quarter of the serial
-// sensor chain per wave, for launches with few tiles.  Every sensor's sums
-// go to LDS by themselves (kSplitRounds sensors per wave between barriers)
-// and are added in sensor order, so a split tile's values are bitwise those
-// of an unsplit one and the plan may take either (kPtSplitTiles in api.cpp).
-constexpr int kSplitRounds = 4;
-template <int RPT, bool WIDE, bool SPLIT>
-__global__ __launch_bounds__(256) void k_pT(const ProbDev* P, const LayerDev* LD, const WfsDev* WD, const IoDev* IO,
+// split over SPLIT waves (sensor i to wave i mod SPLIT): that much less of the
+// serial sensor chain per wave, for launches with few tiles.  Every sensor's
+// sums go to LDS by themselves (kSplitSens sensors between barriers) and are
+// added in sensor order, so a split tile's values are bitwise those of an
+// unsplit one and the plan may take either (kPtSplitTiles in api.cpp).
+constexpr int kSplitSens = 16;
+template <int RPT, bool WIDE, int SPLIT>
+__global__ __launch_bounds__(SPLIT ? 64 * SPLIT : 256) void k_pT(const ProbDev* P, const LayerDev* LD, const WfsDev* WD, const IoDev* IO,
                                             const Tile* tiles, const HatEnt* __restrict__ hats, int n_hats,
                                             const BandRec* __restrict__ bands, const PtEnt* __restrict__ ents,
                                             int mode) {
@@ -3079,13 +3079,13 @@ __global__ __launch_bounds__(256) void k_pT(const ProbDev* P, const LayerDev* LD
   };
   HatEnt hx, hxn;
   BandHdr hd, hdn;
-  constexpr int step = SPLIT ? 4 : 1;
+  constexpr int step = SPLIT ? SPLIT : 1;
   const int i0 = SPLIT ? wv : 0;
-  __shared__ float red[SPLIT ? kSplitRounds * 4 : 1][SPLIT ? kBandRows : 1][SPLIT ? 64 : 1];
+  __shared__ float red[SPLIT ? kSplitSens : 1][SPLIT ? kBandRows : 1][SPLIT ? 64 : 1];
   float sum = 0.f;  // SPLIT: node row p0 + wv
   fetch(ent(min(i0, ne)), hx, hd);
-  for (int r0 = 0; r0 < ne; r0 += SPLIT ? 4 * kSplitRounds : ne) {
-    const int rn = SPLIT ? min(ne - r0, 4 * kSplitRounds) : ne;
+  for (int r0 = 0; r0 < ne; r0 += SPLIT ? kSplitSens : ne) {
+    const int rn = SPLIT ? min(ne - r0, kSplitSens) : ne;
     for (int i = r0 + i0; i < r0 + rn; i += step) {
       fetch(ent(min(i + step, ne)), hxn, hdn);  // issued first: the waits for this sensor's loads cover it
       sensor(ent(i), hx, hd);
@@ -3101,7 +3101,8 @@ __global__ __launch_bounds__(256) void k_pT(const ProbDev* P, const LayerDev* LD
     }
     if constexpr (SPLIT) {
       __syncthreads();
-      for (int i = 0; i < rn; ++i) sum += red[i][wv][lane];
+      if (wv < kBandRows)
+        for (int i = 0; i < rn; ++i) sum += red[i][wv][lane];
       if (r0 + rn < ne) __syncthreads();
     }
   }
@@ -3109,7 +3110,7 @@ __global__ __launch_bounds__(256) void k_pT(const ProbDev* P, const LayerDev* LD
   const gptr_w dst = (gptr_w)((mode == PT_USER) ? io.out : pr.phiadj);
   if constexpr (SPLIT) {
     const int p = p0 + wv;  // wave w stores node row p0 + w
-    if (q < n && p < n) dst[loff + p * n + q] = sum;
+    if (wv < kBandRows && q < n && p < n) dst[loff + p * n + q] = sum;
   } else if (q < n) {
 #pragma unroll
     for (int u = 0; u < RPT; ++u) {
@@ -4232,22 +4233,25 @@ void launch_gammaT(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode)
 void launch_pT(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode) {
   if (ntiles <= 0) return;
 #define FEWHA_PT(RPT, WIDE, SPLIT)                                                                      \
-  k_pT<RPT, WIDE, SPLIT><<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.W, a.IO, tiles, a.hats, a.n_hats, a.bands, \
+  k_pT<RPT, WIDE, SPLIT><<<ntiles, SPLIT ? 64 * SPLIT : 256, 0, a.stream>>>(a.P, a.L, a.W, a.IO, tiles, a.hats, a.n_hats, a.bands, \
                                                        a.pents, mode)
+  // split tiles: 8 waves each while all workgroups are resident together (384
+  // tiles of a 39 m problem 3.8 -> 3.1 us, 768 4.1 -> 3.6, 1536 4.2 -> 5.0)
+  const bool wide_wg = ntiles <= 4 * kCus;
   if (a.pt_split) {
     if (a.pt_wide)
-      FEWHA_PT(4, true, true);
+      wide_wg ? FEWHA_PT(4, true, 8) : FEWHA_PT(4, true, 4);
     else
-      FEWHA_PT(4, false, true);
+      wide_wg ? FEWHA_PT(4, false, 8) : FEWHA_PT(4, false, 4);
   } else if (a.pt_wide) {
     if (a.pt_rows == 8)
-      FEWHA_PT(8, true, false);
+      FEWHA_PT(8, true, 0);
     else
-      FEWHA_PT(4, true, false);
+      FEWHA_PT(4, true, 0);
   } else if (a.pt_rows == 8) {
-    FEWHA_PT(8, false, false);
+    FEWHA_PT(8, false, 0);
   } else {
-    FEWHA_PT(4, false, false);
+    FEWHA_PT(4, false, 0);
   }
 #undef FEWHA_PT
 }

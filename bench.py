@@ -157,6 +157,24 @@ def algorithmic_bytes(cfg, n_slopes, n_corners, res=128):
     }
 
 
+def tiled_bytes(b, cfg, workgroups):
+    """algorithmic_bytes for a plan on the tiled transforms, by the stages'
+    workgroups: the inverse transform is one launch (IDWT_GLOB has none); the
+    forward transform's first three levels are FDWT_GLOB and the block of side
+    n / 8 left by layers with more is FDWT_RES."""
+    n_c = sum(l["n"] ** 2 for l in cfg["layers"])
+    out = dict(b)
+    if workgroups["IDWT_GLOB"] == 0:
+        out["IDWT_RES"] = 4 * 5 * n_c
+        out["IDWT_GLOB"] = 0
+    if workgroups["IDWT_GLOB"] == 0 and workgroups["FDWT_GLOB"] > 0:
+        rest = sum((l["n"] // 8) ** 2 for l in cfg["layers"] if l["levels"] > 3)
+        # input read, p read and q written where it ends, the rest written once
+        out["FDWT_GLOB"] = 4 * (3 * n_c - rest)
+        out["FDWT_RES"] = 4 * 3 * rest
+    return out
+
+
 def path_bytes(n_c, n_corners, n_slopes, iters):
     """Algorithmic bytes of one whole frame (FP32, each operator of the
     paper's factorisation reads its input once and writes its output once):
@@ -184,8 +202,10 @@ def path_rate(bytes_per_frame, frames_per_s, peaks):
     return out
 
 
-def launches_per_frame(cfg, res, iters, fuse=False):
-    """Kernel launches of one open-loop frame of one problem (plain PCG):
+def launches_per_frame(cfg, res, iters, fuse=False, workgroups=None):
+    """Kernel launches of one open-loop frame of one problem (plain PCG), from
+    the workgroups of each stage of its plan, or of a plan on the
+    level-by-level transforms:
     slope input, sensor adjoint, propagation adjoint and forward transform
     for the right-hand side; per iteration the inverse transform, the
     propagation and sensor stages, the forward transform and the update;
@@ -195,6 +215,10 @@ def launches_per_frame(cfg, res, iters, fuse=False):
     def glob(l):
         ng = sum(1 for k in range(1, 16) if res < 2 ** k <= l["n"])
         return ng - 1 if fuse and ng >= 2 else ng
+    if workgroups is not None:
+        idwt = sum(workgroups[k] > 0 for k in ("IDWT_RES", "IDWT_GLOB"))
+        fdwt = sum(workgroups[k] > 0 for k in ("FDWT_RES", "FDWT_GLOB"))
+        return 3 + fdwt + iters * (idwt + fdwt + 4) + idwt
     g = max(glob(l) for l in cfg["layers"])
     return 3 + (1 + g) + iters * (2 * (1 + g) + 4) + (1 + g)
 
@@ -281,7 +305,8 @@ def stage_roofline(fw, batch, ctxs, tuning, iters, peaks, reps=50):
                 "P_T": iters + 1, "FDWT_GLOB": iters + 1, "FDWT_RES": iters + 1, "UPDATE": iters}
     share = {k: stage_us[k][0] * launches[k] for k in STAGES if stage_us[k][1] > 0}
     dom = max(share, key=share.get)
-    per = [problem_bytes(fw, c, tuning["dwt_resident"]) for c in ctxs]
+    wgs = {k: v[1] for k, v in stage_us.items()}
+    per = [tiled_bytes(problem_bytes(fw, c, tuning["dwt_resident"]), c.cfg, wgs) for c in ctxs]
     dom_bytes = sum(b[dom] for b in per)
     us = stage_us[dom][0]
     achieved = dom_bytes / (us * 1e-6) / 1e9
@@ -696,6 +721,7 @@ def main():
 
     lat_graph = latency(lambda i: single.reconstruct([pool[0][pool_index(i, args.pool)]], [st1], [lay1],
                                                      iters=args.iters, use_graph=True), nf)
+    wgs_1 = {k: single.time_stage(i, reps=1)[1] for i, k in enumerate(STAGES)}
     lat_plain = latency(lambda i: c0.reconstruct(pool[0][pool_index(i, args.pool)], st1, lay1, iters=args.iters), nf)
 
     # plain path over the whole batch: B sequential unbatched, ungraphed frames
@@ -764,7 +790,7 @@ def main():
             "batched": path_rate(frame_b, value, peaks),
             "single_frame_graph_p50": path_rate(frame_b, 1e6 / lat_graph["p50_us"], peaks),
             "launches_per_frame_single": launches_per_frame(cfg, tune_1["dwt_resident"], args.iters,
-                                                            bool(tune_1.get("glob_fuse", 0)))},
+                                                            bool(tune_1.get("glob_fuse", 0)), wgs_1)},
         "latency_graph_us": lat_graph,
         "latency_plain_us": lat_plain,
         "batched_nograph_frames_per_s": B / dt_nograph,

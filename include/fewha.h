@@ -406,7 +406,13 @@ FEWHA_API void fewha_batch_destroy(fewha_batch* b);
 
 /* ---- tuning: launch shapes chosen per plan (by an autotuner or by hand) ---- */
 
-/* dwt_resident: side of the largest transform block kept in one workgroup's
+/* Plans whose layers all have sides of 32 or more and 3 to 5 levels (6 with
+ * sides of 64 or more) run the inverse transform as one launch of output
+ * tiles, and the forward transform's first three levels as one launch of
+ * input tiles (except plans of layers up to 64 x 64 with more than 3
+ * levels): dwt_resident, res_split and glob_fuse are checked as below but
+ * choose nothing there.
+ * dwt_resident: side of the largest transform block kept in one workgroup's
  * LDS by the resident DWT kernels (32, 64 or 128; 0 = default 128).  Levels
  * above it run as tiled passes over global memory, one launch per level.
  * Smaller values trade LDS work per workgroup for more workgroups and more
@@ -430,11 +436,11 @@ FEWHA_API void fewha_batch_destroy(fewha_batch* b);
  * layer's resident side to be at least 16 with at least one resident level
  * (else FEWHA_EINVAL when the plan is built).
  * pt_split: 1 = the propagation adjoint's tiles are 4 node rows x 64
- * columns and each tile's sensor list is split over its 4 waves (sensor i
- * to wave i mod 4, every sensor's sums added in sensor order, so the values
- * are bitwise those of unsplit tiles), a quarter of the serial chain of
- * sensors per wave; for launches with few tiles, such as one problem's
- * frame.  Needs pt_rows 0 or 4.  0 = default: split where the launch has few
+ * columns and each tile's sensor list is split over its 4 or 8 waves
+ * (sensor i to wave i mod 4 or 8, every sensor's sums added in sensor order,
+ * so the values are bitwise those of unsplit tiles), that much less of the
+ * serial chain of sensors per wave; for launches with few tiles, such as one
+ * problem's frame.  Needs pt_rows 0 or 4.  0 = default: split where the launch has few
  * tiles.
  * glob_fuse: 1 = a layer with two or more global levels (side above twice
  * dwt_resident) runs its last two inverse levels in one launch: each output

@@ -393,9 +393,9 @@ struct PtLists {
 
 // Side of the output tiles of the one-launch inverse transform: 64 once that
 // gives the chip more than one workgroup per CU, else 32 (four times the
-// workgroups; measured on 39 m problems, 24 tiles of 64 each: 7.0 against 10.4
-// us for one, 10.3 against 11.2 for 8, 15.9 against 15.4 for 16, 25.5 against
-// 20.1 for 32; the level-by-level kernels take 17.0, 18.7, 21.4 and 27.4), or 0
+// workgroups; measured on 39 m problems, 24 tiles of 64 each: 6.0 against 10.4
+// us for one, 10.3 against 11.2 for 8, 15.9 against 15.0 for 16, 25.5 against
+// 19.8 for 32; the level-by-level kernels take 17.0, 18.7, 21.4 and 27.4), or 0
 // where a layer is smaller than a tile or has more levels than a tile can halve (or
 // fewer than kDirMinLevels): the level-by-level kernels then.
 constexpr long kDirTiles64 = 320;
@@ -415,8 +415,9 @@ int dir_tile(const std::vector<const HostModel*>& models) {
 
 // The same for the forward transform's three levels per launch, whose larger
 // tile pays earlier (39 m problems, 24 tiles of 64 each: 5.3 against 5.8 us for
-// one, 6.4 against 5.9 for 4, 7.8 against 6.1 for 8, 20.3 against 11.6 for 32,
-// the rest of the levels 4.2 to 4.4 us more; the level-by-level kernels take
+// one, 6.4 against 5.9 for 4, 7.8 against 6.1 for 8, 20.3 against 11.6 for 32
+// when every task took four pairs, now 4.5 for one at 32 and 5.4, 5.7 and 10.7
+// at 64; the rest of the levels 3.8 to 4.2 us more; the level-by-level kernels take
 // 15.0 in all for one, 15.9 for 8, 19.8 for 32).  A layer needs three levels
 // and leaves at most kResMax x kResMax to one workgroup.  Layers of at most 64
 // x 64 with deeper levels are one launch of one workgroup per layer the other
@@ -444,9 +445,9 @@ int fdir_tile(const std::vector<const HostModel*>& models) {
 // waves) up to this many of them, where the chip has fewer than 16
 // workgroups of them per CU and a launch lasts as long as its longest sensor
 // chain; measured on 39 m problems, 384 split tiles each, against unsplit
-// tiles: 3.8 against 7.3 us for one, 5.6 against 8.0 for 8, 9.2 against 9.0
+// tiles: 3.1 against 7.3 us for one, 5.6 against 8.0 for 8, 9.2 against 9.0
 // for 16, 16.3 against 12.1 for 32; one 37 m problem (six corners per node
-// and axis) 5.0 against 11.2.  The values are bitwise the same.
+// and axis) 3.9 against 11.2.  The values are bitwise the same.
 constexpr long kPtSplitTiles = 4096;
 
 // Byte-offset carving of the arena (256-byte aligned pieces).

@@ -1097,7 +1097,9 @@ __global__ __launch_bounds__(256) void k_idwt_glob2(const ProbDev* P, const Laye
 // Bound: a chain of memory round trips (tile, records, coefficients) and two
 // barriers per level for few tiles, the windows' loads for many.  T = 32
 // loads 1.69 coefficients per output, T = 64 1.30, with a quarter of the
-// workgroups (see dir_tile in api.cpp for the choice).
+// workgroups (see dir_tile in api.cpp for the choice).  A 39 m problem takes
+// 6.0 us and 32 of them 19.8 (58 MB, 2.9 TB/s), where the level-by-level
+// kernels took 17.0 and 27.4.
 template <int T>
 struct DirWin {
   static constexpr int kLevels = T == 64 ? 6 : 5;
@@ -1719,7 +1721,9 @@ __global__ __launch_bounds__(256) void k_fdwt_glob2(const ProbDev* P, const Laye
 //
 // Bound: memory round trips and five barriers for few tiles; for many the
 // window (3.5 samples per input at T = 32, 2.1 at 64) against a quarter of
-// the workgroups.
+// the workgroups.  A 39 m problem takes 4.5 us and 32 of them 10.8 (38 MB, 3.5
+// TB/s), and k_fdwt_res 3.8 and 4.2, where the level-by-level kernels took
+// 15.0 and 19.8 in all.
 template <int T>
 struct FwdWin {
   static constexpr int D(int j) { return T >> j; }                     // detail outputs per direction
@@ -2177,6 +2181,8 @@ __device__ __forceinline__ void epi_levels(const ResLayer& ly, const EpiDst& dst
 // (p) for every level is requested with the input; the others (up to three
 // operands per output) request the top level's with the input and all lower
 // levels' once the top level is done, so that the registers hold one set.
+// Bound: one workgroup's chain; two levels of a 32 x 32 block 4.2 -> 3.8 us
+// with the layer's record read before the first store.
 template <int RMAX, int EPI>
 __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
                                                    const Tile* tiles, Filter F, int iter) {
@@ -3504,7 +3510,9 @@ __global__ __launch_bounds__(256) void k_aug_store(const ProbDev* P, const IoDev
 // UPD_X_PAIR forms x += a_{k-1} p_{k-1}, then += a_k p_k: the same two
 // rounded products and sums in the same order (bitwise the same x), with
 // a_{k-1} summed again from the same slots; 8 of every 56 bytes per
-// coefficient less over the pair.
+// coefficient less over the pair.  Bound: the slot sums' chain for few
+// chunks (39 m: 3.4 -> 3.1 us with only the sums that a step needs), the
+// vectors for many (32 problems: 9.6 and 16.4 us, 3.9 and 5.4 TB/s).
 // KM: most directions kept by a problem of an augmented plan (2 or kAugMax;
 // 0: plain), whose images are requested with the other vectors.
 template <int XM, bool COARSE, int KM>

@@ -195,17 +195,6 @@ __device__ __forceinline__ const double* rho_slots(const ProbDev& pr, int k, int
   n = rho_count(pr, k);
   return dot_group(pr, rho_grp(k));
 }
-// rho_k and rho_{k-1} with their loads in flight together
-__device__ __forceinline__ void rho_sum2(const ProbDev& pr, int k, double& rk, double& rkm) {
-  int n0, n1;
-  const double* const s[2] = {rho_slots(pr, k, n0), rho_slots(pr, k - 1, n1)};
-  const int n[2] = {n0, n1};
-  double o[2];
-  wave_sum_slots_n<2>(s, n, o);
-  rk = o[0];
-  rkm = o[1];
-}
-
 // rho_k with the coarse-level correction of the converged solves:
 // r^T z = r^T J^{-1} r + (Z^T r)^T E^{-1} Z^T r (the second part's slots,
 // written by k_coarse).
@@ -476,44 +465,6 @@ __device__ __forceinline__ void syn_pass(const float* src, float* dst, int m, co
         syn_line<2, S>(src + l, half, k, F, o);
       else
         syn_line<1, S>(src + l, half, k, F, o);
-    }
-  }
-}
-
-// The last synthesis pass (rows) written straight to global memory:
-// g[l gs + t] = scale x_t for line l, each thread its run of 2 np outputs
-// (float4 stores when `vec`: g, gs and the runs 16-byte aligned).
-template <int S>
-__device__ __forceinline__ void syn_pass_out(const float* src, int m, const Filter& F, float* g, int gs,
-                                             float scale, bool vec) {
-  const int half = m >> 1, nt = blockDim.x;
-  const int np = max(1, m * half / nt), nch = half / np, lm = __builtin_ctz(m);
-  typedef v4f __attribute__((address_space(1)))* gw4;
-  typedef float __attribute__((address_space(1)))* gw1;
-  for (int task = threadIdx.x; task < m * nch; task += nt) {
-    const int l = task & (m - 1), K0 = (task >> lm) * np;
-    for (int p0 = 0; p0 < np; p0 += 8) {
-      const int k = K0 + p0, c = min(np - p0, 8);
-      float o[16];
-      if (c == 8)
-        syn_line<8, S>(src + l, half, k, F, o);
-      else if (c == 4)
-        syn_line<4, S>(src + l, half, k, F, o);
-      else if (c == 2)
-        syn_line<2, S>(src + l, half, k, F, o);
-      else
-        syn_line<1, S>(src + l, half, k, F, o);
-      float* dst = g + (long)l * gs + 2 * k;
-      if (vec && c >= 2) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (4 * i < 2 * c)
-            ((gw4)dst)[i] = v4f{o[4 * i] * scale, o[4 * i + 1] * scale, o[4 * i + 2] * scale, o[4 * i + 3] * scale};
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (i < 2 * c) ((gw1)dst)[i] = o[i] * scale;
-      }
     }
   }
 }

@@ -2133,9 +2133,11 @@ __device__ __forceinline__ void epi_levels(const ResLayer& ly, const EpiDst& dst
 // operands per output) request the top level's with the input and all lower
 // levels' once the top level is done, so that the registers hold one set.
 // Bound: one workgroup's chain; two levels of a 32 x 32 block 4.2 -> 3.8 us
-// with the layer's record read before the first store.
+// with the layer's record read before the first store, 3.7 with the 512
+// threads that such a block has tasks for.
+constexpr int fres_threads(int rmax) { return rmax <= 32 ? 512 : 1024; }
 template <int RMAX, int EPI>
-__global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
+__global__ __launch_bounds__(fres_threads(RMAX)) void k_fdwt_res(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
                                                    const Tile* tiles, Filter F, int iter) {
   static_assert(RMAX * RMAX / 2 <= 8 * 1024, "at most 8 output pairs per thread and line at 1024 threads");
   __shared__ float A[RMAX * (RMAX + 1)];
@@ -2147,7 +2149,7 @@ __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const Layer
   const IoDev& io = IO[t.prob];
   const int n = ld.n, R = ld.fres, lr = __builtin_ctz(R), off = ld.off;
   constexpr int S = RMAX + 1;
-  constexpr int nt = 1024;
+  constexpr int nt = fres_threads(RMAX);
   const int ng = ld.fsteps;
   ResLayer ly;
   ly.n = n;
@@ -2164,7 +2166,7 @@ __global__ __launch_bounds__(1024) void k_fdwt_res(const ProbDev* P, const Layer
   // the whole block's loads in flight together, kUL per thread, without branches (indices
   // past the block clamped): with a load under a condition the compiler
   // waited for each before the next
-  constexpr int kUL = RMAX * RMAX / 1024 > 0 ? RMAX * RMAX / 1024 : 1;
+  constexpr int kUL = RMAX * RMAX / nt;
   float v[kUL];
 #pragma unroll
   for (int u = 0; u < kUL; ++u) {
@@ -4124,11 +4126,11 @@ void launch_fdwt_glob(const LaunchArgs& a, const Tile* tiles, int ntiles, int ep
 template <int RMAX>
 static void launch_fdwt_res_r(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter) {
   switch (epi) {
-    case EPI_APPLYM: k_fdwt_res<RMAX, EPI_APPLYM><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    case EPI_PCG: k_fdwt_res<RMAX, EPI_PCG><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    case EPI_RHS: k_fdwt_res<RMAX, EPI_RHS><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    case EPI_RHSQ: k_fdwt_res<RMAX, EPI_RHSQ><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    default: k_fdwt_res<RMAX, EPI_PLAIN><<<ntiles, 1024, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
+    case EPI_APPLYM: k_fdwt_res<RMAX, EPI_APPLYM><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
+    case EPI_PCG: k_fdwt_res<RMAX, EPI_PCG><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
+    case EPI_RHS: k_fdwt_res<RMAX, EPI_RHS><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
+    case EPI_RHSQ: k_fdwt_res<RMAX, EPI_RHSQ><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
+    default: k_fdwt_res<RMAX, EPI_PLAIN><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
   }
 }
 template <int T, int NT>

@@ -4035,13 +4035,10 @@ struct TableArg {
 };
 constexpr int kTableMax = 480;
 template <int N>
-__global__ __launch_bounds__(64) void k_table(const TableArg<N> a, uint64_t* dst, int n, int n_dst) {
+__global__ __launch_bounds__((N + 63) / 64 * 64) void k_table(const TableArg<N> a, uint64_t* dst, int n, int n_dst) {
   typedef uint64_t __attribute__((address_space(1)))* gptr_w64;
-#pragma unroll
-  for (int u = 0; u < (N + 63) / 64; ++u) {
-    const int i = threadIdx.x + 64 * u;
-    if (i < n_dst) ((gptr_w64)dst)[i] = i < n ? a.v[min(i, N - 1)] : 0;
-  }
+  const int i = threadIdx.x;
+  if (i < n_dst) ((gptr_w64)dst)[i] = i < n ? a.v[min(i, N - 1)] : 0;
 }
 
 // ------------------------------------------------------------ launchers
@@ -4062,7 +4059,7 @@ template <int N>
 static void launch_table_n(const uint64_t* v, int n, uint64_t* dst, int n_dst, hipStream_t stream) {
   TableArg<N> a;
   std::memcpy(a.v, v, sizeof(uint64_t) * n);
-  k_table<N><<<1, 64, 0, stream>>>(a, dst, n, n_dst);
+  k_table<N><<<1, (N + 63) / 64 * 64, 0, stream>>>(a, dst, n, n_dst);
 }
 void launch_table(const uint64_t* v, int n, uint64_t* dst, int n_dst, hipStream_t stream) {
   for (int o = 0; o < n_dst; o += kTableMax) {

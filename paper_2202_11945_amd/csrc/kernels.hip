@@ -1177,9 +1177,10 @@ __device__ __forceinline__ void dir_place(const PSrc& ps, bool first, int n, int
 // A run of NP synthesis output pairs, as syn_run, with the rounding of every
 // sum fixed by explicit multiply-adds: six products added in turn, of which
 // the first to be rounded by itself is that of the second tap (K1) or of the
-// first.  Which of the two depends on the level's output side alone, as in
-// the level-by-level kernels at the default resident side (a long PCG run
-// carries a different rounding into its fifth digit): see syn_order.
+// first.  Which of the two depends on the level's output side m alone, as in
+// the level-by-level kernels at the default resident side: the second for
+// m <= 4 and for m > kResMax (a long PCG run carries a different rounding
+// into its fifth digit).
 template <int NP, bool K1>
 __device__ __forceinline__ void syn_run_fixed(const float* a_src, const float* d_src, int S, int base, const Filter& F,
                                               float* dst, int ds) {
@@ -1232,7 +1233,8 @@ __device__ __forceinline__ void dir_levels(int n, int levels, const Filter& F, f
   using W = DirWin<T>;
   if constexpr (J < W::kLevels) dir_levels<T, J + 1, NT>(n, levels, F, A, B);
   if (J > levels) return;
-  if (J > 3 && n >> (J - 1) <= 4)
+  const int m = n >> (J - 1);  // the level's output side
+  if (m > kResMax || (J > 3 && m <= 4))
     dir_level<T, J, NT, true>(F, A, B);
   else
     dir_level<T, J, NT, false>(F, A, B);

@@ -305,10 +305,11 @@ struct OutDst {
   gptr_w a;
   gptr_w dm_out;
   float gain;
-  int mode;  // out_mode, with OUT_FIT split by pr.fitted
+  int mode;     // out_mode, with OUT_FIT split by pr.fitted
+  bool global;  // a layer above kResMax (see control_update)
 };
 enum { OUTD_PHI, OUTD_USER, OUTD_FITTED, OUTD_CONTROL, OUTD_CLOSED };
-__device__ __forceinline__ OutDst out_dst(const ProbDev& pr, const IoDev& io, int out_mode) {
+__device__ __forceinline__ OutDst out_dst(const ProbDev& pr, const IoDev& io, int out_mode, int n) {
   OutDst d;
   d.phi = (gptr_w)pr.phi;
   d.out = (gptr_w)io.out;
@@ -317,6 +318,7 @@ __device__ __forceinline__ OutDst out_dst(const ProbDev& pr, const IoDev& io, in
   d.a = d.aprev + pr.n_act;
   d.dm_out = (gptr_w)io.dm_out;
   d.gain = pr.gain;
+  d.global = n > kResMax;
   d.mode = out_mode == OUT_PHI    ? OUTD_PHI
            : out_mode == OUT_USER ? OUTD_USER
            : pr.fitted            ? OUTD_FITTED
@@ -330,6 +332,16 @@ __device__ __forceinline__ OutLoad out_fetch(const OutDst& d, int e) {
   if (d.mode == OUTD_CLOSED) o.ap = ((gptr_f)d.aprev)[e];
   return o;
 }
+// Open- or closed-loop control of Algorithm 1 from the output v, the previous
+// command a and the one before it, with the rounding fixed by explicit
+// multiply-adds, whichever kernel forms it.  In open loop the product that is
+// rounded by itself is that of a, for layers above kResMax that of v (as the
+// resident and the global levels' kernels have always had it).
+__device__ __forceinline__ float control_update(const OutDst& d, float v, float a, float ap) {
+  if (d.mode == OUTD_CLOSED) return fmaf(d.gain, v - ap, a);
+  const float w = 1.0f - d.gain;
+  return d.global ? fmaf(w, a, d.gain * v) : fmaf(d.gain, v, w * a);
+}
 __device__ __forceinline__ void out_finish(const OutDst& d, int e, float v, const OutLoad& o) {
   if (d.mode == OUTD_PHI) {
     d.phi[e] = v;
@@ -340,7 +352,7 @@ __device__ __forceinline__ void out_finish(const OutDst& d, int e, float v, cons
     if (d.layers_out) d.layers_out[e] = v;
   } else {  // OUT_FIT, F = I: open-loop or closed-loop control of Algorithm 1
     if (d.layers_out) d.layers_out[e] = v;
-    const float nw = d.mode == OUTD_CLOSED ? o.a + d.gain * (v - o.ap) : (1.0f - d.gain) * o.a + d.gain * v;
+    const float nw = control_update(d, v, o.a, o.ap);
     d.aprev[e] = o.a;
     d.a[e] = nw;
     if (d.dm_out) d.dm_out[e] = nw;
@@ -586,7 +598,7 @@ __global__ __launch_bounds__(1024) void k_idwt_res(const ProbDev* P, const Layer
   });
   if (direct) return;
   if (n == R) {
-    const OutDst od = out_dst(pr, io, out_mode);
+    const OutDst od = out_dst(pr, io, out_mode, n);
     for (int e0 = threadIdx.x; e0 < R * R; e0 += kU * nt) {
       OutLoad o[kU];
 #pragma unroll
@@ -732,7 +744,7 @@ __global__ __launch_bounds__(512) void k_idwt_res4(const ProbDev* P, const Layer
   // rows, straight to the output quadrant (the layer, or the coarse block of
   // the first global level)
   const bool final_level = (n == R);
-  const OutDst od = out_dst(pr, io, out_mode);
+  const OutDst od = out_dst(pr, io, out_mode, n);
   const gptr_w nxt = (gptr_w)(pr.tmpa + ly.tmp_off);  // stride R
   const int r0 = qy * h, c0 = qx * h;
   for (int e0 = threadIdx.x; e0 < h * h; e0 += kU * nt) {
@@ -865,7 +877,7 @@ __device__ __forceinline__ void idwt_glob_passes(const ProbDev& pr, const IoDev&
   }
   __syncthreads();
   const bool final_level = (m == n);
-  const OutDst od = out_dst(pr, io, out_mode);
+  const OutDst od = out_dst(pr, io, out_mode, n);
   for (int e0 = threadIdx.x; e0 < kGT * kGT; e0 += kU * nt) {  // rows
     OutLoad o[kU];
     if (final_level) {
@@ -1263,8 +1275,7 @@ __device__ __forceinline__ void out_finish4(const OutDst& d, int e, const v4f& v
     if (d.layers_out) *(gptr_w4u)(d.layers_out + e) = v;
     v4f nw;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      nw[i] = d.mode == OUTD_CLOSED ? o.a[i] + d.gain * (v[i] - o.ap[i]) : (1.0f - d.gain) * o.a[i] + d.gain * v[i];
+    for (int i = 0; i < 4; ++i) nw[i] = control_update(d, v[i], o.a[i], o.ap[i]);
     *(gptr_w4)(d.aprev + e) = o.a;
     *(gptr_w4)(d.a + e) = nw;
     if (d.dm_out) *(gptr_w4u)(d.dm_out + e) = nw;
@@ -1346,7 +1357,7 @@ __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDe
   // every record field before the first store (a store could alias the records)
   const int n = ly.n, off = ly.off, levels = ly.levels;
   const float inv_delta = ly.inv_delta;
-  const OutDst od = out_dst(pr, io, out_mode);
+  const OutDst od = out_dst(pr, io, out_mode, n);
   const CoarseDev* c = C + t.prob;
   if constexpr (COARSE)
     dir_window<T, NT, 4>(pr, n, levels, off, t, ps, iter, c, A);

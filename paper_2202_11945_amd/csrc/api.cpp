@@ -70,6 +70,7 @@ struct Plan {
   bool idwt_split = false;  // launch them instead of one workgroup per layer
   Range idwt_dir;           // the inverse transform in one launch of output tiles
   int dir_tile = 0;         // their side (0: the level-by-level kernels)
+  bool dir_big = false;     // some layer of them is above 2 kResMax
   Range fdwt_dir, fdwt_tail;  // the first three forward levels in one launch of input tiles, and the
                               // layers with deeper levels (the rest in one workgroup each)
   int fdir_tile = 0;        // side of the input tiles (0: the level-by-level kernels)
@@ -774,6 +775,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       // layer and problem records load in parallel
       t_idwt_res.push_back({k, l, 0, 0, 0, 0, pd.layer0 + l, 0});
       const int td = P.dir_tile > 0 ? P.hL[pd.layer0 + l].n / P.dir_tile : 0;
+      P.dir_big = P.dir_big || P.hL[pd.layer0 + l].n > 2 * kResMax;
       for (int ty = 0; ty < td; ++ty)
         for (int tx = 0; tx < td; ++tx) t_idwt_dir.push_back({k, l, ty, tx, 0, 0, pd.layer0 + l, 0});
       for (int q = 0; q < 4; ++q) t_idwt_res4.push_back({k, l, 0, q, 0, 0, pd.layer0 + l, 0});
@@ -1459,6 +1461,7 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
   a.res_max = P.ires_max;
   a.fres_max = P.fres_max;
   a.aug_max = P.aug_max;
+  a.dir_big = P.dir_big ? 1 : 0;
   a.pt_rows = P.pt_rows;
   a.pt_wide = P.pt_wide ? 1 : 0;
   a.pt_split = P.pt_split ? 1 : 0;

@@ -1240,13 +1240,15 @@ __device__ __forceinline__ void dir_level(const Filter& F, float* A, float* B) {
   }
   __syncthreads();
 }
-template <int T, int J, int NT>
+// BIG: layers above 2 kResMax, whose levels below the finest can be above
+// kResMax too.
+template <int T, int J, int NT, bool BIG>
 __device__ __forceinline__ void dir_levels(int n, int levels, const Filter& F, float* A, float* B) {
   using W = DirWin<T>;
-  if constexpr (J < W::kLevels) dir_levels<T, J + 1, NT>(n, levels, F, A, B);
+  if constexpr (J < W::kLevels) dir_levels<T, J + 1, NT, BIG>(n, levels, F, A, B);
   if (J > levels) return;
   const int m = n >> (J - 1);  // the level's output side
-  if (m > kResMax || (J > 3 && m <= 4))
+  if ((BIG && m > kResMax) || (J > 3 && m <= 4))
     dir_level<T, J, NT, true>(F, A, B);
   else
     dir_level<T, J, NT, false>(F, A, B);
@@ -1343,7 +1345,9 @@ __device__ __forceinline__ void dir_finest(const OutDst& od, int off, int n, con
 
 // COARSE: the instantiation for converged solves with the coarse-level
 // correction (its fourth operand costs registers that frames do not have).
-template <int T, int NT, bool COARSE>
+// BIG: the one for launches with layers above 2 kResMax (its second form of
+// the lower levels makes the others 0.2 us slower at 768 tiles of 64).
+template <int T, int NT, bool COARSE, bool BIG>
 __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
                                                  const Tile* tiles, Filter F, int src_mode, int out_mode, int iter,
                                                  const CoarseDev* C) {
@@ -1368,7 +1372,7 @@ __global__ __launch_bounds__(NT) void k_idwt_dir(const ProbDev* P, const LayerDe
   else
     dir_window<T, NT, 1>(pr, n, levels, off, t, ps, iter, c, A);
   __syncthreads();
-  dir_levels<T, 2, NT>(n, levels, F, A, B);
+  dir_levels<T, 2, NT, BIG>(n, levels, F, A, B);
   if (n > kResMax)
     dir_finest<T, NT, true>(od, off, n, t, F, inv_delta, A, B);
   else
@@ -4086,8 +4090,11 @@ void launch_table(const uint64_t* v, int n, uint64_t* dst, int n_dst, hipStream_
 void launch_idwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int src_mode, int out_mode,
                      int iter, const CoarseDev* C) {
   if (ntiles <= 0) return;
-#define FEWHA_ID(T, NT, CO) \
-  k_idwt_dir<T, NT, CO><<<ntiles, NT, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode, out_mode, iter, C)
+#define FEWHA_ID(T, NT, CO)                                                                                        \
+  a.dir_big ? k_idwt_dir<T, NT, CO, true><<<ntiles, NT, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode,      \
+                                                                       out_mode, iter, C)                         \
+            : k_idwt_dir<T, NT, CO, false><<<ntiles, NT, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, src_mode,     \
+                                                                        out_mode, iter, C)
   // no more workgroups than compute units: twice the threads each (96 tiles of
   // the 39 m system 6.4 -> 6.0 us; 336 tiles of nine layers 7.8 -> 8.1 us)
   const bool wide = ntiles <= kCus;

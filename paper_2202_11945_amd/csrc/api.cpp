@@ -103,6 +103,7 @@ struct Plan {
   int nprob_all = 0;                         // problems plus two fitting views per fitted problem
   FitDev* dF = nullptr;
   int max_fit_iters = 0;
+  int n_slots = 0;                           // most slots of p^T M p of a problem
   int aug_max = 0;                           // most directions kept by a problem (augmented PCG)
   Filter F{};
   std::map<int, hipGraphExec_t> graphs;
@@ -784,12 +785,17 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       } else {
         const LayerDev& ld = P.hL[pd.layer0 + l];
         const int tf = ld.n / P.fdir_tile;
+        // slots: one per 32 x 32 piece of the layer, in order, whatever the tile side
+        const int pieces = ld.n / 32, per = P.fdir_tile / 32;
         for (int ty = 0; ty < tf; ++ty)
-          for (int tx = 0; tx < tf; ++tx) t_fdwt_dir.push_back({k, l, ty, tx, slot++, 0, pd.layer0 + l, 0});
+          for (int tx = 0; tx < tf; ++tx)
+            t_fdwt_dir.push_back({k, l, ty, tx, slot + per * (ty * pieces + tx), 0, pd.layer0 + l, 0});
+        slot += pieces * pieces;
         if (ld.levels > 3) t_fdwt_tail.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
       }
     }
     pd.n_slots_fdwt = slot;
+    P.n_slots = std::max(P.n_slots, slot);
     const int nupd = cdiv(pd.n_c, kUpdChunk);
     for (int c = 0; c < nupd; ++c) {
       t_upd.push_back({k, 0, c, 0, c, 0, 0, 0});
@@ -1462,6 +1468,7 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
   a.fres_max = P.fres_max;
   a.aug_max = P.aug_max;
   a.dir_big = P.dir_big ? 1 : 0;
+  a.n_slots = P.n_slots;
   a.pt_rows = P.pt_rows;
   a.pt_wide = P.pt_wide ? 1 : 0;
   a.pt_split = P.pt_split ? 1 : 0;

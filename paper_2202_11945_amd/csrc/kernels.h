@@ -48,6 +48,7 @@ struct LaunchArgs {
   const int2* gtrows;     // Shack-Hartmann adjoint tiles: per window row (span base << 1 | active flag
                           // of window column 32, active flags of window columns 0 .. 31), at tile.level
   int aug_max = 0;  // most directions that a problem of the plan keeps
+  int n_slots = 0;  // most slots of p^T M p of a problem of the plan
   int dir_big = 0;  // 1: layers above 2 kResMax on the one-launch inverse transform
   int pt_rows;         // node rows per thread of the propagation adjoint (4 or 8)
   int pt_wide;         // 1: some pair has K > 3 corners per node (the kernel with wide records)

@@ -9,6 +9,8 @@
 // pairs), so a thread keeps several global loads in flight.
 #include "kernels.h"
 
+#include "fwd_tile.h"
+
 #include <algorithm>
 #include <cstring>
 
@@ -64,11 +66,16 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f<kDppBcast31, 0xC>(v);
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
-__device__ __forceinline__ double wave_sum(double v) {
+// Sum of each row of 16 lanes, in all of its lanes.
+__device__ __forceinline__ double row_sum(double v) {
   v += dpp_d<kDppXor1, 0xF>(v);
   v += dpp_d<kDppXor2, 0xF>(v);
   v += dpp_d<kDppHalfMirror, 0xF>(v);
   v += dpp_d<kDppMirror, 0xF>(v);
+  return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = row_sum(v);
   v += dpp_d<kDppBcast15, 0xA>(v);
   v += dpp_d<kDppBcast31, 0xC>(v);
   const long long b = __double_as_longlong(v);
@@ -96,34 +103,35 @@ __device__ __forceinline__ T block_sum(T v, T* sh, int nthreads) {
 // Two phases, so that a kernel can put the slot loads in flight before its
 // own loads and reduce them while those are in flight: slots_issue requests
 // the first H slots of every lane of every group (up to 64 H per group)
-// together; slots_reduce adds them (and, for longer groups, the rest in a
-// loop).
-template <int G, int H>
+// together (HO of the odd groups); slots_reduce adds them (and, for longer
+// groups, the rest in a loop).
+template <int G, int H, int HO = H>
 struct SlotLoads {
-  double v[G][H];
+  static constexpr int of(int g) { return g % 2 ? HO : H; }
+  double v[G][H > HO ? H : HO];
 };
-template <int G, int H>
-__device__ __forceinline__ void slots_issue(const double* const (&s)[G], const int (&n)[G], SlotLoads<G, H>& L) {
+template <int G, int H, int HO = H>
+__device__ __forceinline__ void slots_issue(const double* const (&s)[G], const int (&n)[G], SlotLoads<G, H, HO>& L) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
 #pragma unroll
-    for (int u = 0; u < H; ++u) L.v[g][u] = 0.0;
+    for (int u = 0; u < L.of(g); ++u) L.v[g][u] = 0.0;
     if (n[g] > 0) {  // wave-uniform; a group of no slots may have no storage
 #pragma unroll
-      for (int u = 0; u < H; ++u) L.v[g][u] = ((gptr_d)s[g])[min(lane + 64 * u, n[g] - 1)];
+      for (int u = 0; u < L.of(g); ++u) L.v[g][u] = ((gptr_d)s[g])[min(lane + 64 * u, n[g] - 1)];
     }
   }
 }
-template <int G, int H>
-__device__ __forceinline__ void slots_reduce(const double* const (&s)[G], const int (&n)[G], const SlotLoads<G, H>& L,
-                                             double (&out)[G]) {
+template <int G, int H, int HO = H>
+__device__ __forceinline__ void slots_reduce(const double* const (&s)[G], const int (&n)[G],
+                                             const SlotLoads<G, H, HO>& L, double (&out)[G]) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     double a = 0.0;
 #pragma unroll
-    for (int u = 0; u < H; ++u) {
+    for (int u = 0; u < L.of(g); ++u) {
       // an opaque copy: without it the compiler folds the first addition
       // into slots_issue's branch, right behind its load, and waits there
       // for the slot before the kernel's own loads are requested
@@ -131,7 +139,7 @@ __device__ __forceinline__ void slots_reduce(const double* const (&s)[G], const 
       asm volatile("" : "+v"(x));
       if (lane + 64 * u < n[g]) a += x;
     }
-    for (int i = lane + 64 * H; i < n[g]; i += 64) a += ((gptr_d)s[g])[i];
+    for (int i = lane + 64 * L.of(g); i < n[g]; i += 64) a += ((gptr_d)s[g])[i];
     out[g] = wave_sum(a);
   }
 }
@@ -1692,29 +1700,6 @@ __global__ __launch_bounds__(256) void k_fdwt_glob2(const ProbDev* P, const Laye
 // the workgroups.  A 39 m problem takes 4.5 us and 32 of them 10.8 (38 MB, 3.5
 // TB/s), and k_fdwt_res 3.8 and 4.2, where the level-by-level kernels took
 // 15.0 and 19.8 in all.
-template <int T>
-struct FwdWin {
-  static constexpr int D(int j) { return T >> j; }                     // detail outputs per direction
-  // coarse window (W(0): the input): W(3) = T / 8, W(j) = 2 W(j + 1) + 4
-  static constexpr int W(int j) { return (T >> j) + 4 * ((8 >> j) - 1); }
-  static constexpr int SR(int j) { return W(j) + D(j) + 1; }          // LDS stride of the row pass's output
-  static constexpr int SX(int j) { return W(j) + 1; }                 // ... of the coarse window
-  // output pairs of a task: four at the finest level; below, as few as the
-  // threads allow (a pass there costs its latency, not its reads)
-  static constexpr int run(int j) { return j == 1 ? 4 : T == 64 && j == 2 ? 2 : 1; }
-  static constexpr int runs(int j) { return W(j) / run(j); }
-  // column tasks, each a column and a run of pairs, in classes of whole
-  // waves: x-high columns (both halves in y are details), x-low columns
-  // under the tile (coarse and detail), the rest of the coarse window
-  static constexpr int det(int j) { return D(j) * D(j) / run(j); }
-  static constexpr int pad(int n) { return (n + 63) / 64 * 64; }
-  static constexpr int at_low(int j) { return pad(det(j)); }
-  static constexpr int at_rest(int j) { return 2 * pad(det(j)); }
-  static constexpr int rest(int j) { return W(j) * runs(j) - det(j); }
-  static constexpr int rounds(int j, int nt) {
-    return ((rest(j) > 0 ? at_rest(j) + rest(j) : at_low(j) + det(j)) + nt - 1) / nt;
-  }
-};
 
 // Epilogue of one output from its unscaled sum a, with the rounding of the
 // level-by-level kernels fixed by explicit multiply-adds: M x and q round the
@@ -1789,33 +1774,12 @@ struct FwdTile {
   EpiDst dst;
 };
 
-// The wave's place in a round of level J's column tasks: first task of the
-// wave (uniform), its class, this thread's column and run.
-enum { FWD_HIGH, FWD_LOW, FWD_REST, FWD_NONE };
+// This thread's column task in round u of level J (its class wave-uniform).
 template <int T, int J, int NT>
-struct FwdTask {
-  int cls, c, r;
-  bool on;
-  __device__ __forceinline__ FwdTask(int u) {
-    using W = FwdWin<T>;
-    constexpr int D = W::D(J), D4 = D / W::run(J);
-    const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63) + u * NT;
-    int e = w0 + ((int)threadIdx.x & 63);
-    cls = w0 < W::at_low(J) ? FWD_HIGH : w0 < W::at_rest(J) ? FWD_LOW : FWD_REST;
-    if (cls != FWD_REST) {
-      e -= cls == FWD_LOW ? W::at_low(J) : 0;
-      on = e < W::det(J);
-      c = e % D;
-      r = on ? e / D : 0;
-    } else {
-      // columns past the tile in its runs, then every column in the runs past it
-      constexpr int side = W::W(J) - D, first = side * D4;
-      e -= W::at_rest(J);
-      on = e < W::rest(J);
-      c = e < first ? D + e % (side > 0 ? side : 1) : (e - first) % W::W(J);
-      r = !on ? 0 : e < first ? e / (side > 0 ? side : 1) : D4 + (e - first) / W::W(J);
-    }
-  }
+struct FwdTask : FwdPlace {
+  __device__ __forceinline__ explicit FwdTask(int u)
+      : FwdPlace(fwd_place<T, J>(__builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63) + u * NT,
+                                 (int)threadIdx.x & 63)) {}
   // the position of the task's first output in half (hy, hx) of the level
   __device__ __forceinline__ int pos(const FwdTile& t, int hy, int hx) const {
     constexpr int D = FwdWin<T>::D(J);
@@ -1837,7 +1801,7 @@ __device__ __forceinline__ void fwd_ops(const EpiSrc& src, const FwdTile& t, Fwd
   constexpr int RL = FwdWin<T>::run(J);
 #pragma unroll
   for (int u = 0; u < FwdOps<T, J, NT>::kR; ++u) {
-    if (u * NT >= FwdWin<T>::at_rest(J)) break;
+    if (u > 0) break;  // every detail is in the first round
     const FwdTask<T, J, NT> k(u);
     if (k.cls == FWD_HIGH) {
       const int a = k.pos(t, 0, 1), d = k.pos(t, 1, 1);
@@ -1934,7 +1898,7 @@ __global__ __launch_bounds__(NT) void k_fdwt_dir(const ProbDev* P, const LayerDe
   using W = FwdWin<T>;
   __shared__ float R[W::W(0) * W::SR(1)];
   __shared__ float X[W::W(1) * W::SX(1)];
-  __shared__ double sh[NT / 64];
+  __shared__ double sh[NT / 16], sh3[8];
   // the deeper levels in the place of level 1's rows once these are used up
   constexpr int at2 = W::W(1) * W::SR(2), at3 = at2 + W::W(2) * W::SX(2);
   float *X2 = R + at2, *R3 = R + at3;
@@ -2003,14 +1967,34 @@ __global__ __launch_bounds__(NT) void k_fdwt_dir(const ProbDev* P, const LayerDe
   fwd_rows<T, 2, NT>(F, X, R);
   __syncthreads();
   fwd_columns<T, 2, NT, EPI>(t, F, R, X2, o2, acc);
+  constexpr bool sums = EPI == EPI_PCG || EPI == EPI_RHS || EPI == EPI_RHSQ;
+  if (sums) {
+    acc = row_sum(acc);
+    if ((threadIdx.x & 15) == 0) sh[threadIdx.x >> 4] = acc;
+    acc = 0.0;
+  }
   if (EPI != EPI_PCG) fwd_ops<T, 3, NT, EPI>(src, t, o3);
   __syncthreads();
   fwd_rows<T, 3, NT>(F, X2, R3);
   __syncthreads();
   fwd_columns<T, 3, NT, EPI>(t, F, R3, nullptr, o3, acc);
-  if (EPI == EPI_PCG || EPI == EPI_RHS || EPI == EPI_RHSQ) {
-    const double s = block_sum(acc, sh, NT);
-    if (threadIdx.x == 0) ((gptr_wd)dots)[(long)dot_group_of(EPI, iter) * n_dots + tile.slot] = s;
+  if (sums) {
+    // one partial per 32 x 32 piece: its rows of lanes in both classes (see FwdWin)
+    static_assert(W::at_rest <= NT, "every detail in the first round");
+    if (threadIdx.x < 2 * 64) {
+      acc = row_sum(acc);
+      if ((threadIdx.x & 15) == 0) sh3[threadIdx.x >> 4] = acc;
+    }
+    __syncthreads();
+    const int p = threadIdx.x;
+    if (p < W::pieces) {
+      auto rows = [&](int cls) {
+        auto at = [&](int i) { return sh[4 * (cls * W::pieces + W::wave_of(cls, p, i)) + W::place_of(p, i)]; };
+        return ((at(0) + at(1)) + (at(2) + at(3))) + sh3[4 * cls + p];
+      };
+      const int slot = tile.slot + p / W::side * (n >> 5) + p % W::side;
+      ((gptr_wd)dots)[(long)dot_group_of(EPI, iter) * n_dots + slot] = rows(FWD_HIGH) + rows(FWD_LOW);
+    }
   }
 }
 
@@ -3485,7 +3469,12 @@ __global__ __launch_bounds__(256) void k_aug_store(const ProbDev* P, const IoDev
 // vectors for many (32 problems: 9.6 and 16.4 us, 3.9 and 5.4 TB/s).
 // KM: most directions kept by a problem of an augmented plan (2 or kAugMax;
 // 0: plain), whose images are requested with the other vectors.
-template <int XM, bool COARSE, int KM>
+// MANY: problems of more than kSlotsFew slots of pi (one per 32 x 32 of the
+// layers), all of which are requested together: nine layers of up to 256 x
+// 256 (345 slots) 3.4 us and 13.4 for eight such problems, against 4.0 and
+// 14.3 with the rest in a loop; the registers cost a 39 m problem (99 slots)
+// 0.2 us.
+template <int XM, bool COARSE, int KM, bool MANY>
 __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* IO, const Tile* tiles, int iter,
                                                 const CoarseDev* C) {
   __shared__ double sh[4];
@@ -3528,8 +3517,9 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
     sl[3] = dot_group(pr, pi_grp(iter - 1));
     nn[3] = pr.n_slots_fdwt;
   }
-  SlotLoads<G, 2> sloads;
-  slots_issue<G, 2>(sl, nn, sloads);
+  constexpr int H = MANY ? 3 : 2, HO = MANY ? 6 : 2;  // the odd groups are those of pi
+  SlotLoads<G, H, HO> sloads;
+  slots_issue(sl, nn, sloads);
   // loads without branches (indices clamped to the chunk), so that the slot
   // sums below wait only for the slots
 #pragma unroll
@@ -3559,7 +3549,7 @@ __global__ __launch_bounds__(256) void k_update(const ProbDev* P, const IoDev* I
   const int n_dots = pr.n_dots, nsu = pr.n_slots_upd;
   // alpha = rho_k / pi_k
   double o[G];
-  slots_reduce<G, 2>(sl, nn, sloads, o);
+  slots_reduce(sl, nn, sloads, o);
   const double rho = COARSE ? o[0] + o[G - 1] : o[0], pi = o[1];
   const float a = (float)((pi > 0.0) ? rho / pi : 0.0);
   // a_{k-1} as the previous step formed it (a frame's steps have no coarse part)
@@ -4059,7 +4049,8 @@ __global__ __launch_bounds__((N + 63) / 64 * 64) void k_table(const TableArg<N> 
 }
 
 // ------------------------------------------------------------ launchers
-constexpr int kCus = 256;  // compute units
+constexpr int kCus = 256;       // compute units
+constexpr int kSlotsFew = 128;  // slots of a group that k_update requests together by default
 
 // The resident kernels are instantiated for LDS capacities 32, 64 and 128 and
 // launched with the smallest that holds the plan's resident side.
@@ -4233,25 +4224,32 @@ void launch_pT(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode) {
   }
 #undef FEWHA_PT
 }
-template <int KM>
+template <int KM, bool MANY>
 static void launch_update_n(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter, const CoarseDev* C, int xm) {
   if (xm == UPD_X_DEFER)
-    k_update<UPD_X_DEFER, false, KM><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    k_update<UPD_X_DEFER, false, KM, MANY><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
   else if (xm == UPD_X_PAIR)
-    k_update<UPD_X_PAIR, false, KM><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    k_update<UPD_X_PAIR, false, KM, MANY><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
   else if (C)  // converged solves: never with augmentation
-    k_update<UPD_X_ONE, true, 0><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    k_update<UPD_X_ONE, true, 0, MANY><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
   else
-    k_update<UPD_X_ONE, false, KM><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+    k_update<UPD_X_ONE, false, KM, MANY><<<ntiles, 256, 0, a.stream>>>(a.P, a.IO, tiles, iter, C);
+}
+template <int KM>
+static void launch_update_k(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter, const CoarseDev* C, int xm) {
+  if (a.n_slots > kSlotsFew)
+    launch_update_n<KM, true>(a, tiles, ntiles, iter, C, xm);
+  else
+    launch_update_n<KM, false>(a, tiles, ntiles, iter, C, xm);
 }
 void launch_update(const LaunchArgs& a, const Tile* tiles, int ntiles, int iter, const CoarseDev* C, int xm) {
   if (ntiles <= 0) return;
   if (a.aug_max == 0)
-    launch_update_n<0>(a, tiles, ntiles, iter, C, xm);
+    launch_update_k<0>(a, tiles, ntiles, iter, C, xm);
   else if (a.aug_max <= 2)
-    launch_update_n<2>(a, tiles, ntiles, iter, C, xm);
+    launch_update_k<2>(a, tiles, ntiles, iter, C, xm);
   else
-    launch_update_n<kAugMax>(a, tiles, ntiles, iter, C, xm);
+    launch_update_k<kAugMax>(a, tiles, ntiles, iter, C, xm);
 }
 void launch_coarse(const LaunchArgs& a, const CoarseTile* tiles, int ntiles, const CoarseDev* members, int k) {
   if (ntiles > 0) k_coarse<<<ntiles, kCoarseThreads, 0, a.stream>>>(tiles, members, k);

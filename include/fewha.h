@@ -406,12 +406,15 @@ FEWHA_API void fewha_batch_destroy(fewha_batch* b);
 
 /* ---- tuning: launch shapes chosen per plan (by an autotuner or by hand) ---- */
 
-/* Plans whose layers all have sides of 32 or more and 3 to 5 levels (6 with
- * sides of 64 or more) run the inverse transform as one launch of output
- * tiles, and the forward transform's first three levels as one launch of
- * input tiles (except plans of layers up to 64 x 64 with more than 3
- * levels): dwt_resident, res_split and glob_fuse are checked as below but
- * choose nothing there.
+/* A problem whose layers all have sides of 32 or more and 3 to 5 levels (or
+ * sides of 64 or more and 3 to 6) runs the inverse transform in one launch of
+ * output tiles; one whose layers have sides of 32 to 1024 and 3 levels or
+ * more runs the forward transform's first three levels in one launch of input
+ * tiles (problems of layers up to 64 x 64 with more than 3 levels, where no
+ * other problem of the plan has such tiles, in one launch of whole layers).
+ * dwt_resident, res_split and glob_fuse are checked as below but choose
+ * nothing for these problems' transforms; the other problems of a batch keep
+ * the level-by-level kernels, in launches of their own.
  * dwt_resident: side of the largest transform block kept in one workgroup's
  * LDS by the resident DWT kernels (32, 64 or 128; 0 = default 128).  Levels
  * above it run as tiled passes over global memory, one launch per level.

@@ -30,6 +30,14 @@ constexpr int kSolveCheck = 16;   // iterations between two convergence checks o
 constexpr int kMaxSweeps = 32;    // refinement sweeps of one solve
 static_assert(kSolveCheck == kDotRing, "a captured block of steps replays on the ring's own period");
 
+// Kernels of a problem's transforms: side of the inverse's output tiles (0:
+// level by level), and whether the first three forward levels are tiles.
+struct Transform {
+  int inverse = 0;
+  bool forward = false;
+  bool canon = false;  // forward level by level, with the sums of the tiles
+};
+
 int ilog2i(int n) {
   int k = 0;
   while ((1 << k) < n) ++k;
@@ -68,12 +76,15 @@ struct Plan {
   Range idwt_res, fdwt_res, pg, gt, pt, upd;
   Range idwt_res4;          // the resident inverse levels in quarters (four tiles per layer)
   bool idwt_split = false;  // launch them instead of one workgroup per layer
-  Range idwt_dir;           // the inverse transform in one launch of output tiles
-  int dir_tile = 0;         // their side (0: the level-by-level kernels)
+  // the problems whose inverse transform is one launch of output tiles, of
+  // 32 and of 64 a side (the others: the level-by-level kernels)
+  Range idwt_dir, idwt_dir64;
   bool dir_big = false;     // some layer of them is above 2 kResMax
-  Range fdwt_dir, fdwt_tail;  // the first three forward levels in one launch of input tiles, and the
-                              // layers with deeper levels (the rest in one workgroup each)
-  int fdir_tile = 0;        // side of the input tiles (0: the level-by-level kernels)
+  Range fdwt_canon;         // whole layers of the problems whose forward transform has Transform::canon
+  Range fdwt_dir;           // the first three forward levels in one launch of input tiles
+  int fdir_tile = 32;       // their side
+  std::vector<Transform> how;  // per problem: its transforms' kernels
+  Range coarse_p;           // vector-update chunks of the problems whose inverse transform is level by level
   int ires_max = 1, fres_max = 1;  // largest blocks of one workgroup, inverse and forward
   Range sin;  // slopes input: 2 x 2 groups of the propagation stage's subaperture tiles
   Range sin_frame, pg_pol;  // a frame's slope input: open-loop problems / closed-loop problems
@@ -393,54 +404,74 @@ struct PtLists {
   }
 };
 
-// Side of the output tiles of the one-launch inverse transform: 64 once that
-// gives the chip more than one workgroup per CU, else 32 (four times the
-// workgroups; measured on 39 m problems, 24 tiles of 64 each: 6.0 against 10.4
-// us for one, 10.3 against 11.2 for 8, 15.9 against 15.0 for 16, 25.5 against
-// 19.8 for 32; the level-by-level kernels take 17.0, 18.7, 21.4 and 27.4), or 0
-// where a layer is smaller than a tile or has more levels than a tile can halve (or
-// fewer than kDirMinLevels): the level-by-level kernels then.
-constexpr long kDirTiles64 = 320;
-int dir_tile(const std::vector<const HostModel*>& models) {
-  bool ok32 = true, ok64 = true;
-  long tiles64 = 0;
-  for (const HostModel* m : models)
-    for (const LayerHost& lh : m->layers) {
+// The kernels of every problem's transforms.  Which ones follows from its own
+// layers, so that a problem's sums do not depend on the batch that it is in;
+// the side of the tiles, which changes no sum, from the number of them.
+//
+// Inverse: output tiles in one launch where every layer is at least as large
+// as a tile and has no more levels than it can halve (5 at 32 a side, 6 at
+// 64), nor fewer than kDirMinLevels.  Tiles of 64 once they give the chip more
+// than one workgroup per CU, else of 32 (four times the workgroups; measured
+// on 39 m problems, 24 tiles of 64 each: 6.0 against 10.4 us for one, 10.3
+// against 11.2 for 8, 15.9 against 15.0 for 16, 25.5 against 19.8 for 32; the
+// level-by-level kernels take 17.0, 18.7, 21.4 and 27.4); problems of six
+// levels have tiles of 64 whatever their number.
+//
+// Forward: three levels per launch of input tiles where every layer has three
+// levels and leaves at most kResMax x kResMax to one workgroup.  The larger
+// tile pays earlier (5.3 against 5.8 us for one, 6.4 against 5.9 for 4, 7.8
+// against 6.1 for 8, 20.3 against 11.6 for 32 when every task took four
+// pairs, now 4.4 for one at 32 and 5.4, 5.7 and 10.7 at 64; the rest of the
+// levels 3.8 to 4.2 us more; the level-by-level kernels take 15.0 in all for
+// one, 15.9 for 8, 19.8 for 32).  Problems of layers of at most 64 x 64 with
+// deeper levels are one launch of one workgroup per layer (canon; 5 layers of
+// 64 x 64, four levels: 6.0 against 4.4 + 3.7 us), unless another problem has
+// the tiles launched anyway (12 such problems beside 12 of the 39 m system:
+// 7.2 + 5.8 us with workgroups of their own, 7.4 + 3.9 with tiles); the sums
+// are the same either way.
+constexpr long kDirTiles64 = 320, kFwdTiles64 = 64;
+std::vector<Transform> transforms_of(const std::vector<const HostModel*>& models, int& fdir_tile) {
+  std::vector<Transform> how(models.size());
+  bool all64 = true, fall64 = true;  // every problem with tiles can have them at 64
+  bool tiled = false;                // some problem has input tiles for its own sake
+  long tiles64 = 0, ftiles64 = 0;
+  std::vector<std::pair<bool, long>> fwd(models.size());  // can have tiles of 64; how many
+  for (size_t k = 0; k < models.size(); ++k) {
+    bool ok32 = true, ok64 = true, fok32 = true, fok64 = true, small = true, deep = false;
+    long t64 = 0;
+    for (const LayerHost& lh : models[k]->layers) {
       const int n = lh.d.n, lv = lh.d.levels;
       ok32 = ok32 && n >= 32 && lv >= kDirMinLevels && lv <= 5;
       ok64 = ok64 && n >= 64 && lv >= kDirMinLevels && lv <= 6;
-      tiles64 += (long)(n / 64) * (n / 64);
-    }
-  if (ok64 && tiles64 >= kDirTiles64) return 64;
-  return ok32 ? 32 : 0;
-}
-
-// The same for the forward transform's three levels per launch, whose larger
-// tile pays earlier (39 m problems, 24 tiles of 64 each: 5.3 against 5.8 us for
-// one, 6.4 against 5.9 for 4, 7.8 against 6.1 for 8, 20.3 against 11.6 for 32
-// when every task took four pairs, now 4.5 for one at 32 and 5.4, 5.7 and 10.7
-// at 64; the rest of the levels 3.8 to 4.2 us more; the level-by-level kernels take
-// 15.0 in all for one, 15.9 for 8, 19.8 for 32).  A layer needs three levels
-// and leaves at most kResMax x kResMax to one workgroup.  Layers of at most 64
-// x 64 with deeper levels are one launch of one workgroup per layer the other
-// way (5 layers of 64 x 64, four levels: 6.2 against 5.2 + 3.7 us).
-constexpr long kFwdTiles64 = 64;
-int fdir_tile(const std::vector<const HostModel*>& models) {
-  bool ok32 = true, ok64 = true, small = true, deep = false;
-  long tiles64 = 0;
-  for (const HostModel* m : models)
-    for (const LayerHost& lh : m->layers) {
-      const int n = lh.d.n;
       small = small && n <= 64;
-      deep = deep || lh.d.levels > 3;
-      const bool ok = lh.d.levels >= 3 && n / 8 <= kResMax;
-      ok32 = ok32 && ok && n >= 32;
-      ok64 = ok64 && ok && n >= 64;
-      tiles64 += (long)(n / 64) * (n / 64);
+      deep = deep || lv > 3;
+      const bool fok = lv >= 3 && n / 8 <= kResMax;
+      fok32 = fok32 && fok && n >= 32;
+      fok64 = fok64 && fok && n >= 64;
+      t64 += (long)(n / 64) * (n / 64);
     }
-  if (small && deep) return 0;
-  if (ok64 && tiles64 >= kFwdTiles64) return 64;
-  return ok32 ? 32 : 0;
+    how[k].inverse = ok32 ? 32 : ok64 ? 64 : 0;
+    how[k].forward = fok32;
+    how[k].canon = fok32 && small && deep;
+    tiled = tiled || (fok32 && !how[k].canon);
+    fwd[k] = {fok64, t64};
+    if (how[k].inverse > 0) {
+      all64 = all64 && ok64;
+      tiles64 += t64;
+    }
+  }
+  for (size_t k = 0; k < models.size(); ++k) {
+    if (how[k].canon && tiled) how[k].canon = false;
+    if (how[k].canon) how[k].forward = false;
+    if (!how[k].forward) continue;
+    fall64 = fall64 && fwd[k].first;
+    ftiles64 += fwd[k].second;
+  }
+  if (all64 && tiles64 >= kDirTiles64)
+    for (Transform& t : how)
+      if (t.inverse > 0) t.inverse = 64;
+  fdir_tile = fall64 && ftiles64 >= kFwdTiles64 ? 64 : 32;
+  return how;
 }
 
 // Split propagation-adjoint tiles (one band record, the sensors over the
@@ -533,8 +564,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   P.pt_split = split_pt;
   P.fit_split = split_fit;
   P.idwt_split = split == 4;
-  P.dir_tile = dir_tile(models);
-  P.fdir_tile = fdir_tile(models);
+  P.how = transforms_of(models, P.fdir_tile);
   P.nprob = (int)models.size();
   P.models = models;
   HIP_TRY(hipSetDevice(device));
@@ -557,7 +587,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   std::vector<ProbLayout> lay(P.nprob);
   Carver cv;
   std::vector<Tile> t_sin, t_sinf, t_pgpol, t_aug, t_r64gt;
-  std::vector<Tile> t_idwt_dir, t_fdwt_dir, t_fdwt_tail;
+  std::vector<Tile> t_idwt_dir, t_idwt_dir64, t_fdwt_dir, t_fdwt_canon, t_coarse_p;
   std::vector<Tile> t_idwt_res, t_idwt_res4, t_fdwt_res, t_pg, t_gt, t_pt, t_upd, t_sinit, t_gprior, t_ghgt, t_r64wfs,
       t_r64pt;
   HatTables hats;  // hat tables and band records of every problem and fitting view, one set per plan
@@ -575,6 +605,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   std::vector<std::vector<GLPar>> glp(P.nprob);
   for (int k = 0; k < P.nprob; ++k) {
     const HostModel& m = *models[k];
+    const Transform how = P.how[k];
     ProbDev pd{};
     const int L = (int)m.layers.size(), G = (int)m.wfs.size();
     pd.L = L;
@@ -599,12 +630,12 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       ld.res = std::min(ld.n, res);
       ld.off = m.layer_off[l];
       ld.n_glob_levels = ilog2i(ld.n / ld.res);
-      ld.fres = P.fdir_tile > 0 ? ld.n / 8 : ld.res;
-      ld.fsteps = P.fdir_tile > 0 ? 1 : ld.n_glob_levels;
-      P.ires_max = std::max(P.ires_max, ld.res);
+      ld.fres = how.forward ? ld.n / 8 : ld.res;
+      ld.fsteps = how.forward ? 1 : ld.n_glob_levels;
+      if (how.inverse == 0) P.ires_max = std::max(P.ires_max, ld.res);
       P.fres_max = std::max(P.fres_max, ld.fres);
       ld.tmp_off = tmp_total;
-      tmp_total += tmp_words(ld, P.fdir_tile > 0);
+      tmp_total += tmp_words(ld, how.forward);
       ld.inv_delta = (float)(1.0 / lh.delta);
       for (int j = 0; j < kMaxLevelsJ; ++j) {
         ld.alpha_d[j] = (float)(m.alpha * lh.dtab[j]);
@@ -750,10 +781,11 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
         // with glob_fuse a layer's first two global levels are one tile at
         // step 0 (its inner coarse block goes where step 1 would put it)
         const bool ffuse = glob_fuse && ld.n_glob_levels >= 2;
-        if (P.fdir_tile == 0 && !(ffuse && s == 1))
+        if (!how.forward && !(ffuse && s == 1))
           for (int ty = 0; ty < tq; ++ty)
             for (int tx = 0; tx < tq; ++tx)
               t_fdwt_glob[s].push_back({k, l, ty, tx, slot++, ilog2i(mf), pd.layer0 + l, (ffuse && s == 0) ? 1 : 0});
+        if (how.inverse > 0) continue;
         // inverse: output side; with glob_fuse a layer's last two global
         // levels are one tile of its full side at the inner level's step
         // (reading that step's scratch), and its last step has no tiles
@@ -774,24 +806,29 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
     for (int l = 0; l < L; ++l) {
       // transform tiles carry the global layer index (mask), so that the
       // layer and problem records load in parallel
-      t_idwt_res.push_back({k, l, 0, 0, 0, 0, pd.layer0 + l, 0});
-      const int td = P.dir_tile > 0 ? P.hL[pd.layer0 + l].n / P.dir_tile : 0;
-      P.dir_big = P.dir_big || P.hL[pd.layer0 + l].n > 2 * kResMax;
-      for (int ty = 0; ty < td; ++ty)
-        for (int tx = 0; tx < td; ++tx) t_idwt_dir.push_back({k, l, ty, tx, 0, 0, pd.layer0 + l, 0});
-      for (int q = 0; q < 4; ++q) t_idwt_res4.push_back({k, l, 0, q, 0, 0, pd.layer0 + l, 0});
-      if (P.fdir_tile == 0) {
-        t_fdwt_res.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
+      const LayerDev& ld = P.hL[pd.layer0 + l];
+      if (how.inverse == 0) {
+        t_idwt_res.push_back({k, l, 0, 0, 0, 0, pd.layer0 + l, 0});
+        for (int q = 0; q < 4; ++q) t_idwt_res4.push_back({k, l, 0, q, 0, 0, pd.layer0 + l, 0});
       } else {
-        const LayerDev& ld = P.hL[pd.layer0 + l];
-        const int tf = ld.n / P.fdir_tile;
+        P.dir_big = P.dir_big || ld.n > 2 * kResMax;
+        for (int ty = 0; ty < ld.n / how.inverse; ++ty)
+          for (int tx = 0; tx < ld.n / how.inverse; ++tx)
+            (how.inverse == 64 ? t_idwt_dir64 : t_idwt_dir).push_back({k, l, ty, tx, 0, 0, pd.layer0 + l, 0});
+      }
+      if (how.forward) {
         // slots: one per 32 x 32 piece of the layer, in order, whatever the tile side
-        const int pieces = ld.n / 32, per = P.fdir_tile / 32;
+        const int tf = ld.n / P.fdir_tile, pieces = ld.n / 32, per = P.fdir_tile / 32;
         for (int ty = 0; ty < tf; ++ty)
           for (int tx = 0; tx < tf; ++tx)
             t_fdwt_dir.push_back({k, l, ty, tx, slot + per * (ty * pieces + tx), 0, pd.layer0 + l, 0});
         slot += pieces * pieces;
-        if (ld.levels > 3) t_fdwt_tail.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
+      }
+      if (how.canon) {  // the slots of the tiles and of the block that they would leave
+        t_fdwt_canon.push_back({k, l, 0, 0, slot, 0, pd.layer0 + l, 0});
+        slot += (ld.n / 32) * (ld.n / 32) + (ld.levels > 3 ? 1 : 0);
+      } else if (!how.forward || ld.levels > 3) {  // the resident block: all that the tiles leave
+        t_fdwt_res.push_back({k, l, 0, 0, slot++, 0, pd.layer0 + l, 0});
       }
     }
     pd.n_slots_fdwt = slot;
@@ -799,6 +836,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
     const int nupd = cdiv(pd.n_c, kUpdChunk);
     for (int c = 0; c < nupd; ++c) {
       t_upd.push_back({k, 0, c, 0, c, 0, 0, 0});
+      if (how.inverse == 0) t_coarse_p.push_back({k, 0, c, 0, c, 0, 0, 0});
       if (m.aug_keep > 0) t_aug.push_back({k, 0, c, 0, c, 0, 0, 0});
     }
     pd.n_slots_upd = nupd;
@@ -1107,8 +1145,10 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
   P.idwt_res = add(t_idwt_res);
   P.idwt_res4 = add(t_idwt_res4);
   P.idwt_dir = add(t_idwt_dir);
+  P.idwt_dir64 = add(t_idwt_dir64);
   P.fdwt_dir = add(t_fdwt_dir);
-  P.fdwt_tail = add(t_fdwt_tail);
+  P.fdwt_canon = add(t_fdwt_canon);
+  P.coarse_p = add(t_coarse_p);
   P.fdwt_res = add(t_fdwt_res);
   P.pg = add(t_pg);
   P.sin = add(t_sin);
@@ -1376,7 +1416,7 @@ fewha_status setup_noalloc(Plan& P, std::string& err) {
     size_t tmp = 4, sd = 4, vadj = 4, part = 4;
     for (int l = 0; l < pd.L; ++l) {
       const LayerDev& ld = P.hL[pd.layer0 + l];
-      tmp = std::max(tmp, sizeof(float) * (size_t)(ld.tmp_off + tmp_words(ld, P.fdir_tile > 0)));
+      tmp = std::max(tmp, sizeof(float) * (size_t)(ld.tmp_off + tmp_words(ld, P.how[k].forward)));
     }
     for (int g = 0; g < pd.G; ++g) {
       const WfsDev& wd = P.hW[pd.wfs0 + g];
@@ -1484,11 +1524,14 @@ LaunchArgs args(const Plan& P, hipStream_t s, const IoDev* io) {
 
 const Tile* T(const Plan& P, const Range& r) { return P.dT + r.off; }
 
-// C: p_k with the coarse-level correction (one-launch transform only)
+// C: p_k with the coarse-level correction, which the output tiles form
+// themselves and launch_coarse_p before the level-by-level kernels
 void enq_idwt(const Plan& P, const LaunchArgs& a, int src, int out, int iter, const CoarseDev* C = nullptr) {
-  if (P.dir_tile > 0) {
-    launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, P.dir_tile, src, out, iter, C);
-    return;
+  launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, 32, src, out, iter, C);
+  launch_idwt_dir(a, T(P, P.idwt_dir64), P.idwt_dir64.n, 64, src, out, iter, C);
+  if (C) {
+    launch_coarse_p(a, C, T(P, P.coarse_p), P.coarse_p.n, iter);
+    src = SRC_PJ;
   }
   if (P.idwt_split)
     launch_idwt_res4(a, T(P, P.idwt_res4), P.idwt_res4.n, src, out, iter);
@@ -1497,16 +1540,13 @@ void enq_idwt(const Plan& P, const LaunchArgs& a, int src, int out, int iter, co
   for (size_t s = 0; s < P.idwt_glob.size(); ++s)
     launch_idwt_glob(a, T(P, P.idwt_glob[s]), P.idwt_glob[s].n, src, out, iter, (int)s);
 }
-// from_in: the caller's io.in instead of phiadj (three-level launch only)
+// from_in: the caller's io.in instead of phiadj (input tiles only)
 void enq_fdwt(const Plan& P, const LaunchArgs& a, int epi, int iter, bool from_in = false) {
-  if (P.fdir_tile > 0) {
-    launch_fdwt_dir(a, T(P, P.fdwt_dir), P.fdwt_dir.n, P.fdir_tile, epi, iter, from_in);
-    launch_fdwt_res(a, T(P, P.fdwt_tail), P.fdwt_tail.n, epi, iter);
-    return;
-  }
+  launch_fdwt_dir(a, T(P, P.fdwt_dir), P.fdwt_dir.n, P.fdir_tile, epi, iter, from_in);
   for (size_t s = 0; s < P.fdwt_glob.size(); ++s)
     launch_fdwt_glob(a, T(P, P.fdwt_glob[s]), P.fdwt_glob[s].n, epi, iter, (int)s);
   launch_fdwt_res(a, T(P, P.fdwt_res), P.fdwt_res.n, epi, iter);
+  launch_fdwt_canon(a, T(P, P.fdwt_canon), P.fdwt_canon.n, epi, iter);
 }
 // A^T C_hat^{-1} (slopes in the work buffer) -> phiadj
 void enq_adjoint(const Plan& P, const LaunchArgs& a, int gt_mode, int pt_mode) {
@@ -1834,10 +1874,7 @@ fewha_status setup_coarse(Plan& P, hipStream_t st, std::string& err) {
 
 // Step k of a solve.
 void enq_solve_step(const Plan& P, const LaunchArgs& a, const CoarseDev* C, int k) {
-  // p_k with the coarse correction: formed by the one-launch transform itself
-  const bool own_p = C && P.dir_tile == 0;
-  if (own_p) launch_coarse_p(a, C, T(P, P.upd), P.upd.n, k);
-  enq_idwt(P, a, own_p ? SRC_PJ : (k == 0 ? SRC_PUPD0 : SRC_PUPD), OUT_PHI, k, own_p ? nullptr : C);
+  enq_idwt(P, a, k == 0 ? SRC_PUPD0 : SRC_PUPD, OUT_PHI, k, C);
   enq_apply_M_core(P, a);
   enq_fdwt(P, a, EPI_PCG, k);
   launch_update(a, T(P, P.upd), P.upd.n, k, C);
@@ -2006,8 +2043,9 @@ fewha_status run_transform(Plan& P, hipStream_t st, bool forward, const std::vec
       return FEWHA_EINVAL;
     }
   HIP_TRY(hipSetDevice(P.device));
-  const bool copy = (forward && P.fdir_tile == 0) || transforms_overlap(P, in, out);
+  const bool overlap = transforms_overlap(P, in, out);
   for (int k = 0; k < P.nprob; ++k) {
+    const bool copy = overlap || (forward && !P.how[k].forward);
     if (copy)
       HIP_TRY(hipMemcpyAsync(P.hP[k].phiadj, in[k], sizeof(float) * P.hP[k].n_c, hipMemcpyDeviceToDevice, st));
     io[k].in = copy ? P.hP[k].phiadj : in[k];
@@ -2887,20 +2925,20 @@ fewha_status fewha_batch_time_stage(fewha_batch* b, int stage, int reps, double*
   auto run = [&]() {
     switch (stage) {
       case FEWHA_STAGE_IDWT_RES:
-        if (P.dir_tile > 0) {
-          launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, P.dir_tile, SRC_PUPD, OUT_PHI, it);
-          wg = P.idwt_dir.n;
-        } else if (P.idwt_split) {
+        launch_idwt_dir(a, T(P, P.idwt_dir), P.idwt_dir.n, 32, SRC_PUPD, OUT_PHI, it);
+        launch_idwt_dir(a, T(P, P.idwt_dir64), P.idwt_dir64.n, 64, SRC_PUPD, OUT_PHI, it);
+        wg = P.idwt_dir.n + P.idwt_dir64.n;
+        if (P.idwt_split) {
           launch_idwt_res4(a, T(P, P.idwt_res4), P.idwt_res4.n, SRC_PUPD, OUT_PHI, it);
-          wg = P.idwt_res4.n;
+          wg += P.idwt_res4.n;
         } else {
           launch_idwt_res(a, T(P, P.idwt_res), P.idwt_res.n, SRC_PUPD, OUT_PHI, it);
-          wg = P.idwt_res.n;
+          wg += P.idwt_res.n;
         }
         break;
       case FEWHA_STAGE_IDWT_GLOB:
         wg = 0;
-        for (size_t st = 0; P.dir_tile == 0 && st < P.idwt_glob.size(); ++st) {
+        for (size_t st = 0; st < P.idwt_glob.size(); ++st) {
           launch_idwt_glob(a, T(P, P.idwt_glob[st]), P.idwt_glob[st].n, SRC_PUPD, OUT_PHI, it, (int)st);
           wg += P.idwt_glob[st].n;
         }
@@ -2918,23 +2956,18 @@ fewha_status fewha_batch_time_stage(fewha_batch* b, int stage, int reps, double*
         wg = P.pt.n;
         break;
       case FEWHA_STAGE_FDWT_GLOB:
-        wg = 0;
-        if (P.fdir_tile > 0) {
-          launch_fdwt_dir(a, T(P, P.fdwt_dir), P.fdwt_dir.n, P.fdir_tile, EPI_PCG, it, false);
-          wg = P.fdwt_dir.n;
-          break;
-        }
+        launch_fdwt_dir(a, T(P, P.fdwt_dir), P.fdwt_dir.n, P.fdir_tile, EPI_PCG, it, false);
+        wg = P.fdwt_dir.n;
         for (size_t st = 0; st < P.fdwt_glob.size(); ++st) {
           launch_fdwt_glob(a, T(P, P.fdwt_glob[st]), P.fdwt_glob[st].n, EPI_PCG, it, (int)st);
           wg += P.fdwt_glob[st].n;
         }
         break;
-      case FEWHA_STAGE_FDWT_RES: {
-        const Range& r = P.fdir_tile > 0 ? P.fdwt_tail : P.fdwt_res;
-        launch_fdwt_res(a, T(P, r), r.n, EPI_PCG, it);
-        wg = r.n;
+      case FEWHA_STAGE_FDWT_RES:
+        launch_fdwt_res(a, T(P, P.fdwt_res), P.fdwt_res.n, EPI_PCG, it);
+        launch_fdwt_canon(a, T(P, P.fdwt_canon), P.fdwt_canon.n, EPI_PCG, it);
+        wg = P.fdwt_res.n + P.fdwt_canon.n;
         break;
-      }
       case FEWHA_STAGE_UPDATE:
         launch_update(a, T(P, P.upd), P.upd.n, it);
         wg = P.upd.n;

@@ -72,6 +72,9 @@ void launch_fdwt_glob(const LaunchArgs& a, const Tile* tiles, int ntiles, int ep
 // from_in: the input is the caller's io.in, else phiadj
 void launch_fdwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int tile, int epi, int iter, bool from_in);
 void launch_fdwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter);
+// whole layers of 32 x 32 or 64 x 64 with three levels or more, with the sums of launch_fdwt_dir's tiles:
+// the slots of the 32 x 32 pieces, then that of the deeper levels
+void launch_fdwt_canon(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter);
 void launch_pgamma(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode);
 // compact slopes io.in -> slope buffer + tip/tilt partials; add = 1: added to the
 // buffer's current values (closed loop after PG_APREV)

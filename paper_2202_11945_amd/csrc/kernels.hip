@@ -419,7 +419,9 @@ __device__ __forceinline__ void epi_finish(const EpiDst& dst, int epi, int e, fl
     const float r0 = epi == EPI_RHS ? (v - l.x0) + l.x1 : v - l.x0;
     dst.b[e] = v;
     dst.r[e] = r0;
-    acc += (double)r0 * (double)r0 * (double)l.x2;
+    double t = (double)r0 * (double)r0 * (double)l.x2;
+    asm("" : "+v"(t));  // rounded before it is added, in every kernel
+    acc += t;
   } else {
     dst.out[e] = v;
   }
@@ -1722,7 +1724,9 @@ __device__ __forceinline__ void epi_put(const EpiDst& dst, int e, float ad, floa
     const float r0 = EPI == EPI_RHS ? d + l.x1 : d;
     dst.b[e] = v;
     dst.r[e] = r0;
-    acc += (double)r0 * (double)r0 * (double)l.x2;
+    double t = (double)r0 * (double)r0 * (double)l.x2;
+    asm("" : "+v"(t));  // rounded before it is added, in every kernel
+    acc += t;
   } else {
     dst.out[e] = v;
   }
@@ -1823,6 +1827,14 @@ __device__ __forceinline__ void fwd_ops(const EpiSrc& src, const FwdTile& t, Fwd
   }
 }
 
+// The inner-product terms of a task's RL output pairs, added in pairs.
+template <int RL>
+__device__ __forceinline__ double pair_sum(const double (&t)[RL]) {
+  if constexpr (RL == 4) return (t[0] + t[1]) + (t[2] + t[3]);
+  if constexpr (RL == 2) return t[0] + t[1];
+  return t[0];
+}
+
 // Columns of level J from its row-pass output R: the coarse window for the
 // next level into X (J < 3), the details with their epilogue.
 template <int T, int J, int NT, int EPI>
@@ -1840,14 +1852,16 @@ __device__ __forceinline__ void fwd_columns(const FwdTile& t, const Filter& F, c
 #pragma unroll
     for (int i = 0; i < 2 * RL + 4; ++i) x[i] = col[i * W::SR(J)];
     ana_run<RL>(x, F.h, a);
+    double term[RL] = {};  // per output pair
     if (k.cls == FWD_HIGH) {
       ana_run<RL>(x, F.g, d);
       const int pa = k.pos(t, 0, 1), pd = k.pos(t, 1, 1);
 #pragma unroll
       for (int p = 0; p < RL; ++p) {
-        epi_put<EPI>(t.dst, pa + p * t.n, t.ad[J - 1], a[p], t.inv_delta, glob, o.l[u][p], acc);
-        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][RL + p], acc);
+        epi_put<EPI>(t.dst, pa + p * t.n, t.ad[J - 1], a[p], t.inv_delta, glob, o.l[u][p], term[p]);
+        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][RL + p], term[p]);
       }
+      acc += pair_sum(term);
       continue;
     }
     if constexpr (J < 3) {
@@ -1856,7 +1870,8 @@ __device__ __forceinline__ void fwd_columns(const FwdTile& t, const Filter& F, c
     } else if (t.last) {
       const int pa = k.pos(t, 0, 0);
 #pragma unroll
-      for (int p = 0; p < RL; ++p) epi_put<EPI>(t.dst, pa + p * t.n, t.ad[2], a[p], t.inv_delta, glob, o.l[u][p], acc);
+      for (int p = 0; p < RL; ++p)
+        epi_put<EPI>(t.dst, pa + p * t.n, t.ad[2], a[p], t.inv_delta, glob, o.l[u][p], term[p]);
     } else {
       const int s = t.n >> 3;
 #pragma unroll
@@ -1867,7 +1882,8 @@ __device__ __forceinline__ void fwd_columns(const FwdTile& t, const Filter& F, c
       const int pd = k.pos(t, 1, 0);
 #pragma unroll
       for (int p = 0; p < RL; ++p)
-        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][RL + p], acc);
+        epi_put<EPI>(t.dst, pd + p * t.n, t.ad[J - 1], d[p], t.inv_delta, glob, o.l[u][RL + p], term[p]);
+      acc += pair_sum(term);
     }
   }
 }
@@ -2082,14 +2098,99 @@ struct ResLayer {
   float ad[7];  // alpha D by block side 1 .. 64
 };
 
+// The inner products of a layer that the input tiles of k_fdwt_dir could have
+// taken as well (the plan decides, by its other problems), so that they are
+// the tiles' to the bit: every task's sum (its term: one output pair, two at
+// the finest level of side 64) goes to LDS, and a wave per piece, of the last
+// ones of the workgroup, adds up the piece's in the tiles' own order, a level
+// behind the transform, which leaves these waves idle below the top level.
+// 60 layers of 64 x 64 take 6.2 us with it, 5.8 with one sum over the block in
+// the lanes' own order.
+struct CanonSums {
+  // terms of levels 1 .. 3 ([task][column], rows of 72, 36 and 18), then those of the third level's coarse band
+  static constexpr int kAt2 = 16 * 72, kAt3 = kAt2 + 16 * 36, kAtLl = kAt3 + 8 * 18, kWords = kAtLl + 64;
+  double* term;
+  double a[2] = {}, a3[2] = {};  // by class: levels 1 and 2; level 3
+  int n, piece, py, px;
+  bool mine;  // one of these waves
+
+  __device__ __forceinline__ void start(double* p, int side_n, int nt) {
+    const int side = side_n >> 5;  // 1 or 2
+    piece = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) - (nt / 64 - side * side);
+    term = p;
+    n = side_n;
+    mine = piece >= 0;
+    py = piece >> (side >> 1);
+    px = piece & (side - 1);
+  }
+  // Task k of column c of the level of output side m has the term v: kept
+  // until the next level's row pass (stored at once, the level's own barrier
+  // would wait for its FP64 chain).
+  double kept = 0.0;
+  int at = -1;
+  __device__ __forceinline__ void keep(int m, int k, int c, double v) {
+    kept = v;
+    at = m == n ? 72 * k + c : 2 * m == n ? kAt2 + 36 * k + c : kAt3 + 18 * k + c;
+  }
+  __device__ __forceinline__ void flush() {
+    if (at >= 0) term[at] = kept;
+    at = -1;
+  }
+  // level J of this wave's piece
+  template <int J>
+  __device__ __forceinline__ void level(bool last, double (&acc)[2]) const {
+    constexpr int D1 = 32 >> J;  // a piece's columns and pairs
+    const FwdPlace k = fwd_place<32, J>(0, (int)threadIdx.x & 63);  // the same lanes in both classes
+    if (!k.on) return;
+    const int y = py * D1 + FwdWin<32>::run(J) * k.r;
+#pragma unroll
+    for (int cls = FWD_HIGH; cls <= FWD_LOW; ++cls) {
+      const int c = (cls == FWD_HIGH ? n >> J : 0) + px * D1 + k.c;
+      if constexpr (J == 1) {
+        if (n == 64) {  // two pairs per task
+          const double* t = term + 72 * (y / 2) + c;
+          acc[cls] += t[0] + t[72];
+        } else {
+          const double* t = term + 72 * y + c;
+          acc[cls] += (t[0] + t[72]) + (t[144] + t[216]);
+        }
+      } else if constexpr (J == 2) {
+        const double* t = term + kAt2 + 36 * y + c;
+        acc[cls] += t[0] + t[36];
+      } else {
+        const double d = term[kAt3 + 18 * y + c];
+        acc[cls] += last && cls == FWD_LOW ? term[kAtLl + 8 * y + c] + d : d;
+      }
+    }
+  }
+  // beside level M of the transform: the one above it
+  template <int M>
+  __device__ __forceinline__ void beside() {
+    if (!mine) return;
+    if constexpr (M == 16 || M == 32)
+      if (2 * M == n) level<1>(false, a);
+    if constexpr (M == 8 || M == 16)
+      if (4 * M == n) level<2>(false, a);
+    if constexpr (M == 4 || M == 8)
+      if (8 * M == n) level<3>(false, a3);
+  }
+  // the piece's sum into its slot (wave_sum adds rows of lanes as the tiles do)
+  __device__ __forceinline__ void finish(bool last, gptr_wd slots) {
+    if (!mine) return;
+    if (last) level<3>(true, a3);
+    const double h = wave_sum(a[FWD_HIGH]) + row_sum(a3[FWD_HIGH]), l = wave_sum(a[FWD_LOW]) + row_sum(a3[FWD_LOW]);
+    if ((threadIdx.x & 63) == 0) slots[piece] = h + l;
+  }
+};
+
 // One analysis level of side M in LDS (A and B with row stride S), NP output
 // pairs per thread and line: rows A -> B (lanes on rows), then columns B -> A
 // (lanes on consecutive columns) with the epilogue of every detail output
 // from operands already in registers; the coarse block stays in A for the
 // next level.
-template <int M, int S, int EPI>
+template <int M, int S, int EPI, bool CANON>
 __device__ __forceinline__ void epi_level(const ResLayer& ly, const EpiDst& dst, float* A, float* B, const Filter& F,
-                                          const EpiLoad* el, double& acc) {
+                                          const EpiLoad* el, double& acc, CanonSums& cs) {
   constexpr int NP = ana_np(M), half = M / 2, lm = ilog2c(M);
   const int n = ly.n, off = ly.off;
   const float ad = ly.ad[lm - 1], inv_delta = ly.inv_delta;
@@ -2104,26 +2205,33 @@ __device__ __forceinline__ void epi_level(const ResLayer& ly, const EpiDst& dst,
       B[c * S + half + K0 + p] = d[p];
     }
   }
+  if constexpr (CANON) cs.flush();
   __syncthreads();
+  if constexpr (CANON) cs.template beside<M>();
+  const bool canon = CANON && (M >= 16 || (M == 8 && n == 32));  // of the first three levels (n = 32 or 64)
   if (mine) {  // columns and the epilogue
     float a[NP], d[NP];
+    double term[NP] = {};
     ana_line<NP, S>(B + c, M, K0, F, a, d);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int k = K0 + p;
-      if (c >= half) epi_finish(dst, EPI, off + k * n + c, ad, a[p] * inv_delta, el[2 * p], acc);
-      epi_finish(dst, EPI, off + (half + k) * n + c, ad, d[p] * inv_delta, el[2 * p + 1], acc);
+      double& t = canon ? term[p] : acc;
+      if (c >= half) epi_finish(dst, EPI, off + k * n + c, ad, a[p] * inv_delta, el[2 * p], t);
+      epi_finish(dst, EPI, off + (half + k) * n + c, ad, d[p] * inv_delta, el[2 * p + 1], t);
       A[k * S + c] = a[p];  // rows >= half of A are no longer read
     }
+    if constexpr (CANON)
+      if (canon) cs.keep(M, K0 / NP, c, NP == 2 ? term[0] + term[NP - 1] : term[0]);
   }
   __syncthreads();
 }
 
-template <int M, int S, int EPI>
+template <int M, int S, int EPI, bool CANON>
 __device__ __forceinline__ void epi_levels(const ResLayer& ly, const EpiDst& dst, float* A, float* B, int R, int m0,
-                                           const Filter& F, const LevelOps<M>& o, double& acc) {
-  if (M <= R && M > m0) epi_level<M, S, EPI>(ly, dst, A, B, F, o.l, acc);
-  if constexpr (M > 2) epi_levels<M / 2, S, EPI>(ly, dst, A, B, R, m0, F, o.next, acc);
+                                           const Filter& F, const LevelOps<M>& o, double& acc, CanonSums& cs) {
+  if (M <= R && M > m0) epi_level<M, S, EPI, CANON>(ly, dst, A, B, F, o.l, acc, cs);
+  if constexpr (M > 2) epi_levels<M / 2, S, EPI, CANON>(ly, dst, A, B, R, m0, F, o.next, acc, cs);
 }
 
 // One workgroup per (problem, layer): all analysis levels from the resident
@@ -2136,14 +2244,18 @@ __device__ __forceinline__ void epi_levels(const ResLayer& ly, const EpiDst& dst
 // Bound: one workgroup's chain; two levels of a 32 x 32 block 4.2 -> 3.8 us
 // with the layer's record read before the first store, 3.7 with the 512
 // threads that such a block has tasks for.
+// CANON: the instantiation for whole layers whose sums are the input tiles'
+// (CanonSums), in launches of their own.
 constexpr int fres_threads(int rmax) { return rmax <= 32 ? 512 : 1024; }
-template <int RMAX, int EPI>
+template <int RMAX, int EPI, bool CANON>
 __global__ __launch_bounds__(fres_threads(RMAX)) void k_fdwt_res(const ProbDev* P, const LayerDev* LD, const IoDev* IO,
                                                    const Tile* tiles, Filter F, int iter) {
   static_assert(RMAX * RMAX / 2 <= 8 * 1024, "at most 8 output pairs per thread and line at 1024 threads");
   __shared__ float A[RMAX * (RMAX + 1)];
   __shared__ float B[RMAX * (RMAX + 1)];
   __shared__ double sh[16];
+  static_assert(!CANON || RMAX <= 64, "layers of 32 x 32 and 64 x 64");
+  __shared__ double terms[CANON ? CanonSums::kWords : 1];
   const Tile t = my_tile(tiles);
   const ProbDev& pr = P[t.prob];
   const LayerDev& ld = LD[t.mask];  // the global layer index, carried by the tile
@@ -2152,6 +2264,7 @@ __global__ __launch_bounds__(fres_threads(RMAX)) void k_fdwt_res(const ProbDev* 
   constexpr int S = RMAX + 1;
   constexpr int nt = fres_threads(RMAX);
   const int ng = ld.fsteps;
+  const int levels = ld.levels;
   ResLayer ly;
   ly.n = n;
   ly.off = off;
@@ -2182,6 +2295,8 @@ __global__ __launch_bounds__(fres_threads(RMAX)) void k_fdwt_res(const ProbDev* 
     }
   };
   double acc = 0.0;
+  CanonSums cs;
+  if constexpr (CANON) cs.start(terms, n, nt);
   const EpiDst dst = epi_dst(pr, io, iter);
   if constexpr (EPI == EPI_PCG) {
     // every level's operands requested with the block: one memory round trip
@@ -2189,19 +2304,19 @@ __global__ __launch_bounds__(fres_threads(RMAX)) void k_fdwt_res(const ProbDev* 
     epi_fetch_levels<RMAX, EPI>(pr, io, iter, off, n, R, m0, ops);
     block_to_lds();
     __syncthreads();
-    epi_levels<RMAX, S, EPI>(ly, dst, A, B, R, m0, F, ops, acc);
+    epi_levels<RMAX, S, EPI, CANON>(ly, dst, A, B, R, m0, F, ops, acc, cs);
   } else {
     block_to_lds();
     {
       OneLevelOps<RMAX> top;
       epi_fetch_level<RMAX, EPI>(pr, io, iter, off, n, R, m0, top.l);
       __syncthreads();
-      if (RMAX <= R && RMAX > m0) epi_level<RMAX, S, EPI>(ly, dst, A, B, F, top.l, acc);
+      if (RMAX <= R && RMAX > m0) epi_level<RMAX, S, EPI, CANON>(ly, dst, A, B, F, top.l, acc, cs);
     }
     if constexpr (RMAX > 2) {
       LevelOps<RMAX / 2> rest;
       epi_fetch_levels<RMAX / 2, EPI>(pr, io, iter, off, n, R, m0, rest);
-      epi_levels<RMAX / 2, S, EPI>(ly, dst, A, B, R, m0, F, rest, acc);
+      epi_levels<RMAX / 2, S, EPI, CANON>(ly, dst, A, B, R, m0, F, rest, acc, cs);
     }
   }
   const float adll = ad_ll;
@@ -2209,11 +2324,29 @@ __global__ __launch_bounds__(fres_threads(RMAX)) void k_fdwt_res(const ProbDev* 
     const int r = e / m0, c = e - r * m0;
     const int pos = off + r * n + c;
     const EpiLoad l = epi_fetch(pr, io, EPI, iter, pos);
-    epi_finish(dst, EPI, pos, adll, A[r * S + c] * ly.inv_delta, l, acc);
+    if (CANON && levels == 3) {  // the third level's own coarse band
+      double ta = 0.0;
+      epi_finish(dst, EPI, pos, adll, A[r * S + c] * ly.inv_delta, l, ta);
+      cs.term[CanonSums::kAtLl + 8 * r + c] = ta;
+    } else {
+      epi_finish(dst, EPI, pos, adll, A[r * S + c] * ly.inv_delta, l, acc);
+    }
   }
   if (EPI == EPI_PCG || EPI == EPI_RHS || EPI == EPI_RHSQ) {
-    const double s = block_sum(acc, sh, nt);
-    if (threadIdx.x == 0) ((gptr_wd)dots)[(long)dot_group_of(EPI, iter) * n_dots + t.slot] = s;
+    const gptr_wd slots = (gptr_wd)dots + (long)dot_group_of(EPI, iter) * n_dots + t.slot;
+    if constexpr (CANON) {
+      // the deeper levels and their coarse band: wave 0 alone forms them
+      const double s = wave_sum(acc);
+      if (threadIdx.x == 0 && levels > 3) slots[(n >> 5) * (n >> 5)] = s;
+      if (levels == 3) {
+        cs.flush();
+        __syncthreads();
+      }
+      cs.finish(levels == 3, slots);
+    } else {
+      const double s = block_sum(acc, sh, nt);
+      if (threadIdx.x == 0) slots[0] = s;
+    }
   }
 }
 
@@ -4131,15 +4264,18 @@ void launch_fdwt_glob(const LaunchArgs& a, const Tile* tiles, int ntiles, int ep
   else
     k_fdwt_glob<<<ntiles, 256, 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, epi, iter, step);
 }
-template <int RMAX>
+template <int RMAX, bool CANON>
 static void launch_fdwt_res_r(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter) {
+#define FEWHA_FR(E, CANON) \
+  k_fdwt_res<RMAX, E, CANON><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter)
   switch (epi) {
-    case EPI_APPLYM: k_fdwt_res<RMAX, EPI_APPLYM><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    case EPI_PCG: k_fdwt_res<RMAX, EPI_PCG><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    case EPI_RHS: k_fdwt_res<RMAX, EPI_RHS><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    case EPI_RHSQ: k_fdwt_res<RMAX, EPI_RHSQ><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
-    default: k_fdwt_res<RMAX, EPI_PLAIN><<<ntiles, fres_threads(RMAX), 0, a.stream>>>(a.P, a.L, a.IO, tiles, a.F, iter); break;
+    case EPI_APPLYM: FEWHA_FR(EPI_APPLYM, false); break;  // no sums
+    case EPI_PCG: FEWHA_FR(EPI_PCG, CANON); break;
+    case EPI_RHS: FEWHA_FR(EPI_RHS, CANON); break;
+    case EPI_RHSQ: FEWHA_FR(EPI_RHSQ, CANON); break;
+    default: FEWHA_FR(EPI_PLAIN, false); break;
   }
+#undef FEWHA_FR
 }
 template <int T, int NT>
 static void launch_fdwt_dir_t(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter, int from_in) {
@@ -4163,11 +4299,14 @@ void launch_fdwt_dir(const LaunchArgs& a, const Tile* tiles, int ntiles, int til
 void launch_fdwt_res(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter) {
   if (ntiles <= 0) return;
   if (a.fres_max <= 32)
-    launch_fdwt_res_r<32>(a, tiles, ntiles, epi, iter);
+    launch_fdwt_res_r<32, false>(a, tiles, ntiles, epi, iter);
   else if (a.fres_max <= 64)
-    launch_fdwt_res_r<64>(a, tiles, ntiles, epi, iter);
+    launch_fdwt_res_r<64, false>(a, tiles, ntiles, epi, iter);
   else
-    launch_fdwt_res_r<128>(a, tiles, ntiles, epi, iter);
+    launch_fdwt_res_r<128, false>(a, tiles, ntiles, epi, iter);
+}
+void launch_fdwt_canon(const LaunchArgs& a, const Tile* tiles, int ntiles, int epi, int iter) {
+  if (ntiles > 0) launch_fdwt_res_r<64, true>(a, tiles, ntiles, epi, iter);
 }
 void launch_pgamma(const LaunchArgs& a, const Tile* tiles, int ntiles, int mode) {
   if (ntiles <= 0) return;

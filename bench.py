@@ -642,7 +642,7 @@ def main():
     from paper_2202_11945_amd import autotune
     default = {"dwt_resident": 128, "pt_rows": 4, "streams": 1, "cached": None}
     tune_b = autotune.tune(ctxs, args.iters) if not args.no_tune else default
-    tune_1 = autotune.tune([c0], args.iters) if not args.no_tune else default
+    tune_1 = autotune.tune([c0], args.iters) if not args.no_tune else dict(default, pt_rows=0)
     H = B // 2
     tune_h = (autotune.tune(ctxs[:H], args.iters) if not args.no_tune else default) if H >= 1 else None
     print("[bench] tuning: batch %s, half %s, single %s" % (tune_b, tune_h, tune_1), file=sys.stderr,

@@ -422,7 +422,8 @@ FEWHA_API void fewha_batch_destroy(fewha_batch* b);
  * launches.  It must be at least every layer's coarsest block (n >> levels),
  * else FEWHA_EINVAL when the plan is built.
  * pt_rows: node rows per thread of the propagation adjoint P^T (4 or 8;
- * 0 = default 4); a tile is 64 node columns by 4 * pt_rows rows.  More rows
+ * 0 = default: 4, in split tiles where the launch has few of them, see
+ * pt_split); a tile is 64 node columns by 4 * pt_rows rows.  More rows
  * put more independent loads in flight per thread, at more registers.
  * streams: batches only (a context takes 0 or 1).  fewha_batch_reconstruct
  * runs the batch as this many contiguous parts of its problem list (1 to 4,
@@ -443,8 +444,9 @@ FEWHA_API void fewha_batch_destroy(fewha_batch* b);
  * (sensor i to wave i mod 4 or 8, every sensor's sums added in sensor order,
  * so the values are bitwise those of unsplit tiles), that much less of the
  * serial chain of sensors per wave; for launches with few tiles, such as one
- * problem's frame.  Needs pt_rows 0 or 4.  0 = default: split where the launch has few
- * tiles.
+ * problem's frame.  Needs pt_rows 0 or 4.  0 = not split where pt_rows is
+ * given; with pt_rows 0 too, split in launches of few tiles (as the fitting
+ * step's tiles on the DM grids are by themselves, except with pt_rows 8).
  * glob_fuse: 1 = a layer with two or more global levels (side above twice
  * dwt_resident) runs its last two inverse levels in one launch: each output
  * tile synthesizes the part of the inner level it needs itself (about 27 %

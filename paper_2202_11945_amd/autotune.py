@@ -7,7 +7,8 @@ Six tunables:
   run as tiled global passes.  A large R means few, heavy workgroups (a
   MAORY-like layer of 128 x 128 is one workgroup); a small R spreads the same
   levels over many more workgroups at the cost of one launch per extra level.
-* the node rows per thread of the propagation adjoint (4 or 8): more rows
+* the node rows per thread of the propagation adjoint (4 or 8, each given
+  explicitly, so that its tiles are not split by their number): more rows
   put more independent loads in flight per thread, at more registers.
 * for the best of those, the propagation adjoint's sensor lists split over
   the waves of 4-row tiles (pt_split), which shortens each wave's serial

@@ -507,6 +507,9 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
     err = "tuning: the resident transform side must be 32, 64 or 128";
     return FEWHA_EINVAL;
   }
+  // rows or the split asked for: as asked for; neither: by the number of tiles
+  const bool auto_split = pt_rows == 0 && pt_split == 0;
+  if (pt_rows == 0) pt_rows = 4;
   if (pt_rows != 4 && pt_rows != 8) {
     err = "tuning: the propagation adjoint takes 4 or 8 node rows per thread";
     return FEWHA_EINVAL;
@@ -534,14 +537,15 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
     err = "tuning: four workgroups per layer need every layer's resident side >= 16 and >= 2 (n >> levels)";
     return FEWHA_EINVAL;
   }
-  // propagation-adjoint tiles, split or not: on request, or while split tiles are few
+  // propagation-adjoint tiles, split or not: on request, or (auto_split) while split tiles are few;
+  // those of the fitting step's DM grids on request or by their own number
   long split_tiles = 0, fit_split_tiles = 0;
   auto tiles_of = [](int n) { return (long)cdiv(n, kBandRows) * cdiv(n, kPtW); };
   for (const HostModel* m : models) {
     for (const LayerHost& lh : m->layers) split_tiles += tiles_of(lh.d.n);
     for (const fewha_dm_desc& dm : m->fit.dms) fit_split_tiles += tiles_of(dm.n_act);
   }
-  const bool split_pt = pt_split || (pt_rows == 4 && split_tiles <= kPtSplitTiles);
+  const bool split_pt = pt_split || (auto_split && split_tiles <= kPtSplitTiles);
   const bool split_fit = pt_split || (pt_rows == 4 && fit_split_tiles <= kPtSplitTiles);
   // node rows of a tile, and its band records per wave
   const int kPtH = split_pt ? kBandRows : 4 * pt_rows, kFitH = split_fit ? kBandRows : 4 * pt_rows;
@@ -2366,7 +2370,7 @@ fewha_status fewha_finalize(fewha_ctx* c) {
   if (c->device >= 0) {
     std::vector<const HostModel*> ms{&c->m};
     s = build_plan(c->plan, ms, c->device, c->m.tune_res > 0 ? c->m.tune_res : kResMax,
-                   c->m.tune_pt_rows > 0 ? c->m.tune_pt_rows : 4, c->m.tune_split, c->m.tune_pt_split,
+                   c->m.tune_pt_rows, c->m.tune_split, c->m.tune_pt_split,
                    c->m.tune_glob_fuse, c->err);
     if (s != FEWHA_OK) return s;
     c->plan->coarse_side = c->coarse_side;
@@ -2698,7 +2702,7 @@ fewha_status fewha_batch_create_tuned(fewha_batch** out, fewha_ctx* const* ctxs,
   if (!b) return FEWHA_ENOMEM;
   b->ctxs.assign(ctxs, ctxs + n);
   const int res = (t && t->dwt_resident > 0) ? t->dwt_resident : kResMax;
-  const int rows = (t && t->pt_rows > 0) ? t->pt_rows : 4;
+  const int rows = t ? t->pt_rows : 0;
   const int split = t ? t->res_split : 0;
   const int pt_split = t ? t->pt_split : 0;
   const int glob_fuse = t ? t->glob_fuse : 0;

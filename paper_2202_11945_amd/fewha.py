@@ -45,7 +45,7 @@ def _ptr64(t, n):
 def _tuning(tuning):
     """fewha_tuning from an int (the resident transform side) or a dict with
     keys dwt_resident, pt_rows, streams, res_split, pt_split and glob_fuse
-    (missing = default)."""
+    (missing = default; pt_rows without pt_split: unsplit tiles)."""
     t = _abi.fewha_tuning()
     if isinstance(tuning, dict):
         t.dwt_resident = int(tuning.get("dwt_resident", 0))

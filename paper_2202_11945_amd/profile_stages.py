@@ -23,7 +23,7 @@ def main():
     ap.add_argument("--iters", type=int, default=4)
     ap.add_argument("--reps", type=int, default=5)
     ap.add_argument("--res", type=int, default=0, help="resident transform side (0 = default)")
-    ap.add_argument("--pt-rows", type=int, default=0, help="node rows per thread of P^T (0 = default)")
+    ap.add_argument("--pt-rows", type=int, default=0, help="node rows per thread of P^T (0 = default, split tiles where few)")
     ap.add_argument("--split", type=int, default=0, help="resident inverse levels: 0 default, 1 or 4 workgroups")
     ap.add_argument("--pt-split", type=int, default=0, help="propagation adjoint: 1 = sensor lists split over waves")
     ap.add_argument("--glob-fuse", type=int, default=0, help="1 = a layer's top two global levels in one launch")

@@ -1,0 +1,43 @@
+"""The launch shapes that a tuning asks for are the ones that run: the stages'
+workgroups tell which kernels a plan has, and the frames agree with those of
+the other shapes (bitwise where the header says so) or with the oracle."""
+
+import numpy as np
+import pytest
+
+from synthetic import get_config
+from test_gpu_batch_rules import frames, same
+from test_gpu_parity import synth_slopes, to_dev
+
+pytestmark = pytest.mark.gpu
+
+STAGE = {"IDWT_RES": 0, "IDWT_GLOB": 1, "P_T": 4, "FDWT_GLOB": 5, "FDWT_RES": 6}
+
+
+def workgroups(batch, stage):
+    return batch.time_stage(STAGE[stage], reps=1)[1]
+
+
+def pt_tiles(cfg, rows):
+    return sum(-(-l["n"] // rows) * -(-l["n"] // 64) for l in cfg["layers"])
+
+
+# narrow and wide pairs (the 37 m system has up to six corners per node), and a fitting step
+@pytest.mark.parametrize("name", ["maory_like", "paper_maory", "small_fit"])
+def test_unsplit_propagation_tiles_on_request(gpu_lib, systems, name):
+    print("\n[gpu-tune] unsplit tiles", name, flush=True)
+    cfg = get_config(name)
+    ctx = gpu_lib.Context(cfg, device=0)
+    s = [to_dev(synth_slopes(systems(name), 0))]
+    out = {}
+    # node rows of a tile: 16 and 32 where rows are asked for, 4 split ones by default and on request
+    for key, tuning, rows in (("rows 4", {"pt_rows": 4}, 16), ("rows 8", {"pt_rows": 8}, 32), ("default", None, 4),
+                              ("split", {"pt_split": 1}, 4), ("split 4", {"pt_rows": 4, "pt_split": 1}, 4)):
+        batch = gpu_lib.Batch([ctx], tuning=tuning)
+        out[key] = frames(batch, s, cfg["iters"])[0]
+        assert workgroups(batch, "P_T") == pt_tiles(cfg, rows), key
+        batch.close()
+    for key, got in out.items():
+        assert same(got, out["default"]), key
+    assert np.isfinite(out["default"][1].cpu().numpy()).all()
+    ctx.close()

@@ -35,7 +35,7 @@ static_assert(kSolveCheck == kDotRing, "a captured block of steps replays on the
 struct Transform {
   int inverse = 0;
   bool forward = false;
-  bool canon = false;  // forward level by level, with the sums of the tiles
+  bool canon = false;  // forward: whole layers in one launch, with the sums of the tiles
 };
 
 int ilog2i(int n) {
@@ -634,10 +634,10 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
       ld.res = std::min(ld.n, res);
       ld.off = m.layer_off[l];
       ld.n_glob_levels = ilog2i(ld.n / ld.res);
-      ld.fres = how.forward ? ld.n / 8 : ld.res;
-      ld.fsteps = how.forward ? 1 : ld.n_glob_levels;
+      ld.fres = how.forward ? ld.n / 8 : how.canon ? ld.n : ld.res;
+      ld.fsteps = how.forward ? 1 : how.canon ? 0 : ld.n_glob_levels;
       if (how.inverse == 0) P.ires_max = std::max(P.ires_max, ld.res);
-      P.fres_max = std::max(P.fres_max, ld.fres);
+      if (!how.canon) P.fres_max = std::max(P.fres_max, ld.fres);
       ld.tmp_off = tmp_total;
       tmp_total += tmp_words(ld, how.forward);
       ld.inv_delta = (float)(1.0 / lh.delta);
@@ -785,7 +785,7 @@ fewha_status build_plan(Plan*& out, const std::vector<const HostModel*>& models,
         // with glob_fuse a layer's first two global levels are one tile at
         // step 0 (its inner coarse block goes where step 1 would put it)
         const bool ffuse = glob_fuse && ld.n_glob_levels >= 2;
-        if (!how.forward && !(ffuse && s == 1))
+        if (!how.forward && !how.canon && !(ffuse && s == 1))
           for (int ty = 0; ty < tq; ++ty)
             for (int tx = 0; tx < tq; ++tx)
               t_fdwt_glob[s].push_back({k, l, ty, tx, slot++, ilog2i(mf), pd.layer0 + l, (ffuse && s == 0) ? 1 : 0});

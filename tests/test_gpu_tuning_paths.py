@@ -41,3 +41,20 @@ def test_unsplit_propagation_tiles_on_request(gpu_lib, systems, name):
         assert same(got, out["default"]), key
     assert np.isfinite(out["default"][1].cpu().numpy()).all()
     ctx.close()
+
+
+# whole layers of 64 x 64 (vlt_like), tiles, three levels
+@pytest.mark.parametrize("name", ["vlt_like", "mid", "small"])
+def test_shapes_of_the_level_by_level_kernels_choose_nothing_elsewhere(gpu_lib, systems, name):
+    print("\n[gpu-tune] tiled", name, flush=True)
+    cfg = get_config(name)
+    ctx = gpu_lib.Context(cfg, device=0)
+    s = [to_dev(synth_slopes(systems(name), 0))]
+    seen = []
+    for tuning in (None, 32, {"dwt_resident": 32, "glob_fuse": 1}, {"dwt_resident": 64, "res_split": 4}):
+        batch = gpu_lib.Batch([ctx], tuning=tuning)
+        seen.append((frames(batch, s, cfg["iters"])[0], [workgroups(batch, k) for k in STAGE if k != "P_T"]))
+        batch.close()
+    for got, wgs in seen[1:]:
+        assert same(got, seen[0][0]) and wgs == seen[0][1]
+    ctx.close()

@@ -2,11 +2,14 @@
 
 Six tunables:
 
-* the resident transform side R (32, 64 or 128): the resident DWT kernels
-  keep every level up to R x R in one workgroup's LDS, and the levels above R
-  run as tiled global passes.  A large R means few, heavy workgroups (a
-  MAORY-like layer of 128 x 128 is one workgroup); a small R spreads the same
-  levels over many more workgroups at the cost of one launch per extra level.
+* the resident transform side R (32, 64 or 128) of the level-by-level
+  transforms: the resident DWT kernels keep every level up to R x R in one
+  workgroup's LDS, and the levels above R run as tiled global passes.  A large
+  R means few, heavy workgroups (a layer of 128 x 128 is one workgroup); a
+  small R spreads the same levels over many more workgroups at the cost of one
+  launch per extra level.  R, glob_fuse and res_split choose nothing for
+  problems whose transforms are tiles (level_by_level), and are not timed for
+  batches of such problems alone.
 * the node rows per thread of the propagation adjoint (4 or 8, each given
   explicitly, so that its tiles are not split by their number): more rows
   put more independent loads in flight per thread, at more registers.
@@ -72,6 +75,21 @@ def split_allowed(ctxs, res):
             if R < 16 or R < 2 * (l["n"] >> l["levels"]):
                 return False
     return True
+
+
+def level_by_level(ctxs):
+    """Whether some problem keeps a level-by-level transform, whose shapes R,
+    glob_fuse and res_split choose (the library's rule: tiles need layers of
+    32 a side and 3 to 5 levels, or of 64 and 3 to 6, for the inverse, and of 32
+    to 1024 and 3 levels for the forward transform).  A context without a
+    configuration counts as one."""
+    for c in ctxs:
+        layers = getattr(c, "cfg", {"layers": [{"n": 0, "levels": 0}]})["layers"]
+        inverse = any(all(l["n"] >= side and 3 <= l["levels"] <= deepest for l in layers)
+                      for side, deepest in ((32, 5), (64, 6)))
+        if not inverse or not all(32 <= l["n"] <= 1024 and l["levels"] >= 3 for l in layers):
+            return True
+    return False
 
 
 def fusable(ctxs, res):
@@ -150,8 +168,12 @@ def tune(ctxs, iters, steps=10, use_cache=True):
         rec = dict(db[key])
         rec["cached"] = True
         return rec
-    us = {(r, pr): time_plan(ctxs, iters, {"dwt_resident": r, "pt_rows": pr}, steps=steps)
-          for r in admissible(ctxs) for pr in PT_ROWS}
+    shaped = level_by_level(ctxs)
+    us = {}
+    for r in admissible(ctxs):
+        for pr in PT_ROWS:
+            same = None if shaped else us.get((admissible(ctxs)[0], pr))  # one plan at any resident side
+            us[(r, pr)] = same or time_plan(ctxs, iters, {"dwt_resident": r, "pt_rows": pr}, steps=steps)
     best = min(us, key=us.get)
     # keep the default shapes unless another choice is clearly faster: near
     # ties would otherwise flip between runs on timing noise
@@ -171,7 +193,7 @@ def tune(ctxs, iters, steps=10, use_cache=True):
     cur = pts_us[shape["pt_split"]]
     fuse_us = {}
     for r in admissible(ctxs):
-        if fusable(ctxs, r):
+        if shaped and fusable(ctxs, r):
             fuse_us[r] = time_plan(ctxs, iters, dict(shape, dwt_resident=r, glob_fuse=1), steps=steps)
     if fuse_us:
         rf = min(fuse_us, key=fuse_us.get)
@@ -181,7 +203,7 @@ def tune(ctxs, iters, steps=10, use_cache=True):
     # then the resident inverse levels in four workgroups per layer against
     # the default one
     split_us = {0: cur}
-    if split_allowed(ctxs, shape["dwt_resident"]):
+    if shaped and split_allowed(ctxs, shape["dwt_resident"]):
         split_us[4] = time_plan(ctxs, iters, dict(shape, res_split=4), steps=steps)
     split = min(split_us, key=split_us.get)
     if split_us[split] > (1.0 - MARGIN) * split_us[0]:

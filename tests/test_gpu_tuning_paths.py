@@ -8,6 +8,7 @@ import pytest
 from synthetic import get_config
 from test_gpu_batch_rules import frames, same
 from test_gpu_parity import synth_slopes, to_dev
+from test_gpu_transforms import layered
 
 pytestmark = pytest.mark.gpu
 
@@ -57,4 +58,22 @@ def test_shapes_of_the_level_by_level_kernels_choose_nothing_elsewhere(gpu_lib, 
         batch.close()
     for got, wgs in seen[1:]:
         assert same(got, seen[0][0]) and wgs == seen[0][1]
+    ctx.close()
+
+
+# the autotuner's rule against the library's: a resident side of 32 changes
+# the transforms' workgroups where some layer above it is level by level
+@pytest.mark.parametrize("grids", [[(32, 3), (64, 5)], [(64, 6), (128, 3)], [(32, 3), (64, 6)], [(64, 4)], [(128, 2)],
+                                   [(16, 3), (64, 3)], [(1024, 5)], [(2048, 6)], [(128, 7)]])
+def test_the_autotuners_rule_is_the_librarys(gpu_lib, grids):
+    from paper_2202_11945_amd import autotune
+    print("\n[gpu-tune] rule", grids, flush=True)
+    ctx = gpu_lib.Context(layered(grids), device=0)
+    wgs = []
+    for res in (128, 32):
+        batch = gpu_lib.Batch([ctx], tuning=res)
+        frames(batch, [to_dev(np.zeros(ctx.n_slopes))], 1)
+        wgs.append([workgroups(batch, k) for k in STAGE if k != "P_T"])
+        batch.close()
+    assert (wgs[0] != wgs[1]) == autotune.level_by_level([ctx])
     ctx.close()

@@ -233,7 +233,7 @@ def measured_traffic(stage, batch, tuning):
     batch size or other launch shapes."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hip", "kernels.h", "fewha_internal.h", "api.cpp"):
+    for f in ("kernels.hip", "kernels.h", "fwd_tile.h", "fewha_internal.h", "api.cpp"):
         h.update(open(os.path.join(ROOT, "paper_2202_11945_amd", "csrc", f), "rb").read())
     sha = h.hexdigest()[:16]
     tune = "%d/%d/%d/%d/%d" % (tuning["dwt_resident"], tuning["pt_rows"], tuning.get("res_split", 0),

@@ -270,7 +270,7 @@ FEWHA_API fewha_status fewha_reconstruct_streamed(fewha_ctx* ctx, const float* h
  * overlap on one device (other streams, other threads, other contexts) race
  * and must be ordered by the caller.  FEWHA_EINVAL if the context's frame
  * needs more than 16 MiB of work buffers (about 2.5 MB for the 39 m
- * MAORY-like system, 8.0 MB for 9 layers of up to 256 x 256) or uses the
+ * MAORY-like system, 7.9 MB for 9 layers of up to 256 x 256) or uses the
  * DM fitting step, augmentation or the true-residual restart. */
 FEWHA_API fewha_status fewha_reconstruct_noalloc(fewha_ctx* ctx, const float* slopes, float* state,
                                                  float* layers_out, float* dm_out, int iters);

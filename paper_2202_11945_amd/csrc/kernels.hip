@@ -1070,9 +1070,9 @@ __global__ __launch_bounds__(256) void k_idwt_glob2(const ProbDev* P, const Laye
 // Bound: a chain of memory round trips (tile, records, coefficients) and two
 // barriers per level for few tiles, the windows' loads for many.  T = 32
 // loads 1.69 coefficients per output, T = 64 1.30, with a quarter of the
-// workgroups (see dir_tile in api.cpp for the choice).  A 39 m problem takes
-// 6.0 us and 32 of them 19.8 (58 MB, 2.9 TB/s), where the level-by-level
-// kernels took 17.0 and 27.4.
+// workgroups (see transforms_of in api.cpp for the choice).  A 39 m problem
+// takes 6.0 us and 32 of them 19.8 (62.9 MB with every operand once, 3.2
+// TB/s), where the level-by-level kernels took 17.0 and 27.4.
 template <int T>
 struct DirWin {
   static constexpr int kLevels = T == 64 ? 6 : 5;
@@ -1695,12 +1695,13 @@ __global__ __launch_bounds__(256) void k_fdwt_glob2(const ProbDev* P, const Laye
 // next level's window and the details with their epilogue, whose PCG operand
 // is requested with the input.  Layers of three levels are done then; of
 // deeper ones the coarse block (side n / 8) goes to scratch for k_fdwt_res.
-// The sums are those of the level-by-level kernels, in the same order.
+// The outputs' sums are those of the level-by-level kernels, in the same
+// order; the inner products have a partial per 32 x 32 piece (see FwdWin).
 //
 // Bound: memory round trips and five barriers for few tiles; for many the
 // window (3.5 samples per input at T = 32, 2.1 at 64) against a quarter of
-// the workgroups.  A 39 m problem takes 4.5 us and 32 of them 10.8 (38 MB, 3.5
-// TB/s), and k_fdwt_res 3.8 and 4.2, where the level-by-level kernels took
+// the workgroups.  A 39 m problem takes 4.4 us and 32 of them 10.7 (38 MB, 3.5
+// TB/s), and k_fdwt_res 3.7 and 4.0, where the level-by-level kernels took
 // 15.0 and 19.8 in all.
 
 // Epilogue of one output from its unscaled sum a, with the rounding of the
